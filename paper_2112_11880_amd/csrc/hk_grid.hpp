@@ -119,6 +119,157 @@ __device__ __forceinline__ bool barrier_last(GridBar* bar, unsigned& epoch, F&& 
   return s_stop != 0;
 }
 
+// ------------------------------------------------- barrier that sums to all
+//
+// The resident solvers' barrier: every workgroup publishes its NV partial
+// sums as 8-byte words and reads every workgroup's words itself, so one trip
+// through memory is both the barrier and the reduction, and every workgroup
+// holds the totals (summed in one order, so the same bits everywhere).  On
+// MI355X it takes 1.9 us with 20 workgroups, 2.4 with 64, 3.5 with 128 and
+// 5.2 with 256 (three sums), against 9.4 us for the flag barrier above with
+// its release fence, workgroup 0's callback and the second trip.
+//
+//  - A word is its own flag: kSumEmpty, a NaN no sum is published as, means
+//    "not there yet".  A workgroup that has seen every word of epoch e knows
+//    that all have finished reading epoch e - 1 and empties its own words of
+//    that epoch; with kSumSets sets in turn they are used again at e + 3.
+//  - Each word is published kSumReps times and a workgroup reads copy
+//    blockIdx.x % kSumReps: 256 workgroups polling one copy slow the stores
+//    to it (64 workgroups: 3.2 us with one copy, 2.4 with eight).
+//  - No release fence: what the other workgroups read (publish below) is
+//    stored past the L2 at agent scope, and every wave waits for its stores
+//    before the words are published.  The plain-store form with an L2
+//    write-back took 13-17 us per barrier and gather at 256 workgroups,
+//    against 7.5-10.
+//  - The acquire (an L1 and L2 invalidate) is thread 0's alone, as above.  It
+//    may run before another workgroup has arrived: what it must drop are
+//    lines of a published vector's previous contents, and a vector is stored
+//    only after a barrier that follows its last reads, so no workgroup reads
+//    it between that barrier and the end of this one.
+constexpr int kSumSets = 4;
+constexpr int kSumReps = 8;
+constexpr int kSumWords = 4;    // at most this many sums
+constexpr int kSumBlocks = 256; // at most this many workgroups
+constexpr size_t kSumSetWords = (size_t)kSumReps * kSumWords * kSumBlocks;
+constexpr unsigned long long kSumEmpty = 0x7ff8dead0000beefull;
+
+struct GridSum {
+  unsigned long long* words;      // kSumSets * kSumSetWords, all kSumEmpty at launch
+  int* abort;                     // 0 at launch
+  unsigned long long spin_limit;  // wall-clock ticks a wait may take before it aborts
+};
+
+__device__ __forceinline__ void st_agent_u64(unsigned long long* p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Stores element i of a vector that other workgroups read after the next
+// barrier: at agent scope, one 16- or 8-byte store.
+__device__ __forceinline__ void publish(double2* p, unsigned i, double2 v) {
+  const nd2 q = {v.x, v.y};
+  asm volatile("global_store_dwordx4 %0, %1, %2 sc1" ::"v"(i * (unsigned)sizeof(v)), "v"(q), "s"(p) : "memory");
+}
+__device__ __forceinline__ void publish(float2* p, unsigned i, float2 v) {
+  const nf2 q = {v.x, v.y};
+  asm volatile("global_store_dwordx2 %0, %1, %2 sc1" ::"v"(i * (unsigned)sizeof(v)), "v"(q), "s"(p) : "memory");
+}
+
+// v + (v of the lane the DPP control names; 0 where there is none)
+template <int CTRL> __device__ __forceinline__ double dpp_add(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// Sum over the wave, valid in lane 63: shifts by 1, 2, 4, 8 within the rows
+// of 16 lanes, then row totals passed on (row_bcast 15 and 31).
+__device__ __forceinline__ double wave_sum63(double v) {
+  v = dpp_add<0x111>(v);
+  v = dpp_add<0x112>(v);
+  v = dpp_add<0x114>(v);
+  v = dpp_add<0x118>(v);
+  v = dpp_add<0x142>(v);
+  return dpp_add<0x143>(v);
+}
+
+// One barrier of a kernel of NT threads per workgroup and at most kSumBlocks
+// workgroups: v (each thread's partial sums) becomes the totals over the
+// grid, in every thread.  `epoch` starts at 0 and prev_nv at 0.  lds: room
+// for kSumWords * (NT / 64 + 4) doubles, used by nothing else.  Returns true
+// if the kernel must stop (a wait passed the limit here or elsewhere).  All
+// threads of every workgroup call it.
+template <int NV, int NT>
+__device__ __forceinline__ bool grid_sum(const GridSum& gs, unsigned& epoch, int& prev_nv, double (&v)[NV],
+                                         double* lds) {
+  static_assert(NV >= 1 && NV <= kSumWords && NT >= kSumBlocks, "sums and pollers");
+  constexpr int W = NT / kWave;
+  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  const int G = gridDim.x;
+  double* totals = lds + kSumWords * W;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const double s = wave_sum63(v[k]);
+    if (lane == kWave - 1) lds[k * W + w] = s;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's published elements
+  __syncthreads();
+  unsigned long long* set = gs.words + (epoch % kSumSets) * kSumSetWords;
+  unsigned long long* old = gs.words + ((epoch + kSumSets - 1) % kSumSets) * kSumSetWords;
+  if (threadIdx.x < NV * kSumReps) {
+    const int k = threadIdx.x % NV, rep = threadIdx.x / NV;
+    double s = 0;
+#pragma unroll
+    for (int j = 0; j < W; ++j) s += lds[k * W + j];
+    // any NaN goes out as the one quiet NaN, never as kSumEmpty
+    const unsigned long long bits = s == s ? (unsigned long long)__double_as_longlong(s) : 0x7ff8000000000000ull;
+    st_agent_u64(set + (size_t)(rep * kSumWords + k) * kSumBlocks + blockIdx.x, bits);
+  }
+  bool ok = true;
+  double part[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) part[k] = 0;
+  if ((int)threadIdx.x < G) {
+    const unsigned long long* rd = set + (size_t)(blockIdx.x % kSumReps) * kSumWords * kSumBlocks + threadIdx.x;
+    const unsigned long long t0 = wall_clock64();
+    unsigned long long q[NV];
+    for (int spins = 0;; ++spins) {
+      bool all = true;
+#pragma unroll
+      for (int k = 0; k < NV; ++k)
+        q[k] = __hip_atomic_load(rd + k * kSumBlocks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int k = 0; k < NV; ++k) all = all && q[k] != kSumEmpty;
+      if (all) break;
+      if (wall_clock64() - t0 > gs.spin_limit) atomicExch(gs.abort, 1);
+      if ((spins & 15) == 15 || wall_clock64() - t0 > gs.spin_limit) {
+        if (ld_relaxed_i32(gs.abort)) { ok = false; break; }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < NV; ++k) part[k] = __longlong_as_double((long long)q[k]);
+  }
+  if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  if (w < kSumBlocks / kWave) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const double s = wave_sum63(part[k]);
+      if (lane == kWave - 1) totals[k * 4 + w] = s;
+    }
+  }
+  const int stop = __syncthreads_or(!ok);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    v[k] = totals[k * 4] + totals[k * 4 + 1] + totals[k * 4 + 2] + totals[k * 4 + 3];
+  }
+  if ((int)threadIdx.x < prev_nv * kSumReps) {
+    const int k = threadIdx.x % prev_nv, rep = threadIdx.x / prev_nv;
+    st_agent_u64(old + (size_t)(rep * kSumWords + k) * kSumBlocks + blockIdx.x, kSumEmpty);
+  }
+  prev_nv = NV;
+  ++epoch;
+  return stop != 0;
+}
+
 // Host: the spin limit of a launch, kSpinLimitTicks unless the environment
 // variable HK_BARRIER_SPIN_TICKS holds a positive count (tests use a tiny
 // one to drive the abort path).

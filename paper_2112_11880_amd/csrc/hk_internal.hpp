@@ -80,6 +80,8 @@ struct hk_csr_s {
   // launch shapes of the solver's fused SpMV+dot kernels, tuned on the
   // first solve of a tuned handle ([0] complex128, [1] complex64)
   hk::SpmvPlan dot_plan[2];
+  // a launch shape was set by the caller: the solvers use it and nothing else
+  bool plan_fixed = false;
   // pinned host words the solver reads its status through
   int* pinned = nullptr;
 };
@@ -90,4 +92,19 @@ int spmv_tiles(const hk_csr_s* A, int L, int U);
 // and stores the fastest in A->plan (cached per matrix shape and dtype).
 int spmv_autotune(hk_csr_s* A, hipStream_t s);
 int default_grid(int ntiles);
+
+// Resident solves (hk_resident.hip): one cooperative launch that keeps the
+// matrix in registers.
+struct ResShape {
+  int entries = 0;  // entries held per row (0: the matrix does not fit)
+  int rpt = 0;      // rows per thread
+  int threads = 0;  // threads per workgroup
+  int rows = 0;     // rows per workgroup
+  int grid = 0;     // workgroups
+};
+// The shape for A's pattern with values of precision prec (0 complex128, 1
+// complex64) and method (HK_BICGSTAB or HK_TFQMR).
+ResShape resident_shape(const hk_csr_s* A, int prec, int method);
+// Words and abort flag of its barriers, in the solver workspace.
+size_t resident_scratch_bytes();
 }

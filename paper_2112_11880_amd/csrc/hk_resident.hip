@@ -1,0 +1,619 @@
+// hk_resident.hip -- Jacobi BiCGStab and TFQMR in one cooperative launch that
+// keeps the matrix in registers (gfx950).
+//
+// A system of up to a few hundred thousand rows fits the register files of
+// the chip: 256 CUs hold 128 MB of them, and the 27 MB of complex128 values of
+// a 48^3 mesh (117,649 rows) take 75 registers of each of 117,649 threads, one
+// row per thread.  Launched as separate kernels (hk_solver.hip) an iteration
+// of such a system is bound by its eight launches and by the chains of
+// dependent loads in each -- 28 us on 4,913 rows, 46-52 us on 117,649, where
+// its bytes alone would take 0.3 and 9 us.  Here an iteration is three (TFQMR:
+// two) barriers that also sum, grid_sum in hk_grid.hpp, and between them
+// row-local arithmetic and the products' gathers: 9.6 us on 4,913 rows, 18.3
+// on 117,649 (5 us per barrier, 3 us per gather of two vectors, which bound it
+// now), TFQMR on 70,224 rows of 27 entries 66 -> 16 us, complex64 BiCGStab on
+// 279,496 rows 60 -> 26.5 us.
+//
+// What keeps the barriers so few: a product's operand is a combination, known
+// only after the barrier's scalars, of vectors known before it, and every
+// thread forms it where it gathers.
+//   BiCGStab  p = r + beta q, q = p - omega v:  v = Ahat p gathers r and q
+//             s = r - alpha v:                  t = Ahat s gathers r and v
+//   TFQMR     y2 = y1 - alpha v:                u2 = Ahat y2 gathers y1 and v
+//             y1' = w + beta y2:                u1 = Ahat y1' gathers w and y2
+// The gathered combination is formed by the same operations as the owner's
+// copy, so it has the same bits.  The vectors that are gathered are stored by
+// their owners at agent scope (publish); everything else stays in the
+// thread.  TFQMR's first half-step needs its scalars only for row-local
+// updates, so both half-steps share one reduction.
+//
+// Row r of workgroup b: consecutive rows, one per lane, so that the gathers of
+// entry k by a wave touch near-consecutive elements on a mesh in node order;
+// xcd_block gives each XCD one range of the rows, whose vectors its L2 holds.
+#include <algorithm>
+
+#include "hk_resident.hpp"
+
+namespace hk {
+
+template <class V> struct Pair { V u, v; };
+
+// acc - a * b, in explicit multiply-adds: a product's operand has the same bits
+// where its owner and where another thread forms it.
+template <class V> __device__ __forceinline__ V cfnma(V a, V b, V acc) {
+  acc.x = fma(-a.x, b.x, fma(a.y, b.y, acc.x));
+  acc.y = fma(-a.x, b.y, fma(-a.y, b.x, acc.y));
+  return acc;
+}
+
+// A value every thread holds alike, moved to scalar registers (the vector
+// ones are for the matrix).
+__device__ __forceinline__ double uni(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double2 uni(double2 v) { return make_double2(uni(v.x), uni(v.y)); }
+
+// Element of a published vector at byte offset `off`: a scalar base and a
+// 32-bit lane offset.
+template <class V> __device__ __forceinline__ V at(const V* base, unsigned off) {
+  return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + off);
+}
+// The column offset, hidden from loop-invariant code motion: otherwise the
+// compiler keeps a 64-bit address per entry and vector in registers across
+// iterations, three times what the entries themselves take.
+__device__ __forceinline__ unsigned fresh(unsigned off) {
+  asm volatile("" : "+v"(off));
+  return off;
+}
+
+// v is computed before this point and later loads are issued after it (the
+// compiler keeps loads in order with the clobber, and otherwise gathers all of
+// them in front of the arithmetic).
+template <class V> __device__ __forceinline__ void here(V& v) {
+  asm volatile("" : "+v"(v.x), "+v"(v.y)::"memory");
+}
+
+__device__ __forceinline__ double2 to_d(double2 a) { return a; }
+__device__ __forceinline__ double2 to_d(float2 a) { return to_c128(a); }
+// The same for a matrix entry, converted where it is used: the plain
+// conversion is loop-invariant and the compiler would keep the doubles.
+__device__ __forceinline__ double2 entry_d(double2 a) { return a; }
+__device__ __forceinline__ double2 entry_d(float2 a) {
+  double2 d;
+  asm volatile("v_cvt_f64_f32 %0, %1" : "=v"(d.x) : "v"(a.x));
+  asm volatile("v_cvt_f64_f32 %0, %1" : "=v"(d.y) : "v"(a.y));
+  return d;
+}
+
+// A thread's rows of Ahat = A D^-1: E entries per row, a row's missing ones
+// zero in value and pointing at the row itself.  The values of the last EL
+// entries of each row are in LDS (lv, [RPT][EL][NT]), where the registers do
+// not take them all.
+template <class V, int E, int EL, int RPT, int NT> struct ResRows {
+  static constexpr int ER = E - EL;
+  V a[RPT][ER];
+  unsigned c[RPT][E];
+  V* lv;
+
+  template <class Args> __device__ __forceinline__ void load(int i, int row, bool has, const Args& A) {
+    const int rc = has ? row : A.n - 1;
+    const int s = A.rowptr[rc], len = has ? A.rowptr[rc + 1] - s : 0;
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int p = len > 0 ? s + min(k, len - 1) : 0;
+      const int cc = A.col[p];
+      const V q = cmul(A.val[p], A.dinv[cc]);
+      V v = k < len ? q : czero<V>();
+      if (k % 4 == 3) here(v);
+      if (k < ER) a[i][k] = v;
+      else lv[(i * EL + k - ER) * NT + threadIdx.x] = v;
+      c[i][k] = (unsigned)(k < len ? cc : rc) * (unsigned)sizeof(V);  // byte offset
+    }
+  }
+  // Sum over the row's entries of a_k comb(k, ld(k, column)), the loads of
+  // kGroup entries at a time issued ahead of the previous group's arithmetic:
+  // left alone the compiler issues every load of the row at once and spills
+  // the matrix.  complex64 rows are summed in double: with a float chain the
+  // refinement cycles of the mixed solve took up to twice the iterations of
+  // the kernels that sum a row's products over lanes (279,496 rows, second
+  // cycle: 606 against 400-425 on average), and the double one costs the same
+  // time, which the gathers set.
+  template <class L, class C> __device__ __forceinline__ V dot(int i, L&& ld, C&& comb) const {
+    constexpr int kBytes = E * RPT * (int)sizeof(V);
+    constexpr int kGroup = kBytes <= 240 ? 4 : kBytes <= 440 ? 3 : 2, NG = (E + kGroup - 1) / kGroup;
+    using X = decltype(ld(0, 0u));
+    double2 acc = make_double2(0, 0);
+    X x[2][kGroup];
+#pragma unroll
+    for (int k = 0; k < kGroup; ++k)
+      if (k < E) x[0][k] = ld(k, fresh(c[i][k]));
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        const int kk = (g + 1) * kGroup + k;
+        if (kk < E) x[(g + 1) & 1][k] = ld(kk, fresh(c[i][kk]));
+      }
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        const int kk = g * kGroup + k;
+        if (kk < ER) acc = cfma(entry_d(a[i][kk]), to_d(comb(kk, x[g & 1][k])), acc);
+        else if (kk < E) acc = cfma(to_d(lv[(i * EL + kk - ER) * NT + threadIdx.x]), to_d(comb(kk, x[g & 1][k])), acc);
+      }
+      here(acc);
+    }
+    return vscal<V>(acc);
+  }
+};
+
+template <int NT> struct ResLds {
+  double sums[kSumWords * (NT / kWave + 4)];
+};
+
+// The row this thread works on as its i-th, and whether there is one.
+template <int RPT, int NT> struct ResMap {
+  int r0, rend;
+  __device__ __forceinline__ ResMap(int n, int rows) {
+    r0 = xcd_block(blockIdx.x, gridDim.x) * rows;
+    rend = min(r0 + rows, n);
+  }
+  __device__ __forceinline__ int row(int i) const { return r0 + i * NT + (int)threadIdx.x; }
+  __device__ __forceinline__ bool has(int i) const { return row(i) < rend; }
+};
+
+// The first statuses of both methods (bb = ||b||^2, rr = ||r0||^2).
+__device__ __forceinline__ int res_first_status(double bb, double rr, double theta2, long long maxit) {
+  if (!isfinite(bb) || !isfinite(rr)) return HK_NONFINITE;
+  if (rr <= theta2) return HK_OK;
+  return maxit <= 0 ? HK_NOT_CONVERGED : S_RUN;
+}
+
+__device__ __forceinline__ void res_publish_state(SolveState* st, int status, int bd, double rr, double bb,
+                                                  long long iter, long long iters_done) {
+  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+  st->status = status;
+  st->bd = bd;
+  st->rr = rr;
+  st->bb = bb;
+  st->iter = iter;
+  st->iters_done = iters_done;
+}
+
+template <class R, int E, int EL, int RPT, int NT>
+__global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
+  using V = cplx<R>;
+  // the rows' gathered r, kept from the v product for the t product where
+  // the registers allow (15 fewer 16-byte gathers per row)
+  constexpr bool kKeep = E * RPT * (int)sizeof(V) <= 256;
+  __shared__ ResLds<NT> lds;
+  __shared__ V s_rh[RPT * NT], s_y[RPT * NT], s_lv[EL > 0 ? RPT * EL * NT : 1];
+  if (*A.flag) return;
+  const ResMap<RPT, NT> m(A.n, A.rows);
+  ResRows<V, E, EL, RPT, NT> M;
+  M.lv = s_lv;
+  V r[RPT], q[RPT], p[RPT], v[RPT], t[RPT];
+  V *const pr = A.pub[0], *const pq = A.pub[1], *const pv = A.pub[2];
+  unsigned epoch = 0;
+  int nv0 = 0;
+  double sum2[2] = {0, 0};
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int row = m.row(i), l = i * NT + threadIdx.x;
+    const bool has = m.has(i);
+    M.load(i, row, has, A);
+    V bi = czero<V>(), ri = czero<V>(), yi = czero<V>();
+    if (has) {
+      bi = A.b[row];
+      ri = A.x0 ? A.r0[row] : bi;
+      if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
+      publish(pr, row, ri);
+      publish(pq, row, czero<V>());
+    }
+    r[i] = ri;
+    q[i] = p[i] = v[i] = t[i] = czero<V>();
+    s_rh[l] = ri;
+    s_y[l] = yi;
+    sum2[0] += nrm2d(bi);
+    sum2[1] += nrm2d(ri);
+  }
+  if (grid_sum<2, NT>(A.gs, epoch, nv0, sum2, lds.sums)) return;
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  const double bb = uni(sum2[0]), theta2 = uni(A.tol * A.tol * bb);
+  double rr = uni(sum2[1]);
+  double2 rho = make_double2(rr, 0), beta = make_double2(0, 0), alpha, omega;
+  int status = res_first_status(bb, rr, theta2, A.maxit), bd = HK_BD_NONE;
+  long long it = 1, done = 0;
+  if (first && A.history) A.history[0] = bb > 0 ? sqrt(rr / bb) : 0.0;
+  while (status == S_RUN) {
+    V rg[RPT][kKeep ? E : 1];
+    // v = Ahat p, p = r + beta q; sigma = rhat^H v
+    double sg[2] = {0, 0};
+    {
+      const V be = vscal<V>(beta);
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+        p[i] = cfma(be, q[i], r[i]);
+        v[i] = M.dot(
+            i, [&](int, unsigned c) { return Pair<V>{at(pr, c), at(pq, c)}; },
+            [&](int k, const Pair<V>& x) {
+              if constexpr (kKeep) rg[i][k] = x.u;
+              return cfma(be, x.v, x.u);
+            });
+        if (m.has(i)) {
+          publish(pv, m.row(i), v[i]);
+          dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
+        }
+      }
+    }
+    if (grid_sum<2, NT>(A.gs, epoch, nv0, sg, lds.sums)) return;
+    const double2 sigma = make_double2(sg[0], sg[1]);
+    if (!cfinite(sigma)) {
+      status = HK_NONFINITE;
+      done = it - 1;
+      break;
+    }
+    if (sigma.x == 0 && sigma.y == 0) {
+      status = HK_BREAKDOWN;
+      bd = HK_BD_SIGMA;
+      done = it - 1;
+      break;
+    }
+    alpha = uni(cdiv(rho, sigma));
+    const V al = vscal<V>(alpha);
+    // t = Ahat s, s = r - alpha v; tau = t^H t, t^H s, ||s||^2
+    double ts[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const V s = cfnma(al, v[i], r[i]);
+      if constexpr (kKeep)
+        t[i] = M.dot(
+            i, [&](int, unsigned c) { return at(pv, c); },
+            [&](int k, V x) { return cfnma(al, x, rg[i][k]); });
+      else
+        t[i] = M.dot(
+            i, [&](int, unsigned c) { return Pair<V>{at(pr, c), at(pv, c)}; },
+            [&](int, const Pair<V>& x) { return cfnma(al, x.v, x.u); });
+      if (m.has(i)) {
+        ts[0] += nrm2d(t[i]);
+        dotc_acc(t[i], s, ts[1], ts[2]);
+        ts[3] += nrm2d(s);
+      }
+    }
+    if (grid_sum<4, NT>(A.gs, epoch, nv0, ts, lds.sums)) return;
+    const double ss = ts[3];
+    const bool half = isfinite(ss) && ss <= theta2;
+    if (!half && (!isfinite(ss) || !isfinite(ts[0]) || !isfinite(ts[1]) || !isfinite(ts[2]))) {
+      status = HK_NONFINITE;
+      done = it - 1;
+      break;
+    }
+    if (half || ts[0] == 0) {
+      // converged on s, or tau = 0: y += alpha p
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+        const int l = i * NT + threadIdx.x;
+        s_y[l] = cfma(al, p[i], s_y[l]);
+      }
+      rr = ss;
+      done = it;
+      status = half ? HK_OK : HK_BREAKDOWN;
+      if (!half) bd = HK_BD_TAU;
+      if (half && first && A.history) A.history[it] = bb > 0 ? sqrt(ss / bb) : 0.0;
+      break;
+    }
+    omega = uni(make_double2(ts[1] / ts[0], ts[2] / ts[0]));
+    const V om = vscal<V>(omega);
+    // y += alpha p + omega s, r = s - omega t, q = p - omega v
+    double xr[3] = {0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const int l = i * NT + threadIdx.x;
+      const V s = cfnma(al, v[i], r[i]);
+      s_y[l] = cfma(om, s, cfma(al, p[i], s_y[l]));
+      r[i] = cfnma(om, t[i], s);
+      q[i] = cfnma(om, v[i], p[i]);
+      if (m.has(i)) {
+        publish(pr, m.row(i), r[i]);
+        publish(pq, m.row(i), q[i]);
+        xr[0] += nrm2d(r[i]);
+        dotc_acc(s_rh[l], r[i], xr[1], xr[2]);
+      }
+    }
+    if (grid_sum<3, NT>(A.gs, epoch, nv0, xr, lds.sums)) return;
+    rr = uni(xr[0]);
+    done = it;
+    const double2 rho1 = uni(make_double2(xr[1], xr[2]));
+    if (first && A.history) A.history[it] = bb > 0 ? sqrt(rr / bb) : 0.0;
+    if (!isfinite(rr) || !cfinite(rho1)) {
+      status = HK_NONFINITE;
+    } else if (rr <= theta2) {
+      status = HK_OK;
+    } else if (omega.x == 0 && omega.y == 0) {
+      status = HK_BREAKDOWN;
+      bd = HK_BD_OMEGA;
+    } else if (rho1.x == 0 && rho1.y == 0) {
+      status = HK_BREAKDOWN;
+      bd = HK_BD_RHO;
+    } else if (it >= A.maxit) {
+      status = HK_NOT_CONVERGED;
+    } else {
+      beta = uni(cmul(cdiv(rho1, rho), cdiv(alpha, omega)));
+      rho = rho1;
+      ++it;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < RPT; ++i)
+    if (m.has(i)) A.y[m.row(i)] = s_y[i * NT + threadIdx.x];
+  res_publish_state(A.st, status, bd, rr, bb, it, done);
+}
+
+// TFQMR (complex128).  Statuses, counts and updates at each exit are those of
+// the kernels in hk_solver.hip.
+template <int E, int EL, int RPT, int NT>
+__global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
+  using V = double2;
+  __shared__ ResLds<NT> lds;
+  __shared__ V s_rh[RPT * NT], s_y[RPT * NT], s_d[RPT * NT], s_lv[EL > 0 ? RPT * EL * NT : 1];
+  if (*A.flag) return;
+  const ResMap<RPT, NT> m(A.n, A.rows);
+  ResRows<V, E, EL, RPT, NT> M;
+  M.lv = s_lv;
+  V y1[RPT], v[RPT], u1[RPT], w[RPT], y2[RPT], u2[RPT];
+  V *const py1 = A.pub[0], *const pv = A.pub[1], *const pw = A.pub[2], *const py2 = A.pub[3];
+  unsigned epoch = 0;
+  int nv0 = 0;
+  double sum2[2] = {0, 0};
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int row = m.row(i), l = i * NT + threadIdx.x;
+    const bool has = m.has(i);
+    M.load(i, row, has, A);
+    V bi = czero<V>(), ri = czero<V>(), yi = czero<V>();
+    if (has) {
+      bi = A.b[row];
+      ri = A.x0 ? A.r0[row] : bi;
+      if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
+      publish(py1, row, ri);
+    }
+    y1[i] = w[i] = ri;
+    v[i] = u1[i] = y2[i] = u2[i] = czero<V>();
+    s_rh[l] = ri;
+    s_y[l] = yi;
+    s_d[l] = czero<V>();
+    sum2[0] += nrm2d(bi);
+    sum2[1] += nrm2d(ri);
+  }
+  if (grid_sum<2, NT>(A.gs, epoch, nv0, sum2, lds.sums)) return;
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  const double bb = uni(sum2[0]), theta2 = uni(A.tol * A.tol * bb);
+  double rr = uni(sum2[1]), tau = uni(sqrt(rr)), theta = 0;
+  V rho = make_double2(rr, 0), alpha = czero<V>(), eta2 = czero<V>(), coef1 = czero<V>();
+  int status = res_first_status(bb, rr, theta2, A.maxit), bd = HK_BD_NONE;
+  long long k = 1, done = 0;
+  if (first && A.history) A.history[0] = bb > 0 ? sqrt(rr / bb) : 0.0;
+  // alpha and the d-update coefficient from sigma = rhat^H v; false at an exit
+  auto sigma_step = [&](const double (&sg)[2]) {
+    const V sigma = make_double2(sg[0], sg[1]);
+    if (!cfinite(sigma)) {
+      status = HK_NONFINITE;
+      done = k - 1;
+    } else if (sigma.x == 0 && sigma.y == 0) {
+      status = HK_BREAKDOWN;
+      bd = HK_BD_SIGMA;
+      done = k - 1;
+    } else {
+      alpha = uni(cdiv(rho, sigma));
+      coef1 = uni(cdiv(cmul(make_double2(theta * theta, 0), eta2), alpha));
+    }
+  };
+  // theta, tau, eta and the bound of half-step h from ||w||^2; returns eta
+  auto half_step = [&](double ww, long long h) {
+    theta = uni(sqrt(ww) / tau);
+    const double c = 1.0 / sqrt(1.0 + theta * theta);
+    tau = uni(tau * theta * c);
+    const V eta = uni(make_double2(c * c * alpha.x, c * c * alpha.y));
+    const double bound = tau * sqrt((double)(h + 1));
+    rr = uni(bound * bound);
+    if (first && A.history) A.history[k] = bb > 0 ? bound / sqrt(bb) : 0.0;
+    return eta;
+  };
+  if (status == S_RUN) {
+    // v = u1 = Ahat y1
+    double sg[2] = {0, 0};
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      u1[i] = M.dot(
+          i, [&](int, unsigned c) { return at(py1, c); }, [&](int, V x) { return x; });
+      v[i] = u1[i];
+      if (m.has(i)) {
+        publish(pv, m.row(i), v[i]);
+        dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
+      }
+    }
+    if (grid_sum<2, NT>(A.gs, epoch, nv0, sg, lds.sums)) return;
+    sigma_step(sg);
+  }
+  while (status == S_RUN) {
+    // half-steps 1 and 2: w -= alpha u1, ||w||^2; u2 = Ahat y2,
+    // w -= alpha u2, ||w||^2, rhat^H w
+    double hs[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      y2[i] = cfnma(alpha, v[i], y1[i]);
+      w[i] = cfnma(alpha, u1[i], w[i]);
+      const double w1 = nrm2d(w[i]);
+      u2[i] = M.dot(
+          i, [&](int, unsigned c) { return Pair<V>{at(py1, c), at(pv, c)}; },
+          [&](int, const Pair<V>& x) { return cfnma(alpha, x.v, x.u); });
+      w[i] = cfnma(alpha, u2[i], w[i]);
+      if (m.has(i)) {
+        publish(pw, m.row(i), w[i]);
+        publish(py2, m.row(i), y2[i]);
+        hs[0] += w1;
+        hs[1] += nrm2d(w[i]);
+        dotc_acc(s_rh[i * NT + threadIdx.x], w[i], hs[2], hs[3]);
+      }
+    }
+    if (grid_sum<4, NT>(A.gs, epoch, nv0, hs, lds.sums)) return;
+    const V eta1 = half_step(hs[0], 2 * k - 1);
+    const V coef2 = uni(cdiv(cmul(make_double2(theta * theta, 0), eta1), alpha));
+    done = k;
+    if (!isfinite(tau) || !cfinite(eta1)) {
+      status = HK_NONFINITE;
+      break;
+    }
+    const bool half1 = rr <= theta2;
+    V rho1 = czero<V>(), beta = czero<V>();
+    if (half1) {
+      status = HK_OK;
+    } else {
+      eta2 = half_step(hs[1], 2 * k);
+      rho1 = uni(make_double2(hs[2], hs[3]));
+      if (!isfinite(tau) || !cfinite(eta2)) status = HK_NONFINITE;
+      else if (rr <= theta2) status = HK_OK;
+      else if (!cfinite(rho1)) status = HK_NONFINITE;
+      else if (rho1.x == 0 && rho1.y == 0) { status = HK_BREAKDOWN; bd = HK_BD_RHO; }
+      else beta = uni(cdiv(rho1, rho));
+    }
+    // d = y1 + coef1 d, y += eta1 d; d = y2 + coef2 d, y += eta2 d
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const int l = i * NT + threadIdx.x;
+      const V d1 = cfma(coef1, s_d[l], y1[i]);
+      V y = cfma(eta1, d1, s_y[l]);
+      if (!half1) {
+        const V d2 = cfma(coef2, d1, y2[i]);
+        if (status != HK_NONFINITE) y = cfma(eta2, d2, y);
+        s_d[l] = d2;
+      }
+      s_y[l] = y;
+    }
+    if (status != S_RUN) break;
+    rho = rho1;
+    if (k >= A.maxit) {
+      status = HK_NOT_CONVERGED;
+      break;
+    }
+    // y1 = w + beta y2; u1 = Ahat y1; v = u1 + beta (u2 + beta v)
+    double sg[2] = {0, 0};
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      y1[i] = cfma(beta, y2[i], w[i]);
+      u1[i] = M.dot(
+          i, [&](int, unsigned c) { return Pair<V>{at(py2, c), at(pw, c)}; },
+          [&](int, const Pair<V>& x) { return cfma(beta, x.u, x.v); });
+      v[i] = cfma(beta, cfma(beta, v[i], u2[i]), u1[i]);
+      if (m.has(i)) {
+        publish(py1, m.row(i), y1[i]);
+        publish(pv, m.row(i), v[i]);
+        dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
+      }
+    }
+    if (grid_sum<2, NT>(A.gs, epoch, nv0, sg, lds.sums)) return;
+    ++k;
+    sigma_step(sg);
+  }
+#pragma unroll
+  for (int i = 0; i < RPT; ++i)
+    if (m.has(i)) A.y[m.row(i)] = s_y[i * NT + threadIdx.x];
+  res_publish_state(A.st, status, bd, rr, bb, k, done);
+}
+
+// ------------------------------------------------------------------ host side
+
+// all barrier words empty, abort flag 0
+__global__ void k_res_reset(unsigned long long* words, int nwords, int* abort) {
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (i < nwords) words[i] = kSumEmpty;
+  if (i == 0) *abort = 0;
+}
+
+size_t resident_scratch_bytes() { return sizeof(unsigned long long) * kSumSets * kSumSetWords + 256; }
+int* resident_abort(void* scratch) {
+  return reinterpret_cast<int*>(static_cast<unsigned long long*>(scratch) + kSumSets * kSumSetWords);
+}
+
+// Rows of up to 8, 15 (tetrahedra) or 27 (hexahedra) entries are held, up to
+// kResMax rows per thread: what 256 registers of each of 512 threads and 160 KB
+// of LDS per CU take.  Beyond it the values no longer fit.  Within it the
+// resident launch is the faster one at every size (1.8M rows do not fit, 279,496
+// in complex64 2.3x, 4,913 rows 4.5x with the recording of the graph that the
+// separate kernels need), so there is no lower limit.
+static int res_class(int max_row) { return max_row <= 8 ? 0 : max_row <= 15 ? 1 : 2; }
+constexpr int kResEntries[3] = {8, 15, 27};
+constexpr int kResMax[2][3] = {{2, 2, 1}, {4, 4, 2}};  // [complex64][class]
+
+ResShape resident_shape(const hk_csr_s* A, int prec, int method) {
+  ResShape sh;
+  if (method != HK_BICGSTAB && method != HK_TFQMR) return sh;
+  if (A->plan_fixed || A->nnz <= 0 || A->max_row > kResEntries[2]) return sh;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, A->device) != hipSuccess) {
+    (void)hipGetLastError();
+    return sh;
+  }
+  cus = std::min(cus, kSumBlocks);
+  const int cl = res_class(A->max_row), rpt_max = kResMax[prec][cl];
+  int rpt = 1;
+  while (rpt <= rpt_max && A->n > (int64_t)cus * 512 * rpt) ++rpt;
+  if (rpt > rpt_max) return sh;
+  // small systems: 256-thread workgroups, one wave per SIMD
+  const int threads = A->n <= 64 * 256 ? 256 : 512;
+  const int64_t even = rpt == 1 ? threads : (A->n + cus - 1) / cus;
+  sh.rows = (int)((even + 63) / 64 * 64);
+  sh.grid = (int)((A->n + sh.rows - 1) / sh.rows);
+  sh.entries = kResEntries[cl];
+  sh.rpt = rpt;
+  sh.threads = threads;
+  return sh;
+}
+
+template <class R> static const void* res_kernel(const ResShape& sh, int method) {
+#define HK_RES(EE, EL, PP, TT)                                                        \
+  if (sh.entries == EE && sh.rpt == PP && sh.threads == TT) {                         \
+    if (method == HK_BICGSTAB) return (const void*)k_res_bicgstab<R, EE, EL, PP, TT>; \
+    if constexpr (sizeof(R) == 8) return (const void*)k_res_tfqmr<EE, EL, PP, TT>;    \
+  }
+  if constexpr (sizeof(R) == 8) {
+    HK_RES(8, 0, 1, 256) HK_RES(8, 0, 1, 512) HK_RES(8, 2, 2, 512)
+    HK_RES(15, 0, 1, 256) HK_RES(15, 0, 1, 512) HK_RES(15, 6, 2, 512)
+    HK_RES(27, 13, 1, 256) HK_RES(27, 13, 1, 512)
+  } else {
+    HK_RES(8, 0, 1, 256) HK_RES(8, 0, 1, 512) HK_RES(8, 0, 2, 512) HK_RES(8, 0, 3, 512) HK_RES(8, 2, 4, 512)
+    HK_RES(15, 0, 1, 256) HK_RES(15, 0, 1, 512) HK_RES(15, 0, 2, 512) HK_RES(15, 4, 3, 512) HK_RES(15, 7, 4, 512)
+    HK_RES(27, 0, 1, 256) HK_RES(27, 0, 1, 512) HK_RES(27, 12, 2, 512)
+  }
+#undef HK_RES
+  return nullptr;
+}
+
+template <class R>
+hipError_t resident_launch(const ResShape& sh, int method, ResArgs<R> args, void* scratch, hipStream_t s) {
+  const void* kern = res_kernel<R>(sh, method);
+  if (!kern) return hipErrorInvalidConfiguration;
+  int per = 0, cus = 0, coop = 0, dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, sh.threads, 0);
+  if (e != hipSuccess) return e;
+  if (!coop || sh.grid > per * cus || sh.grid > kSumBlocks || sh.rows > sh.rpt * sh.threads)
+    return hipErrorInvalidConfiguration;
+  args.rows = sh.rows;
+  args.gs.words = static_cast<unsigned long long*>(scratch);
+  args.gs.abort = resident_abort(scratch);
+  args.gs.spin_limit = barrier_spin_limit();
+  const int nwords = (int)(kSumSets * kSumSetWords);
+  hipLaunchKernelGGL(k_res_reset, dim3(nwords / kBlock), dim3(kBlock), 0, s, args.gs.words, nwords, args.gs.abort);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  void* kargs[] = {&args};
+  return hipLaunchCooperativeKernel(kern, dim3(sh.grid), dim3(sh.threads), kargs, 0, s);
+}
+template hipError_t resident_launch<double>(const ResShape&, int, ResArgs<double>, void*, hipStream_t);
+template hipError_t resident_launch<float>(const ResShape&, int, ResArgs<float>, void*, hipStream_t);
+
+}  // namespace hk

@@ -44,30 +44,14 @@
 #include <vector>
 
 #include "hk_internal.hpp"
+#include "hk_resident.hpp"
+#include "hk_solver.hpp"
 #include "hk_spmv.hpp"
 
 namespace hk {
 
 int spmv_dispatch(const hk_csr_s* A, const void* x, void* y, const void* b, const void* alpha,
                   const void* beta, int mode, hipStream_t s);
-
-// Transient statuses (>= S_RUN): the solve goes on, or an exit is pending
-// until the kernels of the current iteration have applied their last update.
-enum : int { S_RUN = 100, S_HALF = 101, S_TAUBD = 102, S_HALF2 = 103, S_RHOBD = 104 };
-
-struct SolveState {
-  double2 rho, rho_old, alpha, omega, beta;
-  double rr, ss, bb, theta2, rr_true;
-  int status, bd;
-  long long iter, maxit, iters_done;
-  double* history;
-  // TFQMR: theta, tau, the two half-steps' eta (their x updates are applied
-  // by the next kernel that reads d) and the d-update coefficients
-  double tq_theta, tq_tau;
-  double2 tq_eta1, tq_eta2, tq_coef1, tq_coef2;
-  // BiCGStab(l): the minimal-residual coefficients gamma_1..gamma_l
-  double2 bl_gamma[8];
-};
 
 // Most workgroups of a fused SpMV+dot launch (one partial-sum slot each).
 // A launch shape with grid 0 gets one tile per workgroup up to this cap: on
@@ -88,22 +72,6 @@ static inline int ew_blocks(int64_t n) {
 static inline int64_t partial_slots(int64_t n) {
   const int64_t e = ew_blocks(n);
   return e > kMaxGrid ? e : kMaxGrid;
-}
-
-// a solver scalar (double) rounded to the vector type
-template <class V> __device__ __forceinline__ V vscal(double2 a) {
-  return cmake<V>((decltype(V::x))a.x, (decltype(V::x))a.y);
-}
-// |a|^2 in double
-template <class V> __device__ __forceinline__ double nrm2d(V a) {
-  const double x = a.x, y = a.y;
-  return x * x + y * y;
-}
-// acc += conj(a) * b in double (two partial sums: re, im)
-template <class V> __device__ __forceinline__ void dotc_acc(V a, V b, double& re, double& im) {
-  const double ax = a.x, ay = a.y, bx = b.x, by = b.y;
-  re = fma(ax, bx, fma(ay, by, re));
-  im = fma(ax, by, fma(-ay, bx, im));
 }
 
 // ------------------------------------------------------------ set-up kernels
@@ -537,6 +505,7 @@ template <class R> struct Work {
   V *y, *r, *rh, *p, *v, *s, *t, *dinv, *ahat;
   V *u, *d;  // TFQMR only
   double* partials;
+  void* res;  // the resident solves' barrier words
   SolveState* st;
   int* flag;
 };
@@ -561,6 +530,7 @@ template <class R, class Take> static Work<R> layout(Take take, int64_t n, int64
   w.d = (V*)take(sizeof(V) * n);
   w.ahat = (V*)take(sizeof(V) * (nnz + 1));  // one padding entry (paired-entry products)
   w.partials = (double*)take(sizeof(double) * 4 * partial_slots(n));
+  w.res = (void*)take(resident_scratch_bytes());
   w.st = (SolveState*)take(sizeof(SolveState));
   w.flag = (int*)take(64);
   return w;
@@ -775,8 +745,6 @@ static int finish_solve(const hk_csr_s* A, const cplx<R>* val, const cplx<R>* b,
   return HK_OK;
 }
 
-// Runs the whole solve for precision R on values `val` (A's pattern), right
-// side b, solution x (input when use_x0).  Fills info (host), synchronises.
 // Chunked iteration driver shared by the three methods.  enqueue(q)
 // enqueues one chunk (m iterations) on stream q and returns the first launch
 // error.  After each chunk the status word is copied to pinned memory and
@@ -871,6 +839,59 @@ static int run_chunks(int* pin, SolveState* st, int m, long long max_iter, hipSt
   return rc;
 }
 
+// The whole solve in one resident launch (hk_resident.hip), after the set-up
+// (wk.dinv, wk.flag; r0 in wk.r with use_x0).  *ran stays false where the
+// system does not fit, or the launch could not run or timed out: nothing of
+// x is written then and the caller goes on with the kernels below.
+template <class R>
+static int resident_solve(hk_csr_s* A, int method, const cplx<R>* val, const cplx<R>* b, cplx<R>* x,
+                          const hk_solve_opts& o, const Work<R>& wk, hk_solve_info* info, bool* ran, hipStream_t s) {
+  *ran = false;
+  const ResShape sh = resident_shape(A, sizeof(R) == 4 ? 1 : 0, method);
+  if (sh.entries == 0) return HK_OK;
+  ResArgs<R> a{};
+  a.n = (int)A->n;
+  a.rowptr = A->rowptr;
+  a.col = A->col;
+  a.val = val;
+  a.dinv = wk.dinv;
+  a.b = b;
+  a.x0 = o.use_x0 ? x : nullptr;
+  a.r0 = wk.r;
+  a.y = wk.y;
+  a.pub[0] = wk.p;
+  a.pub[1] = wk.v;
+  a.pub[2] = wk.s;
+  a.pub[3] = wk.t;
+  a.st = wk.st;
+  a.flag = wk.flag;
+  a.tol = o.tol;
+  a.maxit = (long long)o.max_iter;
+  a.history = o.d_history;
+  if (resident_launch<R>(sh, method, a, wk.res, s) != hipSuccess) {
+    (void)hipGetLastError();
+    return HK_OK;
+  }
+  int h[2] = {0, 0};
+  HK_HIP(hipMemcpyAsync(&h[0], wk.flag, sizeof(int), hipMemcpyDeviceToHost, s));
+  HK_HIP(hipMemcpyAsync(&h[1], resident_abort(wk.res), sizeof(int), hipMemcpyDeviceToHost, s));
+  HK_HIP(hipStreamSynchronize(s));
+  if (h[0]) HK_FAIL(HK_EINVAL, "krylov solve: zero diagonal entry (Jacobi undefined)");
+  if (h[1]) return HK_OK;
+  *ran = true;
+  const int rc = finish_solve<R>(A, val, b, x, wk, info, s);
+  if (rc != HK_OK) return rc;
+  info->shape[0] = 1;
+  info->shape[1] = sh.rpt;
+  info->shape[2] = sh.threads / kWave;
+  info->shape[3] = 0;
+  info->shape_tuned = 0;
+  info->pad = 0;
+  return HK_OK;
+}
+
+// Runs the whole solve for precision R on values `val` (A's pattern), right
+// side b, solution x (input when use_x0).  Fills info (host), synchronises.
 template <class R>
 static int bicgstab(hk_csr_s* A, const cplx<R>* val, const cplx<R>* b, cplx<R>* x,
                     const hk_solve_opts& o, void* wsbase, hk_solve_info* info, hipStream_t s) {
@@ -885,14 +906,19 @@ static int bicgstab(hk_csr_s* A, const cplx<R>* val, const cplx<R>* b, cplx<R>* 
   hipLaunchKernelGGL(k_diag_inv<V>, ew, dim3(kBlock), 0, s, n, A->rowptr, A->col, val, wk.dinv,
                      o.precond ? 1 : 0, wk.flag);
   HK_CHECK_LAUNCH();
-  launch_scale_cols<V>(A->nnz, A->col, val, wk.dinv, wk.ahat, s);
-  HK_CHECK_LAUNCH();
   if (o.use_x0) {
     hk_csr_s tmp = *A;
     tmp.val = val;
     int rc = spmv_dispatch(&tmp, x, wk.r, b, nullptr, nullptr, 1, s);
     if (rc != HK_OK) return rc;
   }
+  {
+    bool ran = false;
+    const int rc = resident_solve<R>(A, HK_BICGSTAB, val, b, x, o, wk, info, &ran, s);
+    if (rc != HK_OK || ran) return rc;
+  }
+  launch_scale_cols<V>(A->nnz, A->col, val, wk.dinv, wk.ahat, s);
+  HK_CHECK_LAUNCH();
   // fused-product shape: one fixed by hk_csr_set_solver_plan or tuned (on
   // the first solve of a tuned handle), else the handle's CSR shape
   SpmvPlan dp = A->plan;
@@ -1310,14 +1336,19 @@ static int tfqmr(hk_csr_s* A, const double2* val, const double2* b, double2* x, 
   hipLaunchKernelGGL(k_diag_inv<V>, ew, dim3(kBlock), 0, s, n, A->rowptr, A->col, val, wk.dinv,
                      o.precond ? 1 : 0, wk.flag);
   HK_CHECK_LAUNCH();
-  launch_scale_cols<V>(A->nnz, A->col, val, wk.dinv, wk.ahat, s);
-  HK_CHECK_LAUNCH();
   if (o.use_x0) {
     hk_csr_s tmp = *A;
     tmp.val = val;
     int rc = spmv_dispatch(&tmp, x, wk.r, b, nullptr, nullptr, 1, s);
     if (rc != HK_OK) return rc;
   }
+  {
+    bool ran = false;
+    const int rc = resident_solve<R>(A, HK_TFQMR, val, b, x, o, wk, info, &ran, s);
+    if (rc != HK_OK || ran) return rc;
+  }
+  launch_scale_cols<V>(A->nnz, A->col, val, wk.dinv, wk.ahat, s);
+  HK_CHECK_LAUNCH();
   SpmvPlan dp = A->plan;
   dp.nw = 0;
   SpmvPlan& cached = A->dot_plan[0];
@@ -1942,6 +1973,7 @@ extern "C" int hk_krylov_solve(hk_csr A, const void* d_b, void* d_x, const hk_so
   hipStream_t s = as_stream(stream);
   rc = ensure_pinned(A);
   if (rc != HK_OK) return rc;
+  for (int k = 0; k < 4; ++k) info->shape[k] = 0;  // a resident solve reports its own
   if (A->dtype == HK_C64) {
     if (opts->method != HK_BICGSTAB) HK_FAIL(HK_EINVAL, "hk_krylov_solve: complex64 solves use BiCGStab only");
     rc = ensure_ws(&A->ws32, &A->ws32_bytes, work_bytes<float>(A->n, A->nnz), s);
@@ -1963,7 +1995,7 @@ extern "C" int hk_krylov_solve(hk_csr A, const void* d_b, void* d_x, const hk_so
                             info, s);
   }
   if (rc != HK_OK) return rc;
-  report_shape(A, A->dtype == HK_C64 ? 1 : 0, info);
+  if (info->shape[0] == 0) report_shape(A, A->dtype == HK_C64 ? 1 : 0, info);
   return info->status;
 }
 
@@ -2026,6 +2058,7 @@ extern "C" int hk_krylov_solve_mixed(hk_csr A, const void* d_b, void* d_x, doubl
     }
     A32.plan = A->plan32;
   }
+  hk_solve_info inner_shape{};
   const bool trace = getenv("HK_TRACE") != nullptr;
   const bool literal = (opts->flags & HK_MIXED_LITERAL_INNER) != 0;
   io.flags = 0;
@@ -2059,6 +2092,7 @@ extern "C" int hk_krylov_solve_mixed(hk_csr A, const void* d_b, void* d_x, doubl
       fprintf(stderr, "[hk mixed] cycle %d: ||r||/||b|| = %.3e, inner status %d (breakdown %d) after %lld iterations, inner relres %.3e\n",
               k, rel, ii.status, ii.breakdown, (long long)ii.iters, ii.relres_rec);
     inner_total += ii.iters;
+    inner_shape = ii;
     if (ii.status == HK_NONFINITE) { status = HK_NONFINITE; break; }
     hipLaunchKernelGGL(k_add_c64, ew, dim3(kBlock), 0, s, (int)n, (const float2*)d32, (double2*)d_x,
                        1.0 / scale);
@@ -2071,5 +2105,9 @@ extern "C" int hk_krylov_solve_mixed(hk_csr A, const void* d_b, void* d_x, doubl
   info->relres_true = rel;
   info->inner_iters = inner_total;
   report_shape(A, 1, info);
+  if (inner_shape.shape[0] != 0) {  // the inner solves were resident
+    for (int q = 0; q < 4; ++q) info->shape[q] = inner_shape.shape[q];
+    info->shape_tuned = 0;
+  }
   return status;
 }

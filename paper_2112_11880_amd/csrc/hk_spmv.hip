@@ -408,6 +408,7 @@ extern "C" int hk_csr_set_plan(hk_csr A, int32_t L, int32_t U, int32_t grid) {
   if (!A) HK_FAIL(HK_EINVAL, "hk_csr_set_plan: NULL handle");
   if (!valid_shape(L, U) || grid < 0) HK_FAIL(HK_EINVAL, "hk_csr_set_plan: bad shape L=%d U=%d grid=%d", L, U, grid);
   A->plan.L = L; A->plan.U = U; A->plan.grid = grid; A->plan.tuned = 0;
+  A->plan_fixed = true;
   A->dot_plan[0] = A->dot_plan[1] = SpmvPlan{};  // the solvers' products follow the new shape
   return HK_OK;
 }
@@ -424,6 +425,7 @@ extern "C" int hk_csr_set_solver_plan(hk_csr A, int32_t rows_per_wave, int32_t w
   SpmvPlan p;
   p.L = kRowBlockL; p.U = rows_per_wave; p.nw = waves; p.grid = grid; p.pairs = paired; p.tuned = 2;
   A->dot_plan[0] = A->dot_plan[1] = p;
+  A->plan_fixed = true;
   return HK_OK;
 }
 

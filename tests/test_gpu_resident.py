@@ -1,0 +1,129 @@
+"""Resident solves (matrix kept in registers, one cooperative launch) against
+the CPU oracle, at the sizes where their launch shape changes.
+
+Bounds: the systems are diagonally dominant (their Jacobi-scaled rows sum to at
+most 1/2 off the diagonal), so three iterations amplify the rounding of a dot
+over n terms (below 1e-13 relative for n up to 4e5) and of a row by less than
+ten: complex128 iterates within 1e-11 of the oracle's.  complex64 iterates differ
+by the rounding of their vectors, 2^-24 per operation over some thirty
+operations: 1e-5.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def hk():
+    if not torch.cuda.is_available():
+        pytest.fail("no HIP device visible")
+    import paper_2112_11880_amd as hk
+    hk.load()
+    return hk
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def crandn(rng, n):
+    return rng.standard_normal(n) + 1j * rng.standard_normal(n)
+
+
+def dominant(n, row, seed):
+    """Rows of 1 to `row` entries (the longest included), columns near and far from the diagonal."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(1, row + 1, n)
+    lens[: max(1, n // 2)] = row
+    k = max(row - 1, 1)
+    off = np.where(rng.random((n, k)) < 0.7, rng.integers(-40, 41, (n, k)), rng.integers(-n, n + 1, (n, k)))
+    off[0] = np.arange(1, k + 1)  # the one row that surely has no column twice
+    col = np.clip(np.arange(n)[:, None] + off, 0, n - 1)
+    col[np.arange(k)[None, :] >= lens[:, None] - 1] = -1
+    col = np.concatenate([col, np.arange(n)[:, None]], axis=1)
+    col.sort(axis=1)
+    keep = col >= 0
+    keep[:, 1:] &= col[:, 1:] != col[:, :-1]
+    cnt = keep.sum(1)
+    rowptr = np.zeros(n + 1, dtype=np.int32)
+    rowptr[1:] = np.cumsum(cnt)
+    cols = col[keep].astype(np.int32)
+    val = crandn(rng, cols.shape[0]) / (4.0 * row)
+    val[cols == np.repeat(np.arange(n), cnt)] = 1.0 + 0.25 * crandn(rng, n)
+    return rowptr, cols, val, crandn(rng, n)
+
+
+# (rows, longest row, shape's rows per thread and waves, or None: the system does not fit)
+SHAPES = [
+    (1, 1, (1, 4)), (63, 8, (1, 4)), (64, 9, (1, 4)), (65, 15, (1, 4)), (257, 16, (1, 4)), (300, 27, (1, 4)),
+    (300, 28, None), (16384, 15, (1, 4)), (16385, 15, (1, 8)), (16385, 27, (1, 8)),
+    (131072, 15, (1, 8)), (131073, 15, (2, 8)), (131073, 8, (2, 8)), (131073, 27, None),
+    (262144, 15, (2, 8)), (262145, 15, None),
+]
+
+
+@pytest.mark.parametrize("n,row,shape", SHAPES)
+@pytest.mark.parametrize("method", ["bicgstab", "tfqmr"])
+def test_resident_iterates(hk, oracle, n, row, shape, method):
+    print("[case]", method, n, row, flush=True)
+    rowptr, col, val, b = dominant(n, row, n + row)
+    A = hk.CSR(dev(rowptr), dev(col), dev(val))
+    ref = oracle.bicgstab if method == "bicgstab" else oracle.tfqmr
+    for k in (1, 3):
+        x, info, hist = hk.krylov_solve(A, dev(b), tol=0.0, max_iter=k, method=method, history=True)
+        xo, oi, ho = ref(rowptr, col, val, b, tol=0.0, maxit=k, history=True)
+        if n > 1:
+            assert info["status"] == oi["status"] == hk.HK_NOT_CONVERGED and info["iters"] == k, (info, oi)
+            assert np.allclose(hist.cpu().numpy(), ho, rtol=1e-9, atol=0)
+        if shape is not None:
+            assert info["shape"][0] == 1 and tuple(info["shape"][1:3]) == shape, info["shape"]
+        else:
+            assert info["shape"][0] != 1, info["shape"]
+        assert np.linalg.norm(x.cpu().numpy() - xo) <= 1e-11 * np.linalg.norm(xo)
+
+
+@pytest.mark.parametrize("n,row,rpt", [(1000, 8, 1), (16385, 15, 1), (131073, 15, 2), (262145, 15, 3), (393217, 15, 4),
+                                       (131072, 27, 1), (131073, 27, 2), (262145, 8, 3), (393217, 8, 4)])
+def test_resident_complex64_iterates(hk, oracle, n, row, rpt):
+    print("[case] complex64", n, row, flush=True)
+    rowptr, col, val, b = dominant(n, row, n + row)
+    v32, b32 = val.astype(np.complex64), b.astype(np.complex64)
+    x, info = hk.krylov_solve(hk.CSR(dev(rowptr), dev(col), dev(v32)), dev(b32), tol=0.0, max_iter=3)
+    xo, oi = oracle.bicgstab_c64(rowptr, col, v32, b32, tol=0.0, maxit=3)
+    assert info["iters"] == oi["iters"] == 3 and info["shape"][:2] == [1, rpt], info
+    assert np.linalg.norm(x.cpu().numpy() - xo) <= 1e-5 * np.linalg.norm(xo)
+
+
+@pytest.mark.parametrize("method", ["bicgstab", "tfqmr"])
+def test_resident_options_and_fallback(hk, oracle, monkeypatch, method):
+    """x0, no preconditioner, a solve to its tolerance, and the same solve by
+    the separate kernels: a handle with a fixed plan uses them, and so does a
+    resident launch whose barrier waits are not allowed to take any time."""
+    rowptr, col, val, b = dominant(5000, 15, 9)
+    rng = np.random.default_rng(1)
+    x0 = crandn(rng, 5000)
+    A = hk.CSR(dev(rowptr), dev(col), dev(val))
+    B = hk.CSR(dev(rowptr), dev(col), dev(val))
+    B.set_plan(64, 32, 0)
+    ref = oracle.bicgstab if method == "bicgstab" else oracle.tfqmr
+    for kw, okw in (({"x": dev(x0)}, {"x0": x0}), ({"precond": False}, {"precond": False})):
+        print("[case]", method, sorted(kw), flush=True)
+        x, info = hk.krylov_solve(A, dev(b), tol=0.0, max_iter=2, method=method, **kw)
+        xo, _ = ref(rowptr, col, val, b, tol=0.0, maxit=2, **okw)
+        assert info["shape"][0] == 1
+        assert np.linalg.norm(x.cpu().numpy() - xo) <= 1e-11 * np.linalg.norm(xo)
+    x, info = hk.krylov_solve(A, dev(b), tol=1e-12, method=method)
+    y, other = hk.krylov_solve(B, dev(b), tol=1e-12, method=method)
+    assert info["status"] == other["status"] == hk.HK_OK and info["shape"][0] == 1 and other["shape"][0] == 64
+    r = oracle.residual(rowptr, col, val, b, x.cpu().numpy())
+    assert np.linalg.norm(r) <= 1.05e-12 * np.linalg.norm(b) and info["relres_true"] <= 1.05e-12
+    assert torch.equal(x, hk.krylov_solve(A, dev(b), tol=1e-12, method=method)[0])
+    print("[case]", method, "barrier limit of one tick", flush=True)
+    monkeypatch.setenv("HK_BARRIER_SPIN_TICKS", "1")
+    C = hk.CSR(dev(rowptr), dev(col), dev(val))
+    z, late = hk.krylov_solve(C, dev(b), x=dev(x0), tol=1e-12, method=method)
+    assert late["status"] == hk.HK_OK and late["shape"][0] == 64, late
+    assert (z - x).abs().max() <= 1e-10 * x.abs().max()
