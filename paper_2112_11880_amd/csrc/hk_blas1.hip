@@ -99,6 +99,41 @@ __global__ __launch_bounds__(BS) void k_reduce_fin(const double* partials, int n
   }
 }
 
+// Both stages in one workgroup, for vectors of at most kSmallElems elements: a
+// second launch costs more than the loads that one CU takes longer for.
+constexpr int kSmallThreads = 1024;
+constexpr int64_t kSmallElems = 8192;
+template <int KIND>
+__global__ __launch_bounds__(kSmallThreads) void k_reduce_small(int n, const double2* __restrict__ x,
+                                                                const double2* __restrict__ y, double* out) {
+  constexpr int NV = KIND == 2 ? 1 : 2, U = kSmallElems / kSmallThreads;
+  __shared__ double lds[NV * (kSmallThreads / kWave)];
+  double2 a[U], b[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    // past the end: the last element again, left out of the sum
+    const int i = min((int)threadIdx.x + u * kSmallThreads, n - 1);
+    a[u] = x[i];
+    if (KIND != 2) b[u] = y[i];
+  }
+  double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if ((int)threadIdx.x + u * kSmallThreads >= n) break;
+    if (KIND == 0) acc = cfmac(a[u], b[u], acc);
+    else if (KIND == 1) acc = cfma(a[u], b[u], acc);
+    else acc.x = fma(a[u].x, a[u].x, fma(a[u].y, a[u].y, acc.x));
+  }
+  double v[NV];
+  v[0] = acc.x;
+  if (NV == 2) v[NV - 1] = acc.y;
+  block_sum<NV, double, kSmallThreads / kWave>(v, lds);
+  if (threadIdx.x == 0) {
+    if (KIND == 2) out[0] = sqrt(v[0]);
+    else { out[0] = v[0]; out[NV - 1] = v[NV - 1]; }
+  }
+}
+
 template <bool NT>
 __global__ void k_axpy(int64_t n, double2 a, const double2* __restrict__ x, double2* __restrict__ y) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -136,6 +171,12 @@ __global__ void k_zero_res(double* res, int count) {
 // (room for 2 reduce_blocks(n) doubles).
 template <int KIND>
 static int launch_reduce(int64_t n, const void* x, const void* y, void* res, hipStream_t s, double* partials) {
+  if (n <= kSmallElems) {
+    hipLaunchKernelGGL((k_reduce_small<KIND>), dim3(1), dim3(kSmallThreads), 0, s, (int)n, (const double2*)x,
+                       (const double2*)y, (double*)res);
+    HK_CHECK_LAUNCH();
+    return HK_OK;
+  }
   const int nb = reduce_blocks(n);
   if (n >= kNtMinElems)
     hipLaunchKernelGGL((k_reduce<KIND, true>), dim3(nb), dim3(kBlock), 0, s, n, (const double2*)x,
