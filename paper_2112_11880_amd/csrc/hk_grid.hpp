@@ -164,14 +164,27 @@ __device__ __forceinline__ void st_agent_u64(unsigned long long* p, unsigned lon
 }
 
 // Stores element i of a vector that other workgroups read after the next
-// barrier: at agent scope, one 16- or 8-byte store.
+// barrier: at agent scope (sc1), one 16- or 8-byte store.  A buffer store by
+// its builtin, since an agent-scope store of 16 bytes has no other form in the
+// language, and in inline asm the compiler keeps none of the wait states that
+// the store's scalar base and its data registers need around it.
+typedef int ni4 __attribute__((ext_vector_type(4)));
+typedef int ni2 __attribute__((ext_vector_type(2)));
+constexpr int kAuxSc1 = 16;
+template <class V> __device__ __forceinline__ __amdgpu_buffer_rsrc_t pub_rsrc(V* p) {
+  // raw buffer of 32-bit words over the whole offset range; the callers' i is
+  // an element of the vector
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)0xffffffffu, 0x00020000);
+}
 __device__ __forceinline__ void publish(double2* p, unsigned i, double2 v) {
   const nd2 q = {v.x, v.y};
-  asm volatile("global_store_dwordx4 %0, %1, %2 sc1" ::"v"(i * (unsigned)sizeof(v)), "v"(q), "s"(p) : "memory");
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(ni4, q), pub_rsrc(p), (int)(i * (unsigned)sizeof(v)), 0,
+                                         kAuxSc1);
 }
 __device__ __forceinline__ void publish(float2* p, unsigned i, float2 v) {
   const nf2 q = {v.x, v.y};
-  asm volatile("global_store_dwordx2 %0, %1, %2 sc1" ::"v"(i * (unsigned)sizeof(v)), "v"(q), "s"(p) : "memory");
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(ni2, q), pub_rsrc(p), (int)(i * (unsigned)sizeof(v)), 0,
+                                        kAuxSc1);
 }
 
 // v + (v of the lane the DPP control names; 0 where there is none)
