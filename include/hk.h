@@ -235,10 +235,10 @@ typedef struct {
  * check_every iterations (up to 256) is recorded once into a HIP graph on a
  * private stream that waits for `stream`, and replayed; the environment
  * variable HK_SOLVE_GRAPHS=0 launches every kernel on `stream` instead (same
- * results, bit for bit).  BiCGStab and TFQMR on a matrix that fits the
+ * results, bit for bit).  A solve on a matrix that fits the
  * registers and LDS of the device (rows of at most 27 entries; complex128: up
  * to 262,144 rows of at most 15, 131,072 of more; complex64: twice that)
- * instead run as one cooperative launch on `stream`, check_every unused; a
+ * instead runs as one cooperative launch on `stream`, check_every unused; a
  * handle whose launch shape was set (hk_csr_set_plan, hk_csr_set_solver_plan)
  * never does.  A zero
  * diagonal entry with precond = 1, or an unknown method, gives HK_EINVAL.

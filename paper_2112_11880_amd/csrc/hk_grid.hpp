@@ -283,6 +283,88 @@ __device__ __forceinline__ bool grid_sum(const GridSum& gs, unsigned& epoch, int
   return stop != 0;
 }
 
+// ------------------------------------------------ the same for many sums
+//
+// Up to kManySums sums in two trips: every workgroup publishes its partial
+// sums, one wave somewhere in the grid adds each component over the
+// workgroups and publishes the total (kSumReps copies), every workgroup
+// reads the totals.  Two sets of partial words and kSumSets of totals are
+// used in turn: a workgroup that has seen every total of one call knows that
+// all partials of it have been read, and that everybody is past reading the
+// totals of the call before.
+constexpr int kManySums = 96;
+constexpr size_t kManyPart = (size_t)kManySums * kSumBlocks;
+constexpr size_t kManyTot = (size_t)kSumReps * kManySums;
+constexpr size_t kManyWords = 2 * kManyPart + kSumSets * kManyTot;
+
+// `waves`: the workgroup's partial sums by wave, waves[c * W + w] for c < nc,
+// written before the call; totals[c] on return, in LDS.  `call` starts at 0.
+// As grid_sum otherwise; all threads of every workgroup call it.
+template <int NT>
+__device__ __forceinline__ bool grid_sum_many(const GridSum& gs, unsigned long long* many, unsigned& call, int nc,
+                                              const double* waves, double* totals) {
+  constexpr int W = NT / kWave;
+  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  const int G = gridDim.x;
+  unsigned long long* part = many + (call & 1) * kManyPart;
+  unsigned long long* tot = many + 2 * kManyPart + (call % kSumSets) * kManyTot;
+  unsigned long long* old = many + 2 * kManyPart + ((call + kSumSets - 1) % kSumSets) * kManyTot;
+  auto bits_of = [](double s) {
+    return s == s ? (unsigned long long)__double_as_longlong(s) : 0x7ff8000000000000ull;
+  };
+  const unsigned long long t0 = wall_clock64();
+  bool ok = true;
+  auto wait_word = [&](const unsigned long long* p) {
+    unsigned long long q;
+    for (int spins = 0;; ++spins) {
+      q = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (q != kSumEmpty) break;
+      if (wall_clock64() - t0 > gs.spin_limit) atomicExch(gs.abort, 1);
+      if ((spins & 15) == 15 || wall_clock64() - t0 > gs.spin_limit) {
+        if (ld_relaxed_i32(gs.abort)) { ok = false; break; }
+      }
+    }
+    return __longlong_as_double((long long)q);
+  };
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (int c = threadIdx.x; c < nc; c += NT) {
+    double s = 0;
+    for (int j = 0; j < W; ++j) s += waves[c * W + j];
+    st_agent_u64(part + (size_t)c * kSumBlocks + blockIdx.x, bits_of(s));
+  }
+  // the components this wave adds up
+  for (int c = blockIdx.x + G * w; c < nc; c += G * W) {
+    // all of a lane's words in flight together
+    const unsigned long long* pc = part + (size_t)c * kSumBlocks;
+    constexpr int U = kSumBlocks / kWave;
+    unsigned long long v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      v[u] = lane + u * kWave < G
+                 ? __hip_atomic_load(pc + lane + u * kWave, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                 : 0ull;
+    double s = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      s += v[u] == kSumEmpty ? wait_word(pc + lane + u * kWave) : __longlong_as_double((long long)v[u]);
+    s = wave_sum63(s);
+    const unsigned long long q = __shfl(bits_of(s), kWave - 1);
+    if (lane < kSumReps) st_agent_u64(tot + (size_t)lane * kManySums + c, q);
+  }
+  for (int c = threadIdx.x; c < nc; c += NT)
+    totals[c] = wait_word(tot + (size_t)(blockIdx.x % kSumReps) * kManySums + c);
+  if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  const int stop = __syncthreads_or(!ok);
+  for (int c = threadIdx.x; c < nc; c += NT)
+    st_agent_u64(part + (size_t)c * kSumBlocks + blockIdx.x, kSumEmpty);
+  if (call > 0)
+    for (int c = blockIdx.x + G * w; c < nc; c += G * W)
+      if (lane < kSumReps) st_agent_u64(old + (size_t)lane * kManySums + c, kSumEmpty);
+  ++call;
+  return stop != 0;
+}
+
 // Host: the spin limit of a launch, kSpinLimitTicks unless the environment
 // variable HK_BARRIER_SPIN_TICKS holds a positive count (tests use a tiny
 // one to drive the abort path).

@@ -103,8 +103,8 @@ struct ResShape {
   int grid = 0;     // workgroups
 };
 // The shape for A's pattern with values of precision prec (0 complex128, 1
-// complex64) and method (HK_BICGSTAB or HK_TFQMR).
-ResShape resident_shape(const hk_csr_s* A, int prec, int method);
+// complex64).
+ResShape resident_shape(const hk_csr_s* A, int prec);
 // Words and abort flag of its barriers, in the solver workspace.
 size_t resident_scratch_bytes();
 }

@@ -30,156 +30,9 @@
 // Row r of workgroup b: consecutive rows, one per lane, so that the gathers of
 // entry k by a wave touch near-consecutive elements on a mesh in node order;
 // xcd_block gives each XCD one range of the rows, whose vectors its L2 holds.
-#include <algorithm>
-
 #include "hk_resident.hpp"
 
 namespace hk {
-
-template <class V> struct Pair { V u, v; };
-
-// acc - a * b, in explicit multiply-adds: a product's operand has the same bits
-// where its owner and where another thread forms it.
-template <class V> __device__ __forceinline__ V cfnma(V a, V b, V acc) {
-  acc.x = fma(-a.x, b.x, fma(a.y, b.y, acc.x));
-  acc.y = fma(-a.x, b.y, fma(-a.y, b.x, acc.y));
-  return acc;
-}
-
-// A value every thread holds alike, moved to scalar registers (the vector
-// ones are for the matrix).
-__device__ __forceinline__ double uni(double v) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ double2 uni(double2 v) { return make_double2(uni(v.x), uni(v.y)); }
-
-// Element of a published vector at byte offset `off`: a scalar base and a
-// 32-bit lane offset.
-template <class V> __device__ __forceinline__ V at(const V* base, unsigned off) {
-  return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + off);
-}
-// The column offset, hidden from loop-invariant code motion: otherwise the
-// compiler keeps a 64-bit address per entry and vector in registers across
-// iterations, three times what the entries themselves take.
-__device__ __forceinline__ unsigned fresh(unsigned off) {
-  asm volatile("" : "+v"(off));
-  return off;
-}
-
-// v is computed before this point and later loads are issued after it (the
-// compiler keeps loads in order with the clobber, and otherwise gathers all of
-// them in front of the arithmetic).
-template <class V> __device__ __forceinline__ void here(V& v) {
-  asm volatile("" : "+v"(v.x), "+v"(v.y)::"memory");
-}
-
-__device__ __forceinline__ double2 to_d(double2 a) { return a; }
-__device__ __forceinline__ double2 to_d(float2 a) { return to_c128(a); }
-// The same for a matrix entry, converted where it is used: the plain
-// conversion is loop-invariant and the compiler would keep the doubles.
-__device__ __forceinline__ double2 entry_d(double2 a) { return a; }
-__device__ __forceinline__ double2 entry_d(float2 a) {
-  double2 d;
-  asm volatile("v_cvt_f64_f32 %0, %1" : "=v"(d.x) : "v"(a.x));
-  asm volatile("v_cvt_f64_f32 %0, %1" : "=v"(d.y) : "v"(a.y));
-  return d;
-}
-
-// A thread's rows of Ahat = A D^-1: E entries per row, a row's missing ones
-// zero in value and pointing at the row itself.  The values of the last EL
-// entries of each row are in LDS (lv, [RPT][EL][NT]), where the registers do
-// not take them all.
-template <class V, int E, int EL, int RPT, int NT> struct ResRows {
-  static constexpr int ER = E - EL;
-  V a[RPT][ER];
-  unsigned c[RPT][E];
-  V* lv;
-
-  template <class Args> __device__ __forceinline__ void load(int i, int row, bool has, const Args& A) {
-    const int rc = has ? row : A.n - 1;
-    const int s = A.rowptr[rc], len = has ? A.rowptr[rc + 1] - s : 0;
-#pragma unroll
-    for (int k = 0; k < E; ++k) {
-      const int p = len > 0 ? s + min(k, len - 1) : 0;
-      const int cc = A.col[p];
-      const V q = cmul(A.val[p], A.dinv[cc]);
-      V v = k < len ? q : czero<V>();
-      if (k % 4 == 3) here(v);
-      if (k < ER) a[i][k] = v;
-      else lv[(i * EL + k - ER) * NT + threadIdx.x] = v;
-      c[i][k] = (unsigned)(k < len ? cc : rc) * (unsigned)sizeof(V);  // byte offset
-    }
-  }
-  // Sum over the row's entries of a_k comb(k, ld(k, column)), the loads of
-  // kGroup entries at a time issued ahead of the previous group's arithmetic:
-  // left alone the compiler issues every load of the row at once and spills
-  // the matrix.  complex64 rows are summed in double: with a float chain the
-  // refinement cycles of the mixed solve took up to twice the iterations of
-  // the kernels that sum a row's products over lanes (279,496 rows, second
-  // cycle: 606 against 400-425 on average), and the double one costs the same
-  // time, which the gathers set.
-  template <class L, class C> __device__ __forceinline__ V dot(int i, L&& ld, C&& comb) const {
-    constexpr int kBytes = E * RPT * (int)sizeof(V);
-    constexpr int kGroup = kBytes <= 240 ? 4 : kBytes <= 440 ? 3 : 2, NG = (E + kGroup - 1) / kGroup;
-    using X = decltype(ld(0, 0u));
-    double2 acc = make_double2(0, 0);
-    X x[2][kGroup];
-#pragma unroll
-    for (int k = 0; k < kGroup; ++k)
-      if (k < E) x[0][k] = ld(k, fresh(c[i][k]));
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-#pragma unroll
-      for (int k = 0; k < kGroup; ++k) {
-        const int kk = (g + 1) * kGroup + k;
-        if (kk < E) x[(g + 1) & 1][k] = ld(kk, fresh(c[i][kk]));
-      }
-#pragma unroll
-      for (int k = 0; k < kGroup; ++k) {
-        const int kk = g * kGroup + k;
-        if (kk < ER) acc = cfma(entry_d(a[i][kk]), to_d(comb(kk, x[g & 1][k])), acc);
-        else if (kk < E) acc = cfma(to_d(lv[(i * EL + kk - ER) * NT + threadIdx.x]), to_d(comb(kk, x[g & 1][k])), acc);
-      }
-      here(acc);
-    }
-    return vscal<V>(acc);
-  }
-};
-
-template <int NT> struct ResLds {
-  double sums[kSumWords * (NT / kWave + 4)];
-};
-
-// The row this thread works on as its i-th, and whether there is one.
-template <int RPT, int NT> struct ResMap {
-  int r0, rend;
-  __device__ __forceinline__ ResMap(int n, int rows) {
-    r0 = xcd_block(blockIdx.x, gridDim.x) * rows;
-    rend = min(r0 + rows, n);
-  }
-  __device__ __forceinline__ int row(int i) const { return r0 + i * NT + (int)threadIdx.x; }
-  __device__ __forceinline__ bool has(int i) const { return row(i) < rend; }
-};
-
-// The first statuses of both methods (bb = ||b||^2, rr = ||r0||^2).
-__device__ __forceinline__ int res_first_status(double bb, double rr, double theta2, long long maxit) {
-  if (!isfinite(bb) || !isfinite(rr)) return HK_NONFINITE;
-  if (rr <= theta2) return HK_OK;
-  return maxit <= 0 ? HK_NOT_CONVERGED : S_RUN;
-}
-
-__device__ __forceinline__ void res_publish_state(SolveState* st, int status, int bd, double rr, double bb,
-                                                  long long iter, long long iters_done) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  st->status = status;
-  st->bd = bd;
-  st->rr = rr;
-  st->bb = bb;
-  st->iter = iter;
-  st->iters_done = iters_done;
-}
 
 template <class R, int E, int EL, int RPT, int NT>
 __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
@@ -524,17 +377,19 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
 
 // ------------------------------------------------------------------ host side
 
-// all barrier words empty, abort flag 0
+// Scratch: the words of grid_sum, those of grid_sum_many, then 256 bytes that
+// start with the abort flag.  All words empty, abort flag 0:
+constexpr size_t kResWords = kSumSets * kSumSetWords, kResMany = kManyWords;
 __global__ void k_res_reset(unsigned long long* words, int nwords, int* abort) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i < nwords) words[i] = kSumEmpty;
-  if (i == 0) *abort = 0;
+  if (i < nwords) words[i] = words + i == reinterpret_cast<unsigned long long*>(abort) ? 0 : kSumEmpty;
 }
 
-size_t resident_scratch_bytes() { return sizeof(unsigned long long) * kSumSets * kSumSetWords + 256; }
+size_t resident_scratch_bytes() { return sizeof(unsigned long long) * (kResWords + kResMany) + 256; }
 int* resident_abort(void* scratch) {
-  return reinterpret_cast<int*>(static_cast<unsigned long long*>(scratch) + kSumSets * kSumSetWords);
+  return reinterpret_cast<int*>(static_cast<unsigned long long*>(scratch) + kResWords + kResMany);
 }
+unsigned long long* resident_many(void* scratch) { return static_cast<unsigned long long*>(scratch) + kResWords; }
 
 // Rows of up to 8, 15 (tetrahedra) or 27 (hexahedra) entries are held, up to
 // kResMax rows per thread: what 256 registers of each of 512 threads and 160 KB
@@ -546,9 +401,8 @@ static int res_class(int max_row) { return max_row <= 8 ? 0 : max_row <= 15 ? 1 
 constexpr int kResEntries[3] = {8, 15, 27};
 constexpr int kResMax[2][3] = {{2, 2, 1}, {4, 4, 2}};  // [complex64][class]
 
-ResShape resident_shape(const hk_csr_s* A, int prec, int method) {
+ResShape resident_shape(const hk_csr_s* A, int prec) {
   ResShape sh;
-  if (method != HK_BICGSTAB && method != HK_TFQMR) return sh;
   if (A->plan_fixed || A->nnz <= 0 || A->max_row > kResEntries[2]) return sh;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, A->device) != hipSuccess) {
@@ -590,9 +444,8 @@ template <class R> static const void* res_kernel(const ResShape& sh, int method)
   return nullptr;
 }
 
-template <class R>
-hipError_t resident_launch(const ResShape& sh, int method, ResArgs<R> args, void* scratch, hipStream_t s) {
-  const void* kern = res_kernel<R>(sh, method);
+hipError_t resident_launch_kernel(const void* kern, const ResShape& sh, void** kargs, GridSum* gs, void* scratch,
+                                  hipStream_t s) {
   if (!kern) return hipErrorInvalidConfiguration;
   int per = 0, cus = 0, coop = 0, dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -602,16 +455,22 @@ hipError_t resident_launch(const ResShape& sh, int method, ResArgs<R> args, void
   if (e != hipSuccess) return e;
   if (!coop || sh.grid > per * cus || sh.grid > kSumBlocks || sh.rows > sh.rpt * sh.threads)
     return hipErrorInvalidConfiguration;
-  args.rows = sh.rows;
-  args.gs.words = static_cast<unsigned long long*>(scratch);
-  args.gs.abort = resident_abort(scratch);
-  args.gs.spin_limit = barrier_spin_limit();
-  const int nwords = (int)(kSumSets * kSumSetWords);
-  hipLaunchKernelGGL(k_res_reset, dim3(nwords / kBlock), dim3(kBlock), 0, s, args.gs.words, nwords, args.gs.abort);
+  gs->words = static_cast<unsigned long long*>(scratch);
+  gs->abort = resident_abort(scratch);
+  gs->spin_limit = barrier_spin_limit();
+  const int nwords = (int)(resident_scratch_bytes() / sizeof(unsigned long long));
+  hipLaunchKernelGGL(k_res_reset, dim3((nwords + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
+                     static_cast<unsigned long long*>(scratch), nwords, gs->abort);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  void* kargs[] = {&args};
   return hipLaunchCooperativeKernel(kern, dim3(sh.grid), dim3(sh.threads), kargs, 0, s);
+}
+
+template <class R>
+hipError_t resident_launch(const ResShape& sh, int method, ResArgs<R> args, void* scratch, hipStream_t s) {
+  args.rows = sh.rows;
+  void* kargs[] = {&args};
+  return resident_launch_kernel(res_kernel<R>(sh, method), sh, kargs, &args.gs, scratch, s);
 }
 template hipError_t resident_launch<double>(const ResShape&, int, ResArgs<double>, void*, hipStream_t);
 template hipError_t resident_launch<float>(const ResShape&, int, ResArgs<float>, void*, hipStream_t);

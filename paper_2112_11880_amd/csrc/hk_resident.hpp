@@ -1,5 +1,8 @@
-// hk_resident.hpp -- launch interface of the resident solves.
+// hk_resident.hpp -- what the resident solves share (hk_resident.hip,
+// hk_resident_l.hip): a thread's rows of the matrix, the launch.
 #pragma once
+
+#include <algorithm>
 
 #include "hk_grid.hpp"
 #include "hk_internal.hpp"
@@ -27,12 +30,182 @@ template <class R> struct ResArgs {
   double* history;
 };
 
+// ---------------------------------------------------------- device helpers
+
+template <class V> struct Pair { V u, v; };
+
+// acc - a * b, in explicit multiply-adds: a product's operand has the same bits
+// where its owner and where another thread forms it.
+template <class V> __device__ __forceinline__ V cfnma(V a, V b, V acc) {
+  acc.x = fma(-a.x, b.x, fma(a.y, b.y, acc.x));
+  acc.y = fma(-a.x, b.y, fma(-a.y, b.x, acc.y));
+  return acc;
+}
+
+// A value every thread holds alike, moved to scalar registers (the vector
+// ones are for the matrix).
+__device__ __forceinline__ double uni(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double2 uni(double2 v) { return make_double2(uni(v.x), uni(v.y)); }
+template <class T> __device__ __forceinline__ T* uni(T* p) {
+  const unsigned long long b = reinterpret_cast<unsigned long long>(p);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return reinterpret_cast<T*>(((unsigned long long)hi << 32) | lo);
+}
+
+// Element of a published vector at byte offset `off`: a scalar base and a
+// 32-bit lane offset.
+template <class V> __device__ __forceinline__ V at(const V* base, unsigned off) {
+  return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + off);
+}
+// The column offset, hidden from loop-invariant code motion: otherwise the
+// compiler keeps a 64-bit address per entry and vector in registers across
+// iterations, three times what the entries themselves take.
+__device__ __forceinline__ unsigned fresh(unsigned off) {
+  asm volatile("" : "+v"(off));
+  return off;
+}
+
+// v is computed before this point and later loads are issued after it (the
+// compiler keeps loads in order with the clobber, and otherwise gathers all of
+// them in front of the arithmetic).
+template <class V> __device__ __forceinline__ void here(V& v) {
+  asm volatile("" : "+v"(v.x), "+v"(v.y)::"memory");
+}
+
+__device__ __forceinline__ double2 to_d(double2 a) { return a; }
+__device__ __forceinline__ double2 to_d(float2 a) { return to_c128(a); }
+// The same for a matrix entry, converted where it is used: the plain
+// conversion is loop-invariant and the compiler would keep the doubles.
+__device__ __forceinline__ double2 entry_d(double2 a) { return a; }
+__device__ __forceinline__ double2 entry_d(float2 a) {
+  double2 d;
+  asm volatile("v_cvt_f64_f32 %0, %1" : "=v"(d.x) : "v"(a.x));
+  asm volatile("v_cvt_f64_f32 %0, %1" : "=v"(d.y) : "v"(a.y));
+  return d;
+}
+
+// A thread's rows of Ahat = A D^-1: E entries per row, a row's missing ones
+// zero in value and pointing at the row itself.  The values of the last EL
+// entries of each row are in LDS (lv, [RPT][EL][NT]), where the registers do
+// not take them all.
+template <class V, int E, int EL, int RPT, int NT> struct ResRows {
+  static constexpr int ER = E - EL;
+  V a[RPT][ER];
+  unsigned c[RPT][E];
+  V* lv;
+
+  template <class Args> __device__ __forceinline__ void load(int i, int row, bool has, const Args& A) {
+    const int rc = has ? row : A.n - 1;
+    const int s = A.rowptr[rc], len = has ? A.rowptr[rc + 1] - s : 0;
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int p = len > 0 ? s + min(k, len - 1) : 0;
+      const int cc = A.col[p];
+      const V q = cmul(A.val[p], A.dinv[cc]);
+      V v = k < len ? q : czero<V>();
+      if (k % 4 == 3) here(v);
+      if (k < ER) a[i][k] = v;
+      else lv[(i * EL + k - ER) * NT + threadIdx.x] = v;
+      c[i][k] = (unsigned)(k < len ? cc : rc) * (unsigned)sizeof(V);  // byte offset
+    }
+  }
+  // Sum over the row's entries of a_k comb(k, ld(k, column)), the loads of
+  // kGroup entries at a time issued ahead of the previous group's arithmetic:
+  // left alone the compiler issues every load of the row at once and spills
+  // the matrix.  complex64 rows are summed in double: with a float chain the
+  // refinement cycles of the mixed solve took up to twice the iterations of
+  // the kernels that sum a row's products over lanes (279,496 rows, second
+  // cycle: 606 against 400-425 on average), and the double one costs the same
+  // time, which the gathers set.
+  template <class L, class C> __device__ __forceinline__ V dot(int i, L&& ld, C&& comb) const {
+    constexpr int kBytes = E * RPT * (int)sizeof(V);
+    constexpr int kGroup = kBytes <= 240 ? 4 : kBytes <= 440 ? 3 : 2, NG = (E + kGroup - 1) / kGroup;
+    using X = decltype(ld(0, 0u));
+    double2 acc = make_double2(0, 0);
+    X x[2][kGroup];
+#pragma unroll
+    for (int k = 0; k < kGroup; ++k)
+      if (k < E) x[0][k] = ld(k, fresh(c[i][k]));
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        const int kk = (g + 1) * kGroup + k;
+        if (kk < E) x[(g + 1) & 1][k] = ld(kk, fresh(c[i][kk]));
+      }
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        const int kk = g * kGroup + k;
+        if (kk < ER) acc = cfma(entry_d(a[i][kk]), to_d(comb(kk, x[g & 1][k])), acc);
+        else if (kk < E) acc = cfma(to_d(lv[(i * EL + kk - ER) * NT + threadIdx.x]), to_d(comb(kk, x[g & 1][k])), acc);
+      }
+      here(acc);
+    }
+    return vscal<V>(acc);
+  }
+};
+
+template <int NT> struct ResLds {
+  double sums[kSumWords * (NT / kWave + 4)];
+};
+
+// The row this thread works on as its i-th, and whether there is one.
+template <int RPT, int NT> struct ResMap {
+  int r0, rend;
+  __device__ __forceinline__ ResMap(int n, int rows) {
+    r0 = xcd_block(blockIdx.x, gridDim.x) * rows;
+    rend = min(r0 + rows, n);
+  }
+  __device__ __forceinline__ int row(int i) const { return r0 + i * NT + (int)threadIdx.x; }
+  __device__ __forceinline__ bool has(int i) const { return row(i) < rend; }
+};
+
+// The first statuses of both methods (bb = ||b||^2, rr = ||r0||^2).
+__device__ __forceinline__ int res_first_status(double bb, double rr, double theta2, long long maxit) {
+  if (!isfinite(bb) || !isfinite(rr)) return HK_NONFINITE;
+  if (rr <= theta2) return HK_OK;
+  return maxit <= 0 ? HK_NOT_CONVERGED : S_RUN;
+}
+
+__device__ __forceinline__ void res_publish_state(SolveState* st, int status, int bd, double rr, double bb,
+                                                  long long iter, long long iters_done) {
+  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+  st->status = status;
+  st->bd = bd;
+  st->rr = rr;
+  st->bb = bb;
+  st->iter = iter;
+  st->iters_done = iters_done;
+}
+
+// ------------------------------------------------------------------ host side
+
 // Enqueues the solve on s: barrier words, state, then the cooperative
 // launch.  hipErrorInvalidConfiguration (or what the launch gave) if it
 // cannot run here.
 template <class R> hipError_t resident_launch(const ResShape& sh, int method, ResArgs<R> args, void* scratch,
                                               hipStream_t s);
-// The abort flag in the scratch (device address).
+// The same for BiCGStab(l): l = ell; r_q at vecs + 2 q stride and u_q one stride
+// behind it (q = 1 .. ell), read by their row's thread alone; the four
+// published vectors at pubs + i stride (base.pub is not used).
+struct ResLArgs {
+  ResArgs<double> base;
+  int ell;
+  long long stride;
+  double2 *vecs, *pubs;
+  unsigned long long* many;  // words of grid_sum_many, all kSumEmpty at launch
+};
+hipError_t resident_l_launch(const ResShape& sh, ResLArgs args, void* scratch, hipStream_t s);
+// The barrier words at the front of the scratch emptied, the launch itself:
+// kern with sh's grid and the argument struct at kargs[0], whose GridSum is gs.
+hipError_t resident_launch_kernel(const void* kern, const ResShape& sh, void** kargs, GridSum* gs, void* scratch,
+                                  hipStream_t s);
+// The abort flag in the scratch (device address), and the words behind it.
 int* resident_abort(void* scratch);
+unsigned long long* resident_many(void* scratch);
 
 }  // namespace hk

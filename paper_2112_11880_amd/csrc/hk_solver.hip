@@ -840,14 +840,15 @@ static int run_chunks(int* pin, SolveState* st, int m, long long max_iter, hipSt
 }
 
 // The whole solve in one resident launch (hk_resident.hip), after the set-up
-// (wk.dinv, wk.flag; r0 in wk.r with use_x0).  *ran stays false where the
-// system does not fit, or the launch could not run or timed out: nothing of
-// x is written then and the caller goes on with the kernels below.
-template <class R>
-static int resident_solve(hk_csr_s* A, int method, const cplx<R>* val, const cplx<R>* b, cplx<R>* x,
-                          const hk_solve_opts& o, const Work<R>& wk, hk_solve_info* info, bool* ran, hipStream_t s) {
+// (wk.dinv, wk.flag; r0 in wk.r with use_x0).  launch(shape, args) enqueues it
+// with the arguments filled in here.  *ran stays false where the system does
+// not fit, or the launch could not run or timed out: nothing of x is written
+// then and the caller goes on with the kernels below.
+template <class R, class Launch>
+static int resident_solve(hk_csr_s* A, const cplx<R>* val, const cplx<R>* b, cplx<R>* x, const hk_solve_opts& o,
+                          const Work<R>& wk, hk_solve_info* info, bool* ran, hipStream_t s, Launch&& launch) {
   *ran = false;
-  const ResShape sh = resident_shape(A, sizeof(R) == 4 ? 1 : 0, method);
+  const ResShape sh = resident_shape(A, sizeof(R) == 4 ? 1 : 0);
   if (sh.entries == 0) return HK_OK;
   ResArgs<R> a{};
   a.n = (int)A->n;
@@ -859,16 +860,12 @@ static int resident_solve(hk_csr_s* A, int method, const cplx<R>* val, const cpl
   a.x0 = o.use_x0 ? x : nullptr;
   a.r0 = wk.r;
   a.y = wk.y;
-  a.pub[0] = wk.p;
-  a.pub[1] = wk.v;
-  a.pub[2] = wk.s;
-  a.pub[3] = wk.t;
   a.st = wk.st;
   a.flag = wk.flag;
   a.tol = o.tol;
   a.maxit = (long long)o.max_iter;
   a.history = o.d_history;
-  if (resident_launch<R>(sh, method, a, wk.res, s) != hipSuccess) {
+  if (launch(sh, a) != hipSuccess) {
     (void)hipGetLastError();
     return HK_OK;
   }
@@ -888,6 +885,19 @@ static int resident_solve(hk_csr_s* A, int method, const cplx<R>* val, const cpl
   info->shape_tuned = 0;
   info->pad = 0;
   return HK_OK;
+}
+
+// BiCGStab and TFQMR on the workspace wk.
+template <class R>
+static int resident_solve(hk_csr_s* A, int method, const cplx<R>* val, const cplx<R>* b, cplx<R>* x,
+                          const hk_solve_opts& o, const Work<R>& wk, hk_solve_info* info, bool* ran, hipStream_t s) {
+  return resident_solve<R>(A, val, b, x, o, wk, info, ran, s, [&](const ResShape& sh, ResArgs<R>& a) {
+    a.pub[0] = wk.p;
+    a.pub[1] = wk.v;
+    a.pub[2] = wk.s;
+    a.pub[3] = wk.t;
+    return resident_launch<R>(sh, method, a, wk.res, s);
+  });
 }
 
 // Runs the whole solve for precision R on values `val` (A's pattern), right
@@ -1433,6 +1443,8 @@ template <class R> struct BlWork {
   using V = cplx<R>;
   V *y, *rt, *dinv, *ahat;
   BlVecs<R> vec;
+  V* pub[4];  // the resident solve's published vectors
+  void* res;  // and its barrier words
   double* partials;
   SolveState* st;
   int* flag;
@@ -1455,6 +1467,8 @@ template <class R, class Take> static BlWork<R> bl_layout(Take take, int64_t n, 
     w.vec.r[j] = (V*)take(sizeof(V) * n);
     w.vec.u[j] = (V*)take(sizeof(V) * n);
   }
+  for (int j = 0; j < 4; ++j) w.pub[j] = (V*)take(sizeof(V) * n);
+  w.res = (void*)take(resident_scratch_bytes());
   w.ahat = (V*)take(sizeof(V) * (nnz + 1));  // one padding entry (paired-entry products)
   w.partials = (double*)take(sizeof(double) * bl_partial_doubles<R>(n));
   w.st = (SolveState*)take(sizeof(SolveState));
@@ -1826,14 +1840,37 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
   hipLaunchKernelGGL(k_diag_inv<V>, ew, dim3(kBlock), 0, s, n, A->rowptr, A->col, val, wk.dinv,
                      o.precond ? 1 : 0, wk.flag);
   HK_CHECK_LAUNCH();
-  launch_scale_cols<V>(A->nnz, A->col, val, wk.dinv, wk.ahat, s);
-  HK_CHECK_LAUNCH();
   if (o.use_x0) {
     hk_csr_s tmp = *A;
     tmp.val = val;
     int rc = spmv_dispatch(&tmp, x, wk.vec.r[0], b, nullptr, nullptr, 1, s);
     if (rc != HK_OK) return rc;
   }
+  // the common ending (x = D^-1 y, true residual, info) through a Work view
+  Work<R> view{};
+  view.y = wk.y;
+  view.r = wk.vec.r[0];
+  view.dinv = wk.dinv;
+  view.t = wk.vec.u[1];
+  view.partials = wk.partials;
+  view.res = wk.res;
+  view.st = wk.st;
+  view.flag = wk.flag;
+  {
+    bool ran = false;
+    const int rc = resident_solve<R>(A, val, b, x, o, view, info, &ran, s, [&](const ResShape& sh, ResArgs<R>& a) {
+      ResLArgs l{};
+      l.base = a;
+      l.ell = ELL;
+      l.stride = (long long)(align_up(sizeof(V) * A->n) / sizeof(V));
+      l.vecs = wk.vec.r[0];
+      l.pubs = wk.pub[0];
+      return resident_l_launch(sh, l, wk.res, s);
+    });
+    if (rc != HK_OK || ran) return rc;
+  }
+  launch_scale_cols<V>(A->nnz, A->col, val, wk.dinv, wk.ahat, s);
+  HK_CHECK_LAUNCH();
   SpmvPlan dp = A->plan;
   dp.nw = 0;
   SpmvPlan& cached = A->dot_plan[0];
@@ -1906,13 +1943,6 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
     return e;
   });
   if (rc != HK_OK) return rc;
-  // the common ending (x = D^-1 y, true residual, info) through a Work view
-  Work<R> view{};
-  view.y = wk.y;
-  view.dinv = wk.dinv;
-  view.t = wk.vec.u[1];
-  view.partials = wk.partials;
-  view.st = wk.st;
   return finish_solve<R>(A, val, b, x, view, info, s);
 }
 

@@ -85,6 +85,45 @@ def test_resident_iterates(hk, oracle, n, row, shape, method):
         assert np.linalg.norm(x.cpu().numpy() - xo) <= 1e-11 * np.linalg.norm(xo)
 
 
+@pytest.mark.parametrize("n,row,shape", [(1, 1, (1, 4)), (65, 8, (1, 4)), (300, 27, (1, 4)), (300, 28, None), (6000, 15, (1, 4)),
+                                         (16385, 15, (1, 8)), (16385, 8, (1, 8)), (20000, 27, (1, 8)), (131073, 8, (2, 8)),
+                                         (131073, 15, (2, 8))])
+@pytest.mark.parametrize("ell,cycles", [(1, 3), (2, 2), (4, 1)])
+def test_resident_bicgstab_l_iterates(hk, oracle, n, row, shape, ell, cycles):
+    """The minimal-residual coefficients carry the rounding times the condition
+    of the Gram matrix of r_1 .. r_l, whose vectors lie within 1/2 of each other's
+    directions (below 1e5 for l <= 4); they scale a correction of the size of the
+    residual, 1e-2 of the start's by then.  l = 8 is not compared here: eight steps
+    solve these systems, and the oracle's own iterate then changes by 1e6 to 1e10
+    times a change of b (test_resident_bicgstab_8_solves)."""
+    print("[case] bicgstab_l", ell, n, row, flush=True)
+    rowptr, col, val, b = dominant(n, row, n + row)
+    A = hk.CSR(dev(rowptr), dev(col), dev(val))
+    x, info = hk.krylov_solve(A, dev(b), tol=1e-12 if n == 1 else 0.0, max_iter=cycles, method="bicgstab_l", ell=ell)
+    xo, oi = oracle.bicgstab_l(rowptr, col, val, b, ell=ell, tol=1e-12 if n == 1 else 0.0, maxit=cycles)
+    assert info["status"] == oi["status"] and info["iters"] == oi["iters"], (info, oi)
+    assert (tuple(info["shape"][:3]) == (1, *shape)) if shape else info["shape"][0] != 1, info["shape"]
+    assert np.linalg.norm(x.cpu().numpy() - xo) <= 1e-10 * np.linalg.norm(xo)
+
+
+@pytest.mark.parametrize("cells,rpt", [((9, 8, 7), 1), ((30, 29, 31), 1), ((60, 45, 50), 2)])
+def test_resident_bicgstab_8_solves(hk, oracle, cells, rpt):
+    """Meshes of 720, 28,800+ and 143,106 rows, many cycles: the oracle's residual
+    of the solution is the one reported and meets the tolerance, and the monitored
+    residual has not left it by more than the rounding that l = 8 gathers."""
+    from synth import helmholtz as H
+    print("[case] bicgstab(8)", cells, flush=True)
+    m = H.make_mesh(*cells, 1.0 / max(cells), jitter=0.2, rng=np.random.default_rng(3))
+    p = H.build_problem(m)
+    val = H.helmholtz_values(p, complex(9.0, 0.09))
+    b = H.complex_rhs(np.random.default_rng(0), p.n, p.dirichlet)
+    x, info = hk.krylov_solve(hk.CSR(dev(p.rowptr), dev(p.col), dev(val)), dev(b), tol=1e-8, method="bicgstab_l", ell=8)
+    assert info["status"] == hk.HK_OK and info["iters"] > 1 and info["shape"][:2] == [1, rpt], info
+    r = oracle.residual(p.rowptr, p.col, val, b, x.cpu().numpy())
+    rel = np.linalg.norm(r) / np.linalg.norm(b)
+    assert rel <= 1.05e-8 and abs(rel - info["relres_true"]) <= 1e-10 and info["relres_rec"] <= 1e-8
+
+
 @pytest.mark.parametrize("n,row,rpt", [(1000, 8, 1), (16385, 15, 1), (131073, 15, 2), (262145, 15, 3), (393217, 15, 4),
                                        (131072, 27, 1), (131073, 27, 2), (262145, 8, 3), (393217, 8, 4)])
 def test_resident_complex64_iterates(hk, oracle, n, row, rpt):
