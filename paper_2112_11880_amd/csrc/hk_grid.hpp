@@ -125,27 +125,34 @@ __device__ __forceinline__ bool barrier_last(GridBar* bar, unsigned& epoch, F&& 
 // sums as 8-byte words and reads every workgroup's words itself, so one trip
 // through memory is both the barrier and the reduction, and every workgroup
 // holds the totals (summed in one order, so the same bits everywhere).  On
-// MI355X it takes 1.9 us with 20 workgroups, 2.4 with 64, 3.5 with 128 and
-// 5.2 with 256 (three sums), against 9.4 us for the flag barrier above with
-// its release fence, workgroup 0's callback and the second trip.
+// MI355X it takes 1.9 us with 20 workgroups, 2.3 with 64 and 4 with 256
+// (three sums), against 9.4 us for the flag barrier above with its release
+// fence, workgroup 0's callback and the second trip.
 //
 //  - A word is its own flag: kSumEmpty, a NaN no sum is published as, means
 //    "not there yet".  A workgroup that has seen every word of epoch e knows
 //    that all have finished reading epoch e - 1 and empties its own words of
 //    that epoch; with kSumSets sets in turn they are used again at e + 3.
-//  - Each word is published kSumReps times and a workgroup reads copy
-//    blockIdx.x % kSumReps: 256 workgroups polling one copy slow the stores
-//    to it (64 workgroups: 3.2 us with one copy, 2.4 with eight).
+//  - A workgroup's words lie together, so that one 16-byte store or load
+//    moves two of them (each word is still a flag of its own: nothing relies
+//    on the two arriving together).  With three sums a word each, the barrier
+//    took 1.4 us longer at 256 workgroups than with one.
+//  - The words are published kSumReps times and a workgroup reads copy
+//    rank % kSumReps: 256 workgroups polling one copy slow the stores to it
+//    (64 workgroups: 3.2 us with one copy, 2.4 with eight).
 //  - No release fence: what the other workgroups read (publish below) is
 //    stored past the L2 at agent scope, and every wave waits for its stores
 //    before the words are published.  The plain-store form with an L2
 //    write-back took 13-17 us per barrier and gather at 256 workgroups,
 //    against 7.5-10.
-//  - The acquire (an L1 and L2 invalidate) is thread 0's alone, as above.  It
-//    may run before another workgroup has arrived: what it must drop are
-//    lines of a published vector's previous contents, and a vector is stored
-//    only after a barrier that follows its last reads, so no workgroup reads
-//    it between that barrier and the end of this one.
+//  - The acquire (an L1 and L2 invalidate, 1.1 us at 256 workgroups) is thread
+//    0's alone, as above, and only where the caller asks for it: it has to
+//    drop the lines of a published vector's previous contents, so one between
+//    the last reads of a vector's contents and the first reads of the next
+//    ones at the same addresses is enough, and vectors published to kRing
+//    places in turn need one every kRing times (see hk_resident.hpp).  It may
+//    run before another workgroup has arrived: a vector is stored only after
+//    a barrier that follows the last reads of what it overwrites.
 constexpr int kSumSets = 4;
 constexpr int kSumReps = 8;
 constexpr int kSumWords = 4;    // at most this many sums
@@ -163,19 +170,22 @@ __device__ __forceinline__ void st_agent_u64(unsigned long long* p, unsigned lon
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Stores element i of a vector that other workgroups read after the next
-// barrier: at agent scope (sc1), one 16- or 8-byte store.  A buffer store by
-// its builtin, since an agent-scope store of 16 bytes has no other form in the
-// language, and in inline asm the compiler keeps none of the wait states that
-// the store's scalar base and its data registers need around it.
+// Agent-scope (sc1) accesses of 16 bytes have no form in the language; these
+// use the buffer instructions' builtins.  (In inline asm the compiler keeps
+// none of the wait states that a store's scalar base and data registers need
+// around it.)
 typedef int ni4 __attribute__((ext_vector_type(4)));
 typedef int ni2 __attribute__((ext_vector_type(2)));
+typedef unsigned long long nu2 __attribute__((ext_vector_type(2)));
 constexpr int kAuxSc1 = 16;
 template <class V> __device__ __forceinline__ __amdgpu_buffer_rsrc_t pub_rsrc(V* p) {
-  // raw buffer of 32-bit words over the whole offset range; the callers' i is
-  // an element of the vector
+  // raw buffer over the whole 32-bit offset range; the offsets used are those
+  // of elements of p
   return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)0xffffffffu, 0x00020000);
 }
+
+// Stores element i of a vector that other workgroups read after the next
+// barrier.
 __device__ __forceinline__ void publish(double2* p, unsigned i, double2 v) {
   const nd2 q = {v.x, v.y};
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(ni4, q), pub_rsrc(p), (int)(i * (unsigned)sizeof(v)), 0,
@@ -204,20 +214,31 @@ __device__ __forceinline__ double wave_sum63(double v) {
   v = dpp_add<0x142>(v);
   return dpp_add<0x143>(v);
 }
+// A sum as a word: any NaN as the one quiet NaN, never as kSumEmpty.
+__device__ __forceinline__ unsigned long long sum_word(double s) {
+  return s == s ? (unsigned long long)__double_as_longlong(s) : 0x7ff8000000000000ull;
+}
+// (threads that wait) whether to give up: past the limit this thread raises
+// the flag, and now and then looks whether another has.
+__device__ __forceinline__ bool sum_give_up(const GridSum& gs, unsigned long long t0, int spins) {
+  const bool late = wall_clock64() - t0 > gs.spin_limit;
+  if (late) atomicExch(gs.abort, 1);
+  return (late || (spins & 15) == 15) && ld_relaxed_i32(gs.abort) != 0;
+}
 
-// One barrier of a kernel of NT threads per workgroup and at most kSumBlocks
-// workgroups: v (each thread's partial sums) becomes the totals over the
-// grid, in every thread.  `epoch` starts at 0 and prev_nv at 0.  lds: room
-// for kSumWords * (NT / 64 + 4) doubles, used by nothing else.  Returns true
-// if the kernel must stop (a wait passed the limit here or elsewhere).  All
-// threads of every workgroup call it.
+// One barrier of `size` <= kSumBlocks workgroups of NT threads, the caller's
+// being number `rank` of them: v (each thread's partial sums) becomes the
+// totals, in every thread.  `epoch` starts at 0.  lds: room for
+// kSumWords * (NT / 64 + 4) doubles, used by nothing else.  With INV the
+// caller's caches drop what they hold.  Returns true if the kernel must stop
+// (a wait passed the limit here or elsewhere).  All threads of the workgroups
+// call it.
 template <int NV, int NT>
-__device__ __forceinline__ bool grid_sum(const GridSum& gs, unsigned& epoch, int& prev_nv, double (&v)[NV],
-                                         double* lds) {
+__device__ __forceinline__ bool group_sum(const GridSum& gs, int size, int rank, unsigned& epoch, bool inv,
+                                          double (&v)[NV], double* lds) {
   static_assert(NV >= 1 && NV <= kSumWords && NT >= kSumBlocks, "sums and pollers");
-  constexpr int W = NT / kWave;
+  constexpr int W = NT / kWave, NP = (NV + 1) / 2;  // pairs of words
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-  const int G = gridDim.x;
   double* totals = lds + kSumWords * W;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -228,40 +249,46 @@ __device__ __forceinline__ bool grid_sum(const GridSum& gs, unsigned& epoch, int
   __syncthreads();
   unsigned long long* set = gs.words + (epoch % kSumSets) * kSumSetWords;
   unsigned long long* old = gs.words + ((epoch + kSumSets - 1) % kSumSets) * kSumSetWords;
-  if (threadIdx.x < NV * kSumReps) {
-    const int k = threadIdx.x % NV, rep = threadIdx.x / NV;
+  // byte offset of copy `rep` of workgroup b's words
+  auto at_word = [](int rep, int b) { return (rep * kSumBlocks + b) * (kSumWords * 8); };
+  static_assert(kSumReps * kSumWords <= kWave, "one wave publishes");
+  if (threadIdx.x < kSumReps * kSumWords) {
+    const int k = threadIdx.x % kSumWords, rep = threadIdx.x / kSumWords;
     double s = 0;
+    if (k < NV) {
 #pragma unroll
-    for (int j = 0; j < W; ++j) s += lds[k * W + j];
-    // any NaN goes out as the one quiet NaN, never as kSumEmpty
-    const unsigned long long bits = s == s ? (unsigned long long)__double_as_longlong(s) : 0x7ff8000000000000ull;
-    st_agent_u64(set + (size_t)(rep * kSumWords + k) * kSumBlocks + blockIdx.x, bits);
+      for (int j = 0; j < W; ++j) s += lds[k * W + j];
+    }
+    const unsigned long long mine = sum_word(s), next = __shfl_down(mine, 1);
+    if (k % 2 == 0 && k < NV) {
+      const nu2 pair = {mine, next};
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(ni4, pair), pub_rsrc(set), at_word(rep, rank) + k * 8, 0,
+                                             kAuxSc1);
+    }
   }
   bool ok = true;
-  double part[NV];
+  double part[2 * NP];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) part[k] = 0;
-  if ((int)threadIdx.x < G) {
-    const unsigned long long* rd = set + (size_t)(blockIdx.x % kSumReps) * kSumWords * kSumBlocks + threadIdx.x;
+  for (int k = 0; k < 2 * NP; ++k) part[k] = 0;
+  if ((int)threadIdx.x < size) {
+    const int off = at_word(rank % kSumReps, threadIdx.x);
     const unsigned long long t0 = wall_clock64();
-    unsigned long long q[NV];
+    nu2 q[NP];
     for (int spins = 0;; ++spins) {
       bool all = true;
+      asm volatile("" ::: "memory");  // loaded anew in every turn
 #pragma unroll
-      for (int k = 0; k < NV; ++k)
-        q[k] = __hip_atomic_load(rd + k * kSumBlocks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int k = 0; k < NP; ++k)
+        q[k] = __builtin_bit_cast(nu2, __builtin_amdgcn_raw_buffer_load_b128(pub_rsrc(set), off + 16 * k, 0, kAuxSc1));
 #pragma unroll
-      for (int k = 0; k < NV; ++k) all = all && q[k] != kSumEmpty;
+      for (int k = 0; k < NV; ++k) all = all && q[k / 2][k % 2] != kSumEmpty;
       if (all) break;
-      if (wall_clock64() - t0 > gs.spin_limit) atomicExch(gs.abort, 1);
-      if ((spins & 15) == 15 || wall_clock64() - t0 > gs.spin_limit) {
-        if (ld_relaxed_i32(gs.abort)) { ok = false; break; }
-      }
+      if (sum_give_up(gs, t0, spins)) { ok = false; break; }
     }
 #pragma unroll
-    for (int k = 0; k < NV; ++k) part[k] = __longlong_as_double((long long)q[k]);
+    for (int k = 0; k < NV; ++k) part[k] = __longlong_as_double((long long)q[k / 2][k % 2]);
   }
-  if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  if (inv && threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   if (w < kSumBlocks / kWave) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -274,13 +301,19 @@ __device__ __forceinline__ bool grid_sum(const GridSum& gs, unsigned& epoch, int
   for (int k = 0; k < NV; ++k) {
     v[k] = totals[k * 4] + totals[k * 4 + 1] + totals[k * 4 + 2] + totals[k * 4 + 3];
   }
-  if ((int)threadIdx.x < prev_nv * kSumReps) {
-    const int k = threadIdx.x % prev_nv, rep = threadIdx.x / prev_nv;
-    st_agent_u64(old + (size_t)(rep * kSumWords + k) * kSumBlocks + blockIdx.x, kSumEmpty);
+  if (threadIdx.x < 2 * kSumReps) {
+    const nu2 empty = {kSumEmpty, kSumEmpty};
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(ni4, empty), pub_rsrc(old),
+                                           at_word(threadIdx.x / 2, rank) + 16 * (threadIdx.x % 2), 0, kAuxSc1);
   }
-  prev_nv = NV;
   ++epoch;
   return stop != 0;
+}
+
+// The same over the whole grid.
+template <int NV, int NT>
+__device__ __forceinline__ bool grid_sum(const GridSum& gs, unsigned& epoch, bool inv, double (&v)[NV], double* lds) {
+  return group_sum<NV, NT>(gs, gridDim.x, blockIdx.x, epoch, inv, v, lds);
 }
 
 // ------------------------------------------------ the same for many sums
@@ -299,7 +332,7 @@ constexpr size_t kManyWords = 2 * kManyPart + kSumSets * kManyTot;
 
 // `waves`: the workgroup's partial sums by wave, waves[c * W + w] for c < nc,
 // written before the call; totals[c] on return, in LDS.  `call` starts at 0.
-// As grid_sum otherwise; all threads of every workgroup call it.
+// As grid_sum without INV otherwise; all threads of every workgroup call it.
 template <int NT>
 __device__ __forceinline__ bool grid_sum_many(const GridSum& gs, unsigned long long* many, unsigned& call, int nc,
                                               const double* waves, double* totals) {
@@ -309,9 +342,6 @@ __device__ __forceinline__ bool grid_sum_many(const GridSum& gs, unsigned long l
   unsigned long long* part = many + (call & 1) * kManyPart;
   unsigned long long* tot = many + 2 * kManyPart + (call % kSumSets) * kManyTot;
   unsigned long long* old = many + 2 * kManyPart + ((call + kSumSets - 1) % kSumSets) * kManyTot;
-  auto bits_of = [](double s) {
-    return s == s ? (unsigned long long)__double_as_longlong(s) : 0x7ff8000000000000ull;
-  };
   const unsigned long long t0 = wall_clock64();
   bool ok = true;
   auto wait_word = [&](const unsigned long long* p) {
@@ -319,10 +349,7 @@ __device__ __forceinline__ bool grid_sum_many(const GridSum& gs, unsigned long l
     for (int spins = 0;; ++spins) {
       q = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (q != kSumEmpty) break;
-      if (wall_clock64() - t0 > gs.spin_limit) atomicExch(gs.abort, 1);
-      if ((spins & 15) == 15 || wall_clock64() - t0 > gs.spin_limit) {
-        if (ld_relaxed_i32(gs.abort)) { ok = false; break; }
-      }
+      if (sum_give_up(gs, t0, spins)) { ok = false; break; }
     }
     return __longlong_as_double((long long)q);
   };
@@ -331,7 +358,7 @@ __device__ __forceinline__ bool grid_sum_many(const GridSum& gs, unsigned long l
   for (int c = threadIdx.x; c < nc; c += NT) {
     double s = 0;
     for (int j = 0; j < W; ++j) s += waves[c * W + j];
-    st_agent_u64(part + (size_t)c * kSumBlocks + blockIdx.x, bits_of(s));
+    st_agent_u64(part + (size_t)c * kSumBlocks + blockIdx.x, sum_word(s));
   }
   // the components this wave adds up
   for (int c = blockIdx.x + G * w; c < nc; c += G * W) {
@@ -349,12 +376,11 @@ __device__ __forceinline__ bool grid_sum_many(const GridSum& gs, unsigned long l
     for (int u = 0; u < U; ++u)
       s += v[u] == kSumEmpty ? wait_word(pc + lane + u * kWave) : __longlong_as_double((long long)v[u]);
     s = wave_sum63(s);
-    const unsigned long long q = __shfl(bits_of(s), kWave - 1);
+    const unsigned long long q = __shfl(sum_word(s), kWave - 1);
     if (lane < kSumReps) st_agent_u64(tot + (size_t)lane * kManySums + c, q);
   }
   for (int c = threadIdx.x; c < nc; c += NT)
     totals[c] = wait_word(tot + (size_t)(blockIdx.x % kSumReps) * kManySums + c);
-  if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   const int stop = __syncthreads_or(!ok);
   for (int c = threadIdx.x; c < nc; c += NT)
     st_agent_u64(part + (size_t)c * kSumBlocks + blockIdx.x, kSumEmpty);

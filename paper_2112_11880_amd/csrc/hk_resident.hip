@@ -9,10 +9,10 @@
 // dependent loads in each -- 28 us on 4,913 rows, 46-52 us on 117,649, where
 // its bytes alone would take 0.3 and 9 us.  Here an iteration is three (TFQMR:
 // two) barriers that also sum, grid_sum in hk_grid.hpp, and between them
-// row-local arithmetic and the products' gathers: 9.6 us on 4,913 rows, 18.3
-// on 117,649 (5 us per barrier, 3 us per gather of two vectors, which bound it
-// now), TFQMR on 70,224 rows of 27 entries 66 -> 16 us, complex64 BiCGStab on
-// 279,496 rows 60 -> 26.5 us.
+// row-local arithmetic and the products' gathers: 9.6 us on 4,913 rows, 13.3 on
+// 117,649 (3 us per barrier, 2-3 per gather of two vectors, which bound it now),
+// TFQMR on 70,224 rows of 27 entries 66 -> 14.6 us, complex64 BiCGStab on 279,496
+// rows 60 -> 21.8 us.
 //
 // What keeps the barriers so few: a product's operand is a combination, known
 // only after the barrier's scalars, of vectors known before it, and every
@@ -47,9 +47,11 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
   ResRows<V, E, EL, RPT, NT> M;
   M.lv = s_lv;
   V r[RPT], q[RPT], p[RPT], v[RPT], t[RPT];
-  V *const pr = A.pub[0], *const pq = A.pub[1], *const pv = A.pub[2];
+  // r, q and v of iteration `it` (r and q those it starts from).  All three are
+  // read for the last time before the iteration's second barrier, so of the
+  // third barriers of any kRing iterations in a row one drops the caches.
+  auto pub = [&](int i, long long at_it) { return A.pub + (kRing * i + (int)(at_it & (kRing - 1))) * A.stride; };
   unsigned epoch = 0;
-  int nv0 = 0;
   double sum2[2] = {0, 0};
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
@@ -61,8 +63,8 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
       bi = A.b[row];
       ri = A.x0 ? A.r0[row] : bi;
       if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
-      publish(pr, row, ri);
-      publish(pq, row, czero<V>());
+      publish(pub(0, 1), row, ri);
+      publish(pub(1, 1), row, czero<V>());
     }
     r[i] = ri;
     q[i] = p[i] = v[i] = t[i] = czero<V>();
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
     sum2[0] += nrm2d(bi);
     sum2[1] += nrm2d(ri);
   }
-  if (grid_sum<2, NT>(A.gs, epoch, nv0, sum2, lds.sums)) return;
+  if (grid_sum<2, NT>(A.gs, epoch, true, sum2, lds.sums)) return;
   const bool first = blockIdx.x == 0 && threadIdx.x == 0;
   const double bb = uni(sum2[0]), theta2 = uni(A.tol * A.tol * bb);
   double rr = uni(sum2[1]);
@@ -80,6 +82,8 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
   long long it = 1, done = 0;
   if (first && A.history) A.history[0] = bb > 0 ? sqrt(rr / bb) : 0.0;
   while (status == S_RUN) {
+    const V *const pr = pub(0, it), *const pq = pub(1, it);
+    V* const pv = pub(2, it);
     V rg[RPT][kKeep ? E : 1];
     // v = Ahat p, p = r + beta q; sigma = rhat^H v
     double sg[2] = {0, 0};
@@ -100,7 +104,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
         }
       }
     }
-    if (grid_sum<2, NT>(A.gs, epoch, nv0, sg, lds.sums)) return;
+    if (grid_sum<2, NT>(A.gs, epoch, false, sg, lds.sums)) return;
     const double2 sigma = make_double2(sg[0], sg[1]);
     if (!cfinite(sigma)) {
       status = HK_NONFINITE;
@@ -122,11 +126,11 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
       const V s = cfnma(al, v[i], r[i]);
       if constexpr (kKeep)
         t[i] = M.dot(
-            i, [&](int, unsigned c) { return at(pv, c); },
+            i, [&](int, unsigned c) { return at<V>(pv, c); },
             [&](int k, V x) { return cfnma(al, x, rg[i][k]); });
       else
         t[i] = M.dot(
-            i, [&](int, unsigned c) { return Pair<V>{at(pr, c), at(pv, c)}; },
+            i, [&](int, unsigned c) { return Pair<V>{at(pr, c), at<V>(pv, c)}; },
             [&](int, const Pair<V>& x) { return cfnma(al, x.v, x.u); });
       if (m.has(i)) {
         ts[0] += nrm2d(t[i]);
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
         ts[3] += nrm2d(s);
       }
     }
-    if (grid_sum<4, NT>(A.gs, epoch, nv0, ts, lds.sums)) return;
+    if (grid_sum<4, NT>(A.gs, epoch, false, ts, lds.sums)) return;
     const double ss = ts[3];
     const bool half = isfinite(ss) && ss <= theta2;
     if (!half && (!isfinite(ss) || !isfinite(ts[0]) || !isfinite(ts[1]) || !isfinite(ts[2]))) {
@@ -168,13 +172,13 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
       r[i] = cfnma(om, t[i], s);
       q[i] = cfnma(om, v[i], p[i]);
       if (m.has(i)) {
-        publish(pr, m.row(i), r[i]);
-        publish(pq, m.row(i), q[i]);
+        publish(pub(0, it + 1), m.row(i), r[i]);
+        publish(pub(1, it + 1), m.row(i), q[i]);
         xr[0] += nrm2d(r[i]);
         dotc_acc(s_rh[l], r[i], xr[1], xr[2]);
       }
     }
-    if (grid_sum<3, NT>(A.gs, epoch, nv0, xr, lds.sums)) return;
+    if (grid_sum<3, NT>(A.gs, epoch, ((it + 1) & (kRing - 1)) == 0, xr, lds.sums)) return;
     rr = uni(xr[0]);
     done = it;
     const double2 rho1 = uni(make_double2(xr[1], xr[2]));
@@ -215,9 +219,12 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
   ResRows<V, E, EL, RPT, NT> M;
   M.lv = s_lv;
   V y1[RPT], v[RPT], u1[RPT], w[RPT], y2[RPT], u2[RPT];
-  V *const py1 = A.pub[0], *const pv = A.pub[1], *const pw = A.pub[2], *const py2 = A.pub[3];
+  // y1 and v that iteration k starts from, read for the last time before its
+  // first barrier, and w and y2 of its half-steps, before its second: the caches
+  // are dropped at one in kRing of each, y1 and v by second and w and y2 by first
+  // barriers
+  auto pub = [&](int i, long long at_k) { return A.pub + (kRing * i + (int)(at_k & (kRing - 1))) * A.stride; };
   unsigned epoch = 0;
-  int nv0 = 0;
   double sum2[2] = {0, 0};
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
@@ -229,7 +236,7 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
       bi = A.b[row];
       ri = A.x0 ? A.r0[row] : bi;
       if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
-      publish(py1, row, ri);
+      publish(pub(0, 1), row, ri);
     }
     y1[i] = w[i] = ri;
     v[i] = u1[i] = y2[i] = u2[i] = czero<V>();
@@ -239,7 +246,7 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
     sum2[0] += nrm2d(bi);
     sum2[1] += nrm2d(ri);
   }
-  if (grid_sum<2, NT>(A.gs, epoch, nv0, sum2, lds.sums)) return;
+  if (grid_sum<2, NT>(A.gs, epoch, true, sum2, lds.sums)) return;
   const bool first = blockIdx.x == 0 && threadIdx.x == 0;
   const double bb = uni(sum2[0]), theta2 = uni(A.tol * A.tol * bb);
   double rr = uni(sum2[1]), tau = uni(sqrt(rr)), theta = 0;
@@ -276,20 +283,23 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
   if (status == S_RUN) {
     // v = u1 = Ahat y1
     double sg[2] = {0, 0};
+    const V* const py1 = pub(0, 1);
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
       u1[i] = M.dot(
           i, [&](int, unsigned c) { return at(py1, c); }, [&](int, V x) { return x; });
       v[i] = u1[i];
       if (m.has(i)) {
-        publish(pv, m.row(i), v[i]);
+        publish(pub(1, 1), m.row(i), v[i]);
         dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
       }
     }
-    if (grid_sum<2, NT>(A.gs, epoch, nv0, sg, lds.sums)) return;
+    if (grid_sum<2, NT>(A.gs, epoch, false, sg, lds.sums)) return;
     sigma_step(sg);
   }
   while (status == S_RUN) {
+    const V *const py1 = pub(0, k), *const pv = pub(1, k);
+    V *const pw = pub(2, k), *const py2 = pub(3, k);
     // half-steps 1 and 2: w -= alpha u1, ||w||^2; u2 = Ahat y2,
     // w -= alpha u2, ||w||^2, rhat^H w
     double hs[4] = {0, 0, 0, 0};
@@ -310,7 +320,7 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
         dotc_acc(s_rh[i * NT + threadIdx.x], w[i], hs[2], hs[3]);
       }
     }
-    if (grid_sum<4, NT>(A.gs, epoch, nv0, hs, lds.sums)) return;
+    if (grid_sum<4, NT>(A.gs, epoch, (k & (kRing - 1)) == 0, hs, lds.sums)) return;
     const V eta1 = half_step(hs[0], 2 * k - 1);
     const V coef2 = uni(cdiv(cmul(make_double2(theta * theta, 0), eta1), alpha));
     done = k;
@@ -356,16 +366,16 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
     for (int i = 0; i < RPT; ++i) {
       y1[i] = cfma(beta, y2[i], w[i]);
       u1[i] = M.dot(
-          i, [&](int, unsigned c) { return Pair<V>{at(py2, c), at(pw, c)}; },
+          i, [&](int, unsigned c) { return Pair<V>{at<V>(py2, c), at<V>(pw, c)}; },
           [&](int, const Pair<V>& x) { return cfma(beta, x.u, x.v); });
       v[i] = cfma(beta, cfma(beta, v[i], u2[i]), u1[i]);
       if (m.has(i)) {
-        publish(py1, m.row(i), y1[i]);
-        publish(pv, m.row(i), v[i]);
+        publish(pub(0, k + 1), m.row(i), y1[i]);
+        publish(pub(1, k + 1), m.row(i), v[i]);
         dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
       }
     }
-    if (grid_sum<2, NT>(A.gs, epoch, nv0, sg, lds.sums)) return;
+    if (grid_sum<2, NT>(A.gs, epoch, ((k + 1) & (kRing - 1)) == 0, sg, lds.sums)) return;
     ++k;
     sigma_step(sg);
   }
@@ -395,7 +405,7 @@ unsigned long long* resident_many(void* scratch) { return static_cast<unsigned l
 // kResMax rows per thread: what 256 registers of each of 512 threads and 160 KB
 // of LDS per CU take.  Beyond it the values no longer fit.  Within it the
 // resident launch is the faster one at every size (1.8M rows do not fit, 279,496
-// in complex64 2.3x, 4,913 rows 4.5x with the recording of the graph that the
+// in complex64 2.8x, 4,913 rows 4.5x with the recording of the graph that the
 // separate kernels need), so there is no lower limit.
 static int res_class(int max_row) { return max_row <= 8 ? 0 : max_row <= 15 ? 1 : 2; }
 constexpr int kResEntries[3] = {8, 15, 27};

@@ -10,6 +10,17 @@
 
 namespace hk {
 
+// Published vectors go to kRing places in turn, so that the caches have to be
+// dropped (group_sum's argument) once in several publications only: content c
+// is at place c % kRing, and takes the place of content c - kRing.  Wanted is
+// one barrier that drops them, entered by every workgroup after the last reads
+// of content c - kRing -- a barrier that those reads merely precede in their own
+// workgroup is not enough, another one on the same L2 may still read -- and left
+// before the first reads of content c.  Each kernel says which of its barriers
+// these are.  Dropping them at every barrier cost 1.1 us of each at 256
+// workgroups.
+constexpr int kRing = 4;
+
 template <class R> struct ResArgs {
   using V = cplx<R>;
   int n, rows;             // rows per workgroup: a multiple of 64
@@ -21,7 +32,8 @@ template <class R> struct ResArgs {
   const V* x0;             // null: start from 0; else r0 holds b - A x0
   const V* r0;
   V* y;                    // D x at the end
-  V* pub[4];               // vectors the workgroups publish to each other
+  V* pub;                  // published vectors: vector i, place p at pub + (kRing i + p) stride
+  long long stride;        // elements
   SolveState* st;          // the solve's state at the end
   const int* flag;         // zero-diagonal flag of the set-up: nonzero ends the kernel
   GridSum gs;
@@ -190,13 +202,11 @@ __device__ __forceinline__ void res_publish_state(SolveState* st, int status, in
 template <class R> hipError_t resident_launch(const ResShape& sh, int method, ResArgs<R> args, void* scratch,
                                               hipStream_t s);
 // The same for BiCGStab(l): l = ell; r_q at vecs + 2 q stride and u_q one stride
-// behind it (q = 1 .. ell), read by their row's thread alone; the four
-// published vectors at pubs + i stride (base.pub is not used).
+// behind it (q = 1 .. ell), read by their row's thread alone.
 struct ResLArgs {
   ResArgs<double> base;
   int ell;
-  long long stride;
-  double2 *vecs, *pubs;
+  double2* vecs;
   unsigned long long* many;  // words of grid_sum_many, all kSumEmpty at launch
 };
 hipError_t resident_l_launch(const ResShape& sh, ResLArgs args, void* scratch, hipStream_t s);

@@ -4,7 +4,7 @@
 //
 // As separate kernels a BiCG step on 232,897 rows took 75 us: two products of
 // 17.8, the passes over the r_i and u_i of 10.5 and 8.6, finalize launches of 4.7
-// each.  Here it takes 40 us: two barriers of 5, two gathers of two vectors for
+// each.  Here it takes 36 us: two barriers of 4, two gathers of two vectors for
 // two rows per thread of 6-7, the pass over the r_i and u_i.  With j the step,
 //   u_j = r_j - beta u_j:      u_{j+1} = Ahat u_j gathers the last r and u products
 //   r_j - alpha u_{j+1}:       r_{j+1} = Ahat r_j gathers the last r and the new u
@@ -80,10 +80,13 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
   __shared__ int s_ok;
   __shared__ V s_rt[RPT * NT], s_y[RPT * NT], s_lv[EL > 0 ? RPT * EL * NT : 1];
   const ResArgs<double>& A = L.base;
-  // r_q and u_q of the private vectors, and the published ones
-  auto priv_r = [&](int q) { return L.vecs + 2 * q * L.stride; };
-  auto priv_u = [&](int q) { return L.vecs + (2 * q + 1) * L.stride; };
-  auto pub = [&](int i) { return L.pubs + i * L.stride; };
+  // r_q and u_q of the private vectors; the published r and u number c.  u is
+  // read for the last time before the next step's first barrier and r before its
+  // second, so with four places the caches are dropped at every other second
+  // barrier, and where a cycle ends
+  auto priv_r = [&](int q) { return L.vecs + 2 * q * A.stride; };
+  auto priv_u = [&](int q) { return L.vecs + (2 * q + 1) * A.stride; };
+  auto pub = [&](int i, unsigned c) { return A.pub + (kRing * i + (int)(c & (kRing - 1))) * A.stride; };
   if (*A.flag) return;
   const int ell = L.ell, lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
   const ResMap<RPT, NT> m(A.n, A.rows);
@@ -91,7 +94,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
   M.lv = s_lv;
   V r0[RPT], u0[RPT], u1[RPT], un[RPT], rn[RPT];
   unsigned epoch = 0, many_calls = 0;
-  int nv0 = 0;
+  unsigned np = 0;  // number of the newest r and u
   double sum2[2] = {0, 0};
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
@@ -103,8 +106,8 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
       bi = A.b[row];
       ri = A.x0 ? A.r0[row] : bi;
       if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
-      publish(pub(0), row, ri);
-      publish(pub(2), row, czero<V>());
+      publish(pub(0, 0), row, ri);
+      publish(pub(1, 0), row, czero<V>());
     }
     r0[i] = ri;
     u0[i] = u1[i] = un[i] = rn[i] = czero<V>();
@@ -113,7 +116,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
     sum2[0] += nrm2d(bi);
     sum2[1] += nrm2d(ri);
   }
-  if (grid_sum<2, NT>(A.gs, epoch, nv0, sum2, lds.sums)) return;
+  if (grid_sum<2, NT>(A.gs, epoch, true, sum2, lds.sums)) return;
   const bool first = blockIdx.x == 0 && threadIdx.x == 0;
   const double bb = uni(sum2[0]), theta2 = uni(A.tol * A.tol * bb);
   double rr = uni(sum2[1]);
@@ -153,9 +156,8 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
   if (status == S_RUN) cycle_start(make_double2(rr, 0));
   while (status == S_RUN) {
     for (int j = 0; j < ell; ++j) {
-      const V* pr = pub(j & 1);
-      const V* pu = pub(2 + (j & 1));
-      V *pr2 = pub((j + 1) & 1), *pu2 = pub(2 + ((j + 1) & 1));
+      const V *const pr = pub(0, np), *const pu = pub(1, np);
+      V *const pr2 = pub(0, np + 1), *const pu2 = pub(1, np + 1);
       // u_{j+1} = Ahat u_j, u_j = r_j - beta u_j; rt^H u_{j+1}
       double sg[2] = {0, 0};
 #pragma unroll
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
           dotc_acc(s_rt[i * NT + threadIdx.x], un[i], sg[0], sg[1]);
         }
       }
-      if (grid_sum<2, NT>(A.gs, epoch, nv0, sg, lds.sums)) return;
+      if (grid_sum<2, NT>(A.gs, epoch, false, sg, lds.sums)) return;
       const V gam = uni(make_double2(sg[0], sg[1]));
       if (!cfinite(gam)) {
         status = HK_NONFINITE;
@@ -203,7 +205,8 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
         sum2[0] = rs[0];
         break;
       }
-      if (grid_sum<3, NT>(A.gs, epoch, nv0, rs, lds.sums)) return;
+      if (grid_sum<3, NT>(A.gs, epoch, ((np + 1) & 1) == 0, rs, lds.sums)) return;
+      ++np;
       rr = uni(rs[0]);
       stop_r();
       if (status != S_RUN) break;
@@ -345,13 +348,14 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
       r0[i] = r;
       u0[i] = u;
       if (m.has(i)) {
-        publish(pub(0), m.row(i), r);
-        publish(pub(2), m.row(i), u);
+        publish(pub(0, np + 2), m.row(i), r);
+        publish(pub(1, np + 2), m.row(i), u);
         mr[0] += nrm2d(r);
         dotc_acc(s_rt[l], r, mr[1], mr[2]);
       }
     }
-    if (grid_sum<3, NT>(A.gs, epoch, nv0, mr, lds.sums)) return;
+    if (grid_sum<3, NT>(A.gs, epoch, true, mr, lds.sums)) return;
+    np += 2;
     rr = uni(mr[0]);
     done = k;
     note(k);

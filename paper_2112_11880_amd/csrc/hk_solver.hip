@@ -500,12 +500,15 @@ __global__ void k_add_c64(int n, const float2* __restrict__ d, double2* __restri
 
 // ------------------------------------------------------------------- driver
 
+constexpr int kResVecs = 4;  // BiCGStab publishes three vectors, TFQMR four
+
 template <class R> struct Work {
   using V = cplx<R>;
   V *y, *r, *rh, *p, *v, *s, *t, *dinv, *ahat;
   V *u, *d;  // TFQMR only
+  V* pub;     // the resident solves' published vectors (kResVecs kRing of them)
+  void* res;  // and their barrier words
   double* partials;
-  void* res;  // the resident solves' barrier words
   SolveState* st;
   int* flag;
 };
@@ -515,8 +518,10 @@ static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 // The workspace layout is written once, as a sequence of take(bytes) calls;
 // work_bytes runs it with a counting take, carve with one that hands out
 // addresses, so the size and the layout cannot disagree.
-template <class R, class Take> static Work<R> layout(Take take, int64_t n, int64_t nnz) {
+template <class R, class Take> static Work<R> layout(Take take, const hk_csr_s* A) {
   using V = cplx<R>;
+  const int64_t n = A->n, nnz = A->nnz;
+  const bool res = resident_shape(A, sizeof(R) == 4 ? 1 : 0).entries != 0;
   Work<R> w;
   w.y = (V*)take(sizeof(V) * n);
   w.r = (V*)take(sizeof(V) * n);
@@ -530,21 +535,22 @@ template <class R, class Take> static Work<R> layout(Take take, int64_t n, int64
   w.d = (V*)take(sizeof(V) * n);
   w.ahat = (V*)take(sizeof(V) * (nnz + 1));  // one padding entry (paired-entry products)
   w.partials = (double*)take(sizeof(double) * 4 * partial_slots(n));
-  w.res = (void*)take(resident_scratch_bytes());
+  w.pub = (V*)take(res ? kResVecs * kRing * align_up(sizeof(V) * n) : 0);
+  w.res = (void*)take(res ? resident_scratch_bytes() : 0);
   w.st = (SolveState*)take(sizeof(SolveState));
   w.flag = (int*)take(64);
   return w;
 }
 
-template <class R> static size_t work_bytes(int64_t n, int64_t nnz) {
+template <class R> static size_t work_bytes(const hk_csr_s* A) {
   size_t q = 0;
-  (void)layout<R>([&](size_t bytes) { q += align_up(bytes); return (char*)nullptr; }, n, nnz);
+  (void)layout<R>([&](size_t bytes) { q += align_up(bytes); return (char*)nullptr; }, A);
   return q;
 }
 
-template <class R> static Work<R> carve(void* base, int64_t n, int64_t nnz) {
+template <class R> static Work<R> carve(void* base, const hk_csr_s* A) {
   char* q = static_cast<char*>(base);
-  return layout<R>([&](size_t bytes) { char* r = q; q += align_up(bytes); return r; }, n, nnz);
+  return layout<R>([&](size_t bytes) { char* r = q; q += align_up(bytes); return r; }, A);
 }
 
 static int ensure_ws(void** ws, size_t* have, size_t need, hipStream_t s) {
@@ -860,6 +866,7 @@ static int resident_solve(hk_csr_s* A, const cplx<R>* val, const cplx<R>* b, cpl
   a.x0 = o.use_x0 ? x : nullptr;
   a.r0 = wk.r;
   a.y = wk.y;
+  a.stride = (long long)(align_up(sizeof(cplx<R>) * A->n) / sizeof(cplx<R>));
   a.st = wk.st;
   a.flag = wk.flag;
   a.tol = o.tol;
@@ -892,10 +899,7 @@ template <class R>
 static int resident_solve(hk_csr_s* A, int method, const cplx<R>* val, const cplx<R>* b, cplx<R>* x,
                           const hk_solve_opts& o, const Work<R>& wk, hk_solve_info* info, bool* ran, hipStream_t s) {
   return resident_solve<R>(A, val, b, x, o, wk, info, ran, s, [&](const ResShape& sh, ResArgs<R>& a) {
-    a.pub[0] = wk.p;
-    a.pub[1] = wk.v;
-    a.pub[2] = wk.s;
-    a.pub[3] = wk.t;
+    a.pub = wk.pub;
     return resident_launch<R>(sh, method, a, wk.res, s);
   });
 }
@@ -907,7 +911,7 @@ static int bicgstab(hk_csr_s* A, const cplx<R>* val, const cplx<R>* b, cplx<R>* 
                     const hk_solve_opts& o, void* wsbase, hk_solve_info* info, hipStream_t s) {
   using V = cplx<R>;
   const int n = (int)A->n;
-  const Work<R> wk = carve<R>(wsbase, A->n, A->nnz);
+  const Work<R> wk = carve<R>(wsbase, A);
   const dim3 ew((unsigned)((n + kBlock - 1) / kBlock));
   const int gv = ew_blocks(n);
 
@@ -1337,7 +1341,7 @@ static int tfqmr(hk_csr_s* A, const double2* val, const double2* b, double2* x, 
   using R = double;
   using V = double2;
   const int n = (int)A->n;
-  const Work<R> wk = carve<R>(wsbase, A->n, A->nnz);
+  const Work<R> wk = carve<R>(wsbase, A);
   const dim3 ew((unsigned)((n + kBlock - 1) / kBlock));
   const int gv = ew_blocks(n);
   V *w = wk.r, *y1 = wk.p, *y2 = wk.s, *u2 = wk.t, *u1 = wk.u, *d = wk.d, *v = wk.v;
@@ -1443,7 +1447,7 @@ template <class R> struct BlWork {
   using V = cplx<R>;
   V *y, *rt, *dinv, *ahat;
   BlVecs<R> vec;
-  V* pub[4];  // the resident solve's published vectors
+  V* pub;     // the resident solve's published vectors (2 kRing of them)
   void* res;  // and its barrier words
   double* partials;
   SolveState* st;
@@ -1457,8 +1461,10 @@ template <class R> static size_t bl_partial_doubles(int64_t n) {
 }
 
 // One layout for sizing and carving, as for the BiCGStab/TFQMR workspace.
-template <class R, class Take> static BlWork<R> bl_layout(Take take, int64_t n, int64_t nnz, int ell) {
+template <class R, class Take> static BlWork<R> bl_layout(Take take, const hk_csr_s* A, int ell) {
   using V = cplx<R>;
+  const int64_t n = A->n, nnz = A->nnz;
+  const bool res = resident_shape(A, 0).entries != 0;
   BlWork<R> w{};
   w.y = (V*)take(sizeof(V) * n);
   w.rt = (V*)take(sizeof(V) * n);
@@ -1467,8 +1473,8 @@ template <class R, class Take> static BlWork<R> bl_layout(Take take, int64_t n, 
     w.vec.r[j] = (V*)take(sizeof(V) * n);
     w.vec.u[j] = (V*)take(sizeof(V) * n);
   }
-  for (int j = 0; j < 4; ++j) w.pub[j] = (V*)take(sizeof(V) * n);
-  w.res = (void*)take(resident_scratch_bytes());
+  w.pub = (V*)take(res ? 2 * kRing * align_up(sizeof(V) * n) : 0);
+  w.res = (void*)take(res ? resident_scratch_bytes() : 0);
   w.ahat = (V*)take(sizeof(V) * (nnz + 1));  // one padding entry (paired-entry products)
   w.partials = (double*)take(sizeof(double) * bl_partial_doubles<R>(n));
   w.st = (SolveState*)take(sizeof(SolveState));
@@ -1476,15 +1482,15 @@ template <class R, class Take> static BlWork<R> bl_layout(Take take, int64_t n, 
   return w;
 }
 
-template <class R> static size_t bl_work_bytes(int64_t n, int64_t nnz, int ell) {
+template <class R> static size_t bl_work_bytes(const hk_csr_s* A, int ell) {
   size_t q = 0;
-  (void)bl_layout<R>([&](size_t bytes) { q += align_up(bytes); return (char*)nullptr; }, n, nnz, ell);
+  (void)bl_layout<R>([&](size_t bytes) { q += align_up(bytes); return (char*)nullptr; }, A, ell);
   return q;
 }
 
-template <class R> static BlWork<R> bl_carve(void* base, int64_t n, int64_t nnz, int ell) {
+template <class R> static BlWork<R> bl_carve(void* base, const hk_csr_s* A, int ell) {
   char* q = static_cast<char*>(base);
-  return bl_layout<R>([&](size_t bytes) { char* r = q; q += align_up(bytes); return r; }, n, nnz, ell);
+  return bl_layout<R>([&](size_t bytes) { char* r = q; q += align_up(bytes); return r; }, A, ell);
 }
 
 // u_i = r_i - beta u_i, i = 0..j
@@ -1832,7 +1838,7 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
   using R = double;
   using V = double2;
   const int n = (int)A->n;
-  const BlWork<R> wk = bl_carve<R>(wsbase, A->n, A->nnz, ELL);
+  const BlWork<R> wk = bl_carve<R>(wsbase, A, ELL);
   const dim3 ew((unsigned)((n + kBlock - 1) / kBlock));
   const int gv = ew_blocks(n);
 
@@ -1862,9 +1868,8 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
       ResLArgs l{};
       l.base = a;
       l.ell = ELL;
-      l.stride = (long long)(align_up(sizeof(V) * A->n) / sizeof(V));
+      l.base.pub = wk.pub;
       l.vecs = wk.vec.r[0];
-      l.pubs = wk.pub[0];
       return resident_l_launch(sh, l, wk.res, s);
     });
     if (rc != HK_OK || ran) return rc;
@@ -2006,13 +2011,13 @@ extern "C" int hk_krylov_solve(hk_csr A, const void* d_b, void* d_x, const hk_so
   for (int k = 0; k < 4; ++k) info->shape[k] = 0;  // a resident solve reports its own
   if (A->dtype == HK_C64) {
     if (opts->method != HK_BICGSTAB) HK_FAIL(HK_EINVAL, "hk_krylov_solve: complex64 solves use BiCGStab only");
-    rc = ensure_ws(&A->ws32, &A->ws32_bytes, work_bytes<float>(A->n, A->nnz), s);
+    rc = ensure_ws(&A->ws32, &A->ws32_bytes, work_bytes<float>(A), s);
     if (rc != HK_OK) return rc;
     rc = bicgstab<float>(A, (const float2*)A->val, (const float2*)d_b, (float2*)d_x, *opts, A->ws32,
                          info, s);
   } else {
-    const size_t need = opts->method == HK_BICGSTAB_L ? bl_work_bytes<double>(A->n, A->nnz, opts->ell)
-                                                      : work_bytes<double>(A->n, A->nnz);
+    const size_t need = opts->method == HK_BICGSTAB_L ? bl_work_bytes<double>(A, opts->ell)
+                                                      : work_bytes<double>(A);
     rc = ensure_ws(&A->ws, &A->ws_bytes, need, s);
     if (rc != HK_OK) return rc;
     if (opts->method == HK_BICGSTAB_L)
@@ -2045,13 +2050,13 @@ extern "C" int hk_krylov_solve_mixed(hk_csr A, const void* d_b, void* d_x, doubl
   const size_t extra = align_up(16 * n) + 2 * align_up(8 * n) + align_up(64);
   rc = ensure_pinned(A);
   if (rc != HK_OK) return rc;
-  rc = ensure_ws(&A->ws32, &A->ws32_bytes, work_bytes<float>(A->n, A->nnz) + extra, s);
+  rc = ensure_ws(&A->ws32, &A->ws32_bytes, work_bytes<float>(A) + extra, s);
   if (rc != HK_OK) return rc;
   if (!A->val32) {
     if (hipMalloc(&A->val32, 8 * (size_t)(A->nnz > 0 ? A->nnz : 1)) != hipSuccess)
       HK_FAIL(HK_ENOMEM, "hk_krylov_solve_mixed: hipMalloc failed");
   }
-  char* tail = (char*)A->ws32 + work_bytes<float>(A->n, A->nnz);
+  char* tail = (char*)A->ws32 + work_bytes<float>(A);
   double2* r = (double2*)tail;
   float2* r32 = (float2*)(tail + align_up(16 * n));
   float2* d32 = (float2*)(tail + align_up(16 * n) + align_up(8 * n));
