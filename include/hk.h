@@ -281,7 +281,7 @@ int hk_krylov_solve_mixed(hk_csr A, const void* d_b, void* d_x, double inner_tol
  * longer than the limit (default 4 s; the environment variable
  * HK_BARRIER_SPIN_TICKS, read at each call, sets it in 100 MHz ticks) raises
  * an abort flag, every workgroup leaves at its next barrier, and the call
- * frees its workspace and returns HK_EHIP with "grid barrier timed out".
+ * returns HK_EHIP with "grid barrier timed out".
  * With opts->d_history non-null (device, 8 (max_iter + 1) doubles, caller
  * owned) the solve records barrier times in it: entry e (e >= 1, the e-th
  * barrier of the launch) = the device's 100 MHz wall clock when the last
@@ -346,7 +346,12 @@ int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, const int32_
  * {32, 0, 0, TR} gives each row 32 lanes.  With opts->shape all 0 the
  * shape is tuned and cached as for hk_sweep_solve (key: device, n, nnz,
  * longest row, nsys) over all 14 candidates; a nonzero opts->shape must be
- * one of them.  infos[k].shape holds the shape used.
+ * one of them.  infos[k].shape holds the shape.  Where every system fits the
+ * registers of the device (the limits of hk_krylov_solve, per system), no
+ * shape is given and no barrier times are asked for, the systems are instead
+ * solved side by side by workgroups that keep their rows in registers, still
+ * in one cooperative launch; the tiled launch in the shape reported takes over
+ * if that one times out.  The workspace is kept in the handle.
  */
 int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off, const void* d_b, void* d_x,
                        const hk_solve_opts* opts, hk_solve_info* infos, void* stream);

@@ -29,6 +29,7 @@
 
 #include "hk_grid.hpp"
 #include "hk_internal.hpp"
+#include "hk_resident.hpp"
 #include "hk_spmv.hpp"
 
 namespace hk {
@@ -1775,13 +1776,14 @@ __global__ void k_sweep_diag_check(int n, int nsys, const double* kd, const doub
 
 // d, dinv of a complex CSR; flag[0] |= 1 on a zero diagonal; flag[0] |= 2 if
 // a row has a column outside its system's row range.
-__global__ void k_bd_diag(int n, const int* __restrict__ rowptr, const int* __restrict__ col,
-                          const double2* __restrict__ val, const int* __restrict__ sys_of_row,
-                          const int* __restrict__ sys_begin, const int* __restrict__ sys_end,
-                          double2* d, double2* dinv, int* flag) {
+__global__ void k_bd_diag(int n, int nsys, const int* __restrict__ rowptr, const int* __restrict__ col,
+                          const double2* __restrict__ val, const int* __restrict__ sys_begin,
+                          const int* __restrict__ sys_end, double2* d, double2* dinv, int* flag) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
-  const int s = sys_of_row[i];
+  int s = 0;  // the last system that begins at or before row i
+  for (int step = kSys / 2; step > 0; step /= 2)
+    if (s + step < nsys && sys_begin[s + step] <= i) s += step;
   const int lo = sys_begin[s], hi = sys_end[s];
   double2 dd = make_double2(0, 0);
   for (int p = rowptr[i]; p < rowptr[i + 1]; ++p) {
@@ -2167,67 +2169,93 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
     gmax = std::max(gmax, g);
   }
   std::vector<int> sys_end(kSys, 0), sys_begin(kSys, 0);
-  std::vector<int> sys_of_row((size_t)A->n);
   for (int k = 0; k < nsys; ++k) {
     sys_begin[k] = (int)row_off[k];
     sys_end[k] = (int)row_off[k + 1];
-    for (int64_t r = row_off[k]; r < row_off[k + 1]; ++r) sys_of_row[r] = k;
   }
+  // the resident solve of the systems (hk_resident.hip), where each fits; the
+  // barrier stamps are those of the tiled launch, and a shape given is its
+  ResBatchPlan rp;
+  const bool resident = !shape_given(opts) && !opts->d_history && resident_batch_plan(A, nsys, row_off, &rp);
   // static tiles of tile_rows rows that never straddle systems; the arrays
   // are sized for the smallest tiles
   int nt_max = 0;
   for (int k = 0; k < nsys; ++k) nt_max += (int)((row_off[k + 1] - row_off[k] + 511) / 512);
   const int64_t n = A->n;
   Arena ar;
-  const size_t bytes = 8 * a256(16 * (size_t)n) + 3 * a256(4 * (size_t)nt_max) +
-                       a256(4 * (size_t)n) + 4 * a256(4 * (kSys + 1)) + a256(8 * 4 * (size_t)gmax * kSys) +
+  // the tiled launch's six vectors, or the resident solve's published ones
+  const size_t vstride = a256(16 * (size_t)std::max<int64_t>(n, rp.stride)) / 16;
+  const size_t nvec = resident ? std::max(6, 3 * kRing) : 6;
+  const size_t set_words = kSumSets * kSumSetWords, njobs = rp.job_sys.size();
+  const size_t bytes = 16 * vstride * nvec + 2 * a256(16 * (size_t)n) + 3 * a256(4 * (size_t)nt_max) +
+                       3 * a256(4 * (kSys + 1)) + a256(8 * 4 * (size_t)gmax * kSys) +
                        a256(sizeof(BatchState)) + a256(sizeof(GridBar)) + a256(8 * 4 * (size_t)kXcds * kSys) +
-                       a256(64);
-  if (hipMalloc((void**)&ar.base, bytes) != hipSuccess) HK_FAIL(HK_ENOMEM, "hk_blockdiag_solve: hipMalloc(%zu)", bytes);
+                       a256(64) + (resident ? a256(8 * (2 * nsys * set_words + 32)) +
+                       a256(sizeof(ResBatchSystem) * kSys) + a256(sizeof(ResBatchEnd) * kSys) +
+                       a256(4 * rp.job_ptr.size()) + 2 * a256(4 * njobs) : 0);
+  if (A->bws_bytes < bytes) {
+    if (A->bws) {
+      HK_HIP(hipStreamSynchronize(s));
+      HK_HIP(hipFree(A->bws));
+      A->bws = nullptr;
+      A->bws_bytes = 0;
+    }
+    if (hipMalloc(&A->bws, bytes) != hipSuccess) {
+      A->bws = nullptr;
+      HK_FAIL(HK_ENOMEM, "hk_blockdiag_solve: hipMalloc(%zu)", bytes);
+    }
+    A->bws_bytes = bytes;
+  }
+  ar.base = (char*)A->bws;
   BdArgs a{};
   a.n = (int)n; a.nsys = nsys; a.rowptr = A->rowptr; a.col = A->col;
   a.val = (const double2*)A->val;
-  a.R = ar.take<double2>(n); a.RH = ar.take<double2>(n); a.PH = ar.take<double2>(n);
-  a.V = ar.take<double2>(n); a.SH = ar.take<double2>(n); a.T = ar.take<double2>(n);
+  double2* const vecs = ar.take<double2>(vstride * nvec);
+  a.R = vecs; a.RH = vecs + vstride; a.PH = vecs + 2 * vstride;
+  a.V = vecs + 3 * vstride; a.SH = vecs + 4 * vstride; a.T = vecs + 5 * vstride;
   double2* d = ar.take<double2>(n);
   double2* dinv = ar.take<double2>(n);
   a.act_sys = ar.take<int>(nt_max);
   a.act_row0 = ar.take<int>(nt_max);
   a.act_end = ar.take<int>(nt_max);
-  int* d_sor = ar.take<int>(n);
   int* d_send = ar.take<int>(kSys + 1);
   int* d_sbeg = ar.take<int>(kSys + 1);
   int* d_t0 = ar.take<int>(kSys + 1);
-  (void)ar.take<int>(kSys + 1);
   a.partials = ar.take<double>(4 * (size_t)gmax * kSys);
   a.st = ar.take<BatchState>(1);
   a.bar = ar.take<GridBar>(1);
   double* gpart = ar.take<double>(4 * (size_t)kXcds * kSys);
   int* flag = ar.take<int>(16);
-  if (ar.off > bytes) {
-    (void)hipFree(ar.base);
-    HK_FAIL(HK_EINVAL, "hk_blockdiag_solve: workspace layout exceeds its allocation");
+  // resident: the barrier words (two sets of sets per system, then the abort
+  // flag), the systems, their ends, the job lists
+  unsigned long long* words = nullptr;
+  ResBatchSystem* d_sys = nullptr;
+  ResBatchEnd* d_ends = nullptr;
+  int *d_jptr = nullptr, *d_jsys = nullptr, *d_jrank = nullptr;
+  if (resident) {
+    words = ar.take<unsigned long long>(2 * nsys * set_words + 32);
+    d_sys = ar.take<ResBatchSystem>(kSys);
+    d_ends = ar.take<ResBatchEnd>(kSys);
+    d_jptr = ar.take<int>(rp.job_ptr.size());
+    d_jsys = ar.take<int>(njobs);
+    d_jrank = ar.take<int>(njobs);
   }
+  if (ar.off > bytes) HK_FAIL(HK_EINVAL, "hk_blockdiag_solve: workspace layout exceeds its allocation");
   a.d = d; a.dinv = dinv; a.sys_begin = d_sbeg; a.sys_end = d_send; a.sys_tile0 = d_t0;
   a.B = (const double2*)d_b; a.X = (double2*)d_x;
   int hflag = 0;
-  hipError_t e = hipMemcpyAsync(d_sor, sys_of_row.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(d_send, sys_end.data(), 4 * kSys, hipMemcpyHostToDevice, s);
+  hipError_t e = hipMemcpyAsync(d_send, sys_end.data(), 4 * kSys, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(d_sbeg, sys_begin.data(), 4 * kSys, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemsetAsync(flag, 0, 64, s);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_bd_diag, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, (int)n,
-                       A->rowptr, A->col, (const double2*)A->val, d_sor, d_sbeg, d_send, d, dinv, flag);
+                       (int)nsys, A->rowptr, A->col, (const double2*)A->val, d_sbeg, d_send, d, dinv, flag);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host vectors above go out of scope
-  if (e != hipSuccess) {
-    (void)hipFree(ar.base);
-    HK_FAIL(HK_EHIP, "hk_blockdiag_solve: %s", hipGetErrorString(e));
-  }
+  if (e != hipSuccess) HK_FAIL(HK_EHIP, "hk_blockdiag_solve: %s", hipGetErrorString(e));
   if (hflag) {
-    (void)hipFree(ar.base);
     if (hflag & 2) HK_FAIL(HK_EINVAL, "hk_blockdiag_solve: matrix is not block-diagonal for the given offsets");
     HK_FAIL(HK_EINVAL, "hk_blockdiag_solve: zero diagonal entry (Jacobi undefined)");
   }
@@ -2303,7 +2331,6 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
         bool ab = false;
         if (e == hipSuccess) e = aborted(&ab);
         if (e != hipSuccess || ab) {
-          (void)hipFree(ar.base);
           if (ab) HK_FAIL(HK_EHIP, "hk_blockdiag_solve: grid barrier timed out");
           HK_FAIL(HK_EHIP, "hk_blockdiag_solve: trial launch: %s", hipGetErrorString(e));
         }
@@ -2315,13 +2342,64 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
       g_bd_plans.put(key, shape);
     }
   }
-  e = launch(shape, opts->tol, opts->max_iter, nullptr);
   BatchState hs{};
   GridBar hb{};
+  if (resident) {
+    ResBatchArgs ra{};
+    ra.base.n = (int)n;
+    ra.base.rowptr = A->rowptr;
+    ra.base.col = A->col;
+    ra.base.val = (const double2*)A->val;
+    ra.base.dinv = dinv;
+    ra.base.b = (const double2*)d_b;
+    ra.base.pub = vecs;
+    ra.base.stride = (long long)vstride;
+    ra.base.tol = opts->tol;
+    ra.base.maxit = opts->max_iter;
+    ra.base.gs.words = words;
+    ra.base.gs.abort = (int*)(words + 2 * nsys * set_words);
+    ra.base.gs.spin_limit = spin;
+    ra.words2 = words + nsys * set_words;
+    ra.sys = d_sys;
+    ra.job_ptr = d_jptr;
+    ra.job_sys = d_jsys;
+    ra.job_rank = d_jrank;
+    ra.X = (double2*)d_x;
+    ra.end = d_ends;
+    std::vector<ResBatchEnd> ends(kSys);
+    int ab = 0;
+    e = hipMemcpyAsync(d_sys, rp.sys.data(), sizeof(ResBatchSystem) * nsys, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(d_jptr, rp.job_ptr.data(), 4 * rp.job_ptr.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(d_jsys, rp.job_sys.data(), 4 * njobs, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(d_jrank, rp.job_rank.data(), 4 * njobs, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = resident_reset(words, 2 * nsys * set_words, ra.base.gs.abort, s);
+    const hipError_t le = e == hipSuccess ? resident_batch_launch(rp, ra, s) : e;
+    if (e == hipSuccess && le == hipSuccess) {
+      e = hipMemcpyAsync(ends.data(), d_ends, sizeof(ResBatchEnd) * nsys, hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess) e = hipMemcpyAsync(&ab, ra.base.gs.abort, sizeof(int), hipMemcpyDeviceToHost, s);
+    }
+    const hipError_t se = hipStreamSynchronize(s);  // the job lists live on this frame
+    if (e == hipSuccess) e = se;
+    if (e != hipSuccess) HK_FAIL(HK_EHIP, "hk_blockdiag_solve: %s", hipGetErrorString(e));
+    if (le == hipSuccess && !ab) {
+      for (int k = 0; k < nsys; ++k) {
+        hs.status[k] = ends[k].status;
+        hs.bd[k] = ends[k].bd;
+        hs.iters[k] = ends[k].iters;
+        hs.bb[k] = ends[k].bb;
+        hs.rr[k] = ends[k].rr;
+        hs.rr_true[k] = ends[k].rr_true;
+      }
+      fill_infos(hs, nsys, infos);
+      set_shape(infos, nsys, shape, tuned);
+      return worst_status(infos, nsys);
+    }
+    (void)hipGetLastError();  // not run, or timed out: the tiled launch starts over
+  }
+  e = launch(shape, opts->tol, opts->max_iter, nullptr);
   if (e == hipSuccess) e = hipMemcpyAsync(&hs, a.st, sizeof(hs), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipMemcpyAsync(&hb, a.bar, sizeof(hb), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)hipFree(ar.base);
   if (e != hipSuccess) HK_FAIL(HK_EHIP, "hk_blockdiag_solve: %s", hipGetErrorString(e));
   if (hb.abort) HK_FAIL(HK_EHIP, "hk_blockdiag_solve: grid barrier timed out");
   fill_infos(hs, nsys, infos);

@@ -82,6 +82,9 @@ struct hk_csr_s {
   hk::SpmvPlan dot_plan[2];
   // a launch shape was set by the caller: the solvers use it and nothing else
   bool plan_fixed = false;
+  // workspace of the batched solve (device), kept like the solver's
+  void* bws = nullptr;
+  size_t bws_bytes = 0;
   // pinned host words the solver reads its status through
   int* pinned = nullptr;
 };

@@ -30,22 +30,39 @@
 // Row r of workgroup b: consecutive rows, one per lane, so that the gathers of
 // entry k by a wave touch near-consecutive elements on a mesh in node order;
 // xcd_block gives each XCD one range of the rows, whose vectors its L2 holds.
+#include <cmath>
+#include <utility>
+
 #include "hk_resident.hpp"
 
 namespace hk {
 
+// How a solve ended.
+struct ResEnd {
+  int status, bd;
+  double rr, bb;
+  long long iter, iters_done;
+};
+
+// LDS of one BiCGStab solve.
+template <class R, int EL, int RPT, int NT> struct ResBiLds {
+  ResLds<NT> sums;
+  cplx<R> rh[RPT * NT], y[RPT * NT], lv[EL > 0 ? RPT * EL * NT : 1];
+};
+
+// BiCGStab on the rows [r0, rend) of this workgroup, number `rank` of the `size`
+// that solve the system: D x is left in lds.y.  Returns true if the kernel must
+// stop.
 template <class R, int E, int EL, int RPT, int NT>
-__global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
+__device__ __forceinline__ bool res_bicgstab(const ResArgs<R>& A, const GridSum& gs, int size, int rank,
+                                             const ResMap<RPT, NT>& m, ResBiLds<R, EL, RPT, NT>& lds, ResEnd& end) {
   using V = cplx<R>;
   // the rows' gathered r, kept from the v product for the t product where
   // the registers allow (15 fewer 16-byte gathers per row)
   constexpr bool kKeep = E * RPT * (int)sizeof(V) <= 256;
-  __shared__ ResLds<NT> lds;
-  __shared__ V s_rh[RPT * NT], s_y[RPT * NT], s_lv[EL > 0 ? RPT * EL * NT : 1];
-  if (*A.flag) return;
-  const ResMap<RPT, NT> m(A.n, A.rows);
+  V *const s_rh = lds.rh, *const s_y = lds.y;
   ResRows<V, E, EL, RPT, NT> M;
-  M.lv = s_lv;
+  M.lv = lds.lv;
   V r[RPT], q[RPT], p[RPT], v[RPT], t[RPT];
   // r, q and v of iteration `it` (r and q those it starts from).  All three are
   // read for the last time before the iteration's second barrier, so of the
@@ -57,14 +74,14 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
   for (int i = 0; i < RPT; ++i) {
     const int row = m.row(i), l = i * NT + threadIdx.x;
     const bool has = m.has(i);
-    M.load(i, row, has, A);
+    M.load(i, row, has, m.r0, m.shift, A);
     V bi = czero<V>(), ri = czero<V>(), yi = czero<V>();
     if (has) {
       bi = A.b[row];
       ri = A.x0 ? A.r0[row] : bi;
       if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
-      publish(pub(0, 1), row, ri);
-      publish(pub(1, 1), row, czero<V>());
+      publish(pub(0, 1), m.pub(i), ri);
+      publish(pub(1, 1), m.pub(i), czero<V>());
     }
     r[i] = ri;
     q[i] = p[i] = v[i] = t[i] = czero<V>();
@@ -73,8 +90,8 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
     sum2[0] += nrm2d(bi);
     sum2[1] += nrm2d(ri);
   }
-  if (grid_sum<2, NT>(A.gs, epoch, true, sum2, lds.sums)) return;
-  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  if (group_sum<2, NT>(gs, size, rank, epoch, true, sum2, lds.sums.sums)) return true;
+  const bool first = rank == 0 && threadIdx.x == 0;
   const double bb = uni(sum2[0]), theta2 = uni(A.tol * A.tol * bb);
   double rr = uni(sum2[1]);
   double2 rho = make_double2(rr, 0), beta = make_double2(0, 0), alpha, omega;
@@ -99,12 +116,12 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
               return cfma(be, x.v, x.u);
             });
         if (m.has(i)) {
-          publish(pv, m.row(i), v[i]);
+          publish(pv, m.pub(i), v[i]);
           dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
         }
       }
     }
-    if (grid_sum<2, NT>(A.gs, epoch, false, sg, lds.sums)) return;
+    if (group_sum<2, NT>(gs, size, rank, epoch, false, sg, lds.sums.sums)) return true;
     const double2 sigma = make_double2(sg[0], sg[1]);
     if (!cfinite(sigma)) {
       status = HK_NONFINITE;
@@ -138,7 +155,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
         ts[3] += nrm2d(s);
       }
     }
-    if (grid_sum<4, NT>(A.gs, epoch, false, ts, lds.sums)) return;
+    if (group_sum<4, NT>(gs, size, rank, epoch, false, ts, lds.sums.sums)) return true;
     const double ss = ts[3];
     const bool half = isfinite(ss) && ss <= theta2;
     if (!half && (!isfinite(ss) || !isfinite(ts[0]) || !isfinite(ts[1]) || !isfinite(ts[2]))) {
@@ -172,13 +189,13 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
       r[i] = cfnma(om, t[i], s);
       q[i] = cfnma(om, v[i], p[i]);
       if (m.has(i)) {
-        publish(pub(0, it + 1), m.row(i), r[i]);
-        publish(pub(1, it + 1), m.row(i), q[i]);
+        publish(pub(0, it + 1), m.pub(i), r[i]);
+        publish(pub(1, it + 1), m.pub(i), q[i]);
         xr[0] += nrm2d(r[i]);
         dotc_acc(s_rh[l], r[i], xr[1], xr[2]);
       }
     }
-    if (grid_sum<3, NT>(A.gs, epoch, ((it + 1) & (kRing - 1)) == 0, xr, lds.sums)) return;
+    if (group_sum<3, NT>(gs, size, rank, epoch, ((it + 1) & (kRing - 1)) == 0, xr, lds.sums.sums)) return true;
     rr = uni(xr[0]);
     done = it;
     const double2 rho1 = uni(make_double2(xr[1], xr[2]));
@@ -201,11 +218,80 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
       ++it;
     }
   }
+  end = ResEnd{status, bd, rr, bb, it, done};
+  return false;
+}
+
+template <class R, int E, int EL, int RPT, int NT>
+__global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
+  __shared__ ResBiLds<R, EL, RPT, NT> lds;
+  if (*A.flag) return;
+  const ResMap<RPT, NT> m(A.n, A.rows);
+  ResEnd e;
+  if (res_bicgstab<R, E, EL, RPT, NT>(A, A.gs, gridDim.x, blockIdx.x, m, lds, e)) return;
 #pragma unroll
   for (int i = 0; i < RPT; ++i)
-    if (m.has(i)) A.y[m.row(i)] = s_y[i * NT + threadIdx.x];
-  res_publish_state(A.st, status, bd, rr, bb, it, done);
+    if (m.has(i)) A.y[m.row(i)] = lds.y[i * NT + threadIdx.x];
+  res_publish_state(A.st, e.status, e.bd, e.rr, e.bb, e.iter, e.iters_done);
 }
+
+// Systems of a block-diagonal matrix, each solved by as many workgroups as its
+// rows need.  A workgroup works through the list of its systems (jobs), whose
+// order is one order over all systems: the first unfinished one finds all its
+// workgroups done with what comes before it, so every wait ends.  After a
+// solve its workgroups publish x and sum the true residual's norm.
+template <int E, int EL, int RPT, int NT>
+__global__ __launch_bounds__(NT) void k_res_batch(ResBatchArgs B) {
+  using V = double2;
+  __shared__ ResBiLds<double, EL, RPT, NT> lds;
+  const ResArgs<double>& A = B.base;
+  const int l = xcd_block(blockIdx.x, gridDim.x);
+  for (int j = B.job_ptr[l]; j < B.job_ptr[l + 1]; ++j) {
+    const int sys = __builtin_amdgcn_readfirstlane(B.job_sys[j]), rank = __builtin_amdgcn_readfirstlane(B.job_rank[j]);
+    const ResBatchSystem S = B.sys[sys];
+    GridSum gs = A.gs;
+    gs.words += (size_t)sys * kSumSets * kSumSetWords;
+    const ResMap<RPT, NT> m(S.row0 + rank * S.rows, S.row0 + rank * S.rows + S.rows, S.row1, S.shift);
+    ResEnd e;
+    __syncthreads();
+    if (res_bicgstab<double, E, EL, RPT, NT>(A, gs, S.size, rank, m, lds, e)) return;
+    // x = D^-1 y, and ||b - A x||^2
+    V* const px = A.pub;  // r's first place: all of its readers are done
+    double rt[1] = {0};
+    unsigned epoch = 0;
+    gs.words = B.words2 + (size_t)sys * kSumSets * kSumSetWords;
+    __syncthreads();
+    if (group_sum<1, NT>(gs, S.size, rank, epoch, true, rt, lds.sums.sums)) return;
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      if (!m.has(i)) continue;
+      const V x = cmul(A.dinv[m.row(i)], lds.y[i * NT + threadIdx.x]);
+      B.X[m.row(i)] = x;
+      publish(px, m.pub(i), x);
+    }
+    if (group_sum<1, NT>(gs, S.size, rank, epoch, true, rt, lds.sums.sums)) return;
+    rt[0] = 0;
+#pragma unroll 1
+    for (int i = 0; i < RPT; ++i) {
+      if (!m.has(i)) continue;
+      const int row = m.row(i), p1 = A.rowptr[row + 1];
+      V r = A.b[row];
+      for (int p = A.rowptr[row]; p < p1; ++p) r = cfnma(A.val[p], px[A.col[p] + S.shift], r);
+      rt[0] += nrm2d(r);
+    }
+    if (group_sum<1, NT>(gs, S.size, rank, epoch, false, rt, lds.sums.sums)) return;
+    if (rank == 0 && threadIdx.x == 0) {
+      ResBatchEnd& o = B.end[sys];
+      o.status = e.status;
+      o.bd = e.bd;
+      o.rr = e.rr;
+      o.bb = e.bb;
+      o.rr_true = rt[0];
+      o.iters = e.iters_done;
+    }
+  }
+}
+
 
 // TFQMR (complex128).  Statuses, counts and updates at each exit are those of
 // the kernels in hk_solver.hip.
@@ -230,13 +316,13 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
   for (int i = 0; i < RPT; ++i) {
     const int row = m.row(i), l = i * NT + threadIdx.x;
     const bool has = m.has(i);
-    M.load(i, row, has, A);
+    M.load(i, row, has, m.r0, m.shift, A);
     V bi = czero<V>(), ri = czero<V>(), yi = czero<V>();
     if (has) {
       bi = A.b[row];
       ri = A.x0 ? A.r0[row] : bi;
       if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
-      publish(pub(0, 1), row, ri);
+      publish(pub(0, 1), m.pub(i), ri);
     }
     y1[i] = w[i] = ri;
     v[i] = u1[i] = y2[i] = u2[i] = czero<V>();
@@ -290,7 +376,7 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
           i, [&](int, unsigned c) { return at(py1, c); }, [&](int, V x) { return x; });
       v[i] = u1[i];
       if (m.has(i)) {
-        publish(pub(1, 1), m.row(i), v[i]);
+        publish(pub(1, 1), m.pub(i), v[i]);
         dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
       }
     }
@@ -313,8 +399,8 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
           [&](int, const Pair<V>& x) { return cfnma(alpha, x.v, x.u); });
       w[i] = cfnma(alpha, u2[i], w[i]);
       if (m.has(i)) {
-        publish(pw, m.row(i), w[i]);
-        publish(py2, m.row(i), y2[i]);
+        publish(pw, m.pub(i), w[i]);
+        publish(py2, m.pub(i), y2[i]);
         hs[0] += w1;
         hs[1] += nrm2d(w[i]);
         dotc_acc(s_rh[i * NT + threadIdx.x], w[i], hs[2], hs[3]);
@@ -370,8 +456,8 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
           [&](int, const Pair<V>& x) { return cfma(beta, x.u, x.v); });
       v[i] = cfma(beta, cfma(beta, v[i], u2[i]), u1[i]);
       if (m.has(i)) {
-        publish(pub(0, k + 1), m.row(i), y1[i]);
-        publish(pub(1, k + 1), m.row(i), v[i]);
+        publish(pub(0, k + 1), m.pub(i), y1[i]);
+        publish(pub(1, k + 1), m.pub(i), v[i]);
         dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
       }
     }
@@ -387,12 +473,17 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
 
 // ------------------------------------------------------------------ host side
 
-// Scratch: the words of grid_sum, those of grid_sum_many, then 256 bytes that
-// start with the abort flag.  All words empty, abort flag 0:
+// Scratch: the words of grid_sum, those of grid_sum_many, the abort flag.
 constexpr size_t kResWords = kSumSets * kSumSetWords, kResMany = kManyWords;
-__global__ void k_res_reset(unsigned long long* words, int nwords, int* abort) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i < nwords) words[i] = words + i == reinterpret_cast<unsigned long long*>(abort) ? 0 : kSumEmpty;
+__global__ void k_res_reset(unsigned long long* words, size_t count, int* abort) {
+  const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i < count) words[i] = kSumEmpty;
+  if (i == 0) *abort = 0;
+}
+hipError_t resident_reset(unsigned long long* words, size_t count, int* abort, hipStream_t s) {
+  hipLaunchKernelGGL(k_res_reset, dim3((unsigned)((count + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, words, count,
+                     abort);
+  return hipGetLastError();
 }
 
 size_t resident_scratch_bytes() { return sizeof(unsigned long long) * (kResWords + kResMany) + 256; }
@@ -435,6 +526,97 @@ ResShape resident_shape(const hk_csr_s* A, int prec) {
   return sh;
 }
 
+// Time of one BiCGStab iteration in us, as measured: the barriers grow with the
+// workgroups (9.6 us at 20, 13.3 at 230), a second row per thread costs the
+// gathers again.
+static double res_iteration_us(int size, int rpt) { return 9.3 + 0.0175 * size + 6.5 * (rpt - 1); }
+
+// Each system is given to the run of workgroups that is free first, the large
+// ones first; with one or two rows per thread, whichever ends earlier (the
+// iterations of a mesh's system taken as proportional to its rows' cube root).
+bool resident_batch_plan(const hk_csr_s* A, int nsys, const int64_t* row_off, ResBatchPlan* plan) {
+  if (A->nnz <= 0 || A->max_row > kResEntries[2]) return false;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, A->device) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const int G = std::min(cus, kSumBlocks), cl = res_class(A->max_row);
+  std::vector<int> order(nsys);
+  for (int k = 0; k < nsys; ++k) order[k] = k;
+  auto rows_of = [&](int k) { return row_off[k + 1] - row_off[k]; };
+  std::stable_sort(order.begin(), order.end(), [&](int p, int q) { return rows_of(p) > rows_of(q); });
+  double best = -1;
+  for (int rpt = 1; rpt <= kResMax[0][cl]; ++rpt) {
+    if (rows_of(order[0]) > (int64_t)G * 512 * rpt) continue;
+    ResBatchPlan p;
+    p.entries = kResEntries[cl];
+    p.rpt = rpt;
+    p.grid = G;
+    p.sys.resize(nsys);
+    std::vector<double> free_at(G, 0.0);
+    std::vector<std::vector<std::pair<int, int>>> jobs(G);
+    double end = 0;
+    for (int k = 0; k < nsys; ++k) {
+      // 64 elements: whole cache lines
+      p.sys[k].shift = (int)(p.stride - row_off[k]);
+      p.stride += (rows_of(k) + 63) / 64 * 64;
+    }
+    for (int k : order) {
+      ResBatchSystem& s = p.sys[k];
+      s.row0 = (int)row_off[k];
+      s.row1 = (int)row_off[k + 1];
+      const int least = (int)((rows_of(k) + 512 * rpt - 1) / (512 * rpt));
+      s.rows = (int)(((rows_of(k) + least - 1) / least + 63) / 64 * 64);
+      s.size = (int)((rows_of(k) + s.rows - 1) / s.rows);
+      int at = 0;
+      double when = -1;
+      for (int l = 0; l + s.size <= G; ++l) {
+        double t = 0;
+        for (int q = l; q < l + s.size; ++q) t = std::max(t, free_at[q]);
+        if (when < 0 || t < when) { when = t; at = l; }
+      }
+      const double t = when + std::cbrt((double)rows_of(k)) * res_iteration_us(s.size, rpt);
+      for (int q = 0; q < s.size; ++q) {
+        free_at[at + q] = t;
+        jobs[at + q].push_back({k, q});
+      }
+      end = std::max(end, t);
+    }
+    p.job_ptr.push_back(0);
+    for (const auto& v : jobs) {
+      for (const auto& jb : v) {
+        p.job_sys.push_back(jb.first);
+        p.job_rank.push_back(jb.second);
+      }
+      p.job_ptr.push_back((int)p.job_sys.size());
+    }
+    if (best < 0 || end < best) {
+      best = end;
+      *plan = std::move(p);
+    }
+  }
+  return best >= 0;
+}
+
+hipError_t resident_batch_launch(const ResBatchPlan& plan, ResBatchArgs args, hipStream_t s) {
+  const void* kern = nullptr;
+#define HK_RES(EE, EL, PP) \
+  if (plan.entries == EE && plan.rpt == PP) kern = (const void*)k_res_batch<EE, EL, PP, 512>;
+  HK_RES(8, 0, 1) HK_RES(8, 2, 2) HK_RES(15, 0, 1) HK_RES(15, 6, 2) HK_RES(27, 13, 1)
+#undef HK_RES
+  if (!kern) return hipErrorInvalidConfiguration;
+  int per = 0, cus = 0, coop = 0, dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, 512, 0);
+  if (e != hipSuccess) return e;
+  if (!coop || plan.grid > per * cus) return hipErrorInvalidConfiguration;
+  void* kargs[] = {&args};
+  return hipLaunchCooperativeKernel(kern, dim3(plan.grid), dim3(512), kargs, 0, s);
+}
+
 template <class R> static const void* res_kernel(const ResShape& sh, int method) {
 #define HK_RES(EE, EL, PP, TT)                                                        \
   if (sh.entries == EE && sh.rpt == PP && sh.threads == TT) {                         \
@@ -468,10 +650,7 @@ hipError_t resident_launch_kernel(const void* kern, const ResShape& sh, void** k
   gs->words = static_cast<unsigned long long*>(scratch);
   gs->abort = resident_abort(scratch);
   gs->spin_limit = barrier_spin_limit();
-  const int nwords = (int)(resident_scratch_bytes() / sizeof(unsigned long long));
-  hipLaunchKernelGGL(k_res_reset, dim3((nwords + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
-                     static_cast<unsigned long long*>(scratch), nwords, gs->abort);
-  e = hipGetLastError();
+  e = resident_reset(gs->words, kResWords + kResMany, gs->abort, s);
   if (e != hipSuccess) return e;
   return hipLaunchCooperativeKernel(kern, dim3(sh.grid), dim3(sh.threads), kargs, 0, s);
 }

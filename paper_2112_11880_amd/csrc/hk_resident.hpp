@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <vector>
 
 #include "hk_grid.hpp"
 #include "hk_internal.hpp"
@@ -110,8 +111,9 @@ template <class V, int E, int EL, int RPT, int NT> struct ResRows {
   unsigned c[RPT][E];
   V* lv;
 
-  template <class Args> __device__ __forceinline__ void load(int i, int row, bool has, const Args& A) {
-    const int rc = has ? row : A.n - 1;
+  // (row: the i-th of this thread where `has`; published at row + shift)
+  template <class Args> __device__ __forceinline__ void load(int i, int row, bool has, int r0, int shift, const Args& A) {
+    const int rc = has ? row : r0;
     const int s = A.rowptr[rc], len = has ? A.rowptr[rc + 1] - s : 0;
 #pragma unroll
     for (int k = 0; k < E; ++k) {
@@ -122,7 +124,7 @@ template <class V, int E, int EL, int RPT, int NT> struct ResRows {
       if (k % 4 == 3) here(v);
       if (k < ER) a[i][k] = v;
       else lv[(i * EL + k - ER) * NT + threadIdx.x] = v;
-      c[i][k] = (unsigned)(k < len ? cc : rc) * (unsigned)sizeof(V);  // byte offset
+      c[i][k] = (unsigned)((k < len ? cc : rc) + shift) * (unsigned)sizeof(V);  // byte offset
     }
   }
   // Sum over the row's entries of a_k comb(k, ld(k, column)), the loads of
@@ -168,11 +170,14 @@ template <int NT> struct ResLds {
 // The row this thread works on as its i-th, and whether there is one.
 template <int RPT, int NT> struct ResMap {
   int r0, rend;
+  int shift = 0;  // row r is element r + shift of the published vectors
   __device__ __forceinline__ ResMap(int n, int rows) {
     r0 = xcd_block(blockIdx.x, gridDim.x) * rows;
     rend = min(r0 + rows, n);
   }
+  __device__ __forceinline__ ResMap(int from, int to, int end, int sh) : r0(from), rend(min(to, end)), shift(sh) {}
   __device__ __forceinline__ int row(int i) const { return r0 + i * NT + (int)threadIdx.x; }
+  __device__ __forceinline__ int pub(int i) const { return row(i) + shift; }
   __device__ __forceinline__ bool has(int i) const { return row(i) < rend; }
 };
 
@@ -210,10 +215,45 @@ struct ResLArgs {
   unsigned long long* many;  // words of grid_sum_many, all kSumEmpty at launch
 };
 hipError_t resident_l_launch(const ResShape& sh, ResLArgs args, void* scratch, hipStream_t s);
+// The systems of a block-diagonal matrix (complex128 BiCGStab): system s is rows
+// [row0, row1), `size` workgroups of `rows` rows, published at row + shift.  The
+// shifts keep systems, which publish at different times, off each other's
+// cache lines: a line that another system's workgroup on the same L2 has read
+// in between would hide the newer content.
+struct ResBatchSystem {
+  int row0, row1, size, rows, shift;
+};
+struct ResBatchEnd {
+  int status, bd;
+  double rr, bb, rr_true;
+  long long iters;
+};
+struct ResBatchArgs {
+  ResArgs<double> base;       // gs.words: kSumSets * kSumSetWords for each system, and so are words2
+  unsigned long long* words2;
+  const ResBatchSystem* sys;
+  // workgroup l (in XCD order) has jobs job_ptr[l] .. job_ptr[l + 1]: system and rank in it
+  const int *job_ptr, *job_sys, *job_rank;
+  double2* X;
+  ResBatchEnd* end;
+};
+// Rows per thread (1 or 2), rows per workgroup and the job lists for systems of
+// the given rows; false if one does not fit.
+struct ResBatchPlan {
+  int entries = 0, rpt = 0, grid = 0;
+  int64_t stride = 0;  // elements of a published vector
+  std::vector<ResBatchSystem> sys;
+  std::vector<int> job_ptr, job_sys, job_rank;
+};
+bool resident_batch_plan(const hk_csr_s* A, int nsys, const int64_t* row_off, ResBatchPlan* plan);
+hipError_t resident_batch_launch(const ResBatchPlan& plan, ResBatchArgs args, hipStream_t s);
+
 // The barrier words at the front of the scratch emptied, the launch itself:
 // kern with sh's grid and the argument struct at kargs[0], whose GridSum is gs.
 hipError_t resident_launch_kernel(const void* kern, const ResShape& sh, void** kargs, GridSum* gs, void* scratch,
                                   hipStream_t s);
+// All of `count` barrier words empty, *abort (which may lie behind them) 0.
+hipError_t resident_reset(unsigned long long* words, size_t count, int* abort, hipStream_t s);
 // The abort flag in the scratch (device address), and the words behind it.
 int* resident_abort(void* scratch);
 unsigned long long* resident_many(void* scratch);

@@ -100,14 +100,14 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
   for (int i = 0; i < RPT; ++i) {
     const int row = m.row(i), l = i * NT + threadIdx.x;
     const bool has = m.has(i);
-    M.load(i, row, has, A);
+    M.load(i, row, has, m.r0, m.shift, A);
     V bi = czero<V>(), ri = czero<V>(), yi = czero<V>();
     if (has) {
       bi = A.b[row];
       ri = A.x0 ? A.r0[row] : bi;
       if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
-      publish(pub(0, 0), row, ri);
-      publish(pub(1, 0), row, czero<V>());
+      publish(pub(0, 0), m.pub(i), ri);
+      publish(pub(1, 0), m.pub(i), czero<V>());
     }
     r0[i] = ri;
     u0[i] = u1[i] = un[i] = rn[i] = czero<V>();
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
             i, [&](int, unsigned c) { return Pair<V>{at(pr, c), at(pu, c)}; },
             [&](int, const Pair<V>& x) { return cfnma(beta, x.v, x.u); });
         if (m.has(i)) {
-          publish(pu2, m.row(i), un[i]);
+          publish(pu2, m.pub(i), un[i]);
           dotc_acc(s_rt[i * NT + threadIdx.x], un[i], sg[0], sg[1]);
         }
       }
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
             i, [&](int, unsigned c) { return Pair<V>{at(pr, c), at(static_cast<const V*>(pu2), c)}; },
             [&](int, const Pair<V>& x) { return cfnma(alpha, x.v, x.u); });
         if (m.has(i)) {
-          if (j + 1 < ell) publish(pr2, m.row(i), rn[i]);
+          if (j + 1 < ell) publish(pr2, m.pub(i), rn[i]);
           rs[0] += nrm2d(r0[i]);
           dotc_acc(s_rt[l], rn[i], rs[1], rs[2]);
         }
@@ -348,8 +348,8 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
       r0[i] = r;
       u0[i] = u;
       if (m.has(i)) {
-        publish(pub(0, np + 2), m.row(i), r);
-        publish(pub(1, np + 2), m.row(i), u);
+        publish(pub(0, np + 2), m.pub(i), r);
+        publish(pub(1, np + 2), m.pub(i), u);
         mr[0] += nrm2d(r);
         dotc_acc(s_rt[l], r, mr[1], mr[2]);
       }

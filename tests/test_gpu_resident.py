@@ -166,3 +166,48 @@ def test_resident_options_and_fallback(hk, oracle, monkeypatch, method):
     z, late = hk.krylov_solve(C, dev(b), x=dev(x0), tol=1e-12, method=method)
     assert late["status"] == hk.HK_OK and late["shape"][0] == 64, late
     assert (z - x).abs().max() <= 1e-10 * x.abs().max()
+
+
+def block_diagonal(sizes, row, seed):
+    parts = [dominant(n, min(row, n), seed + k) for k, n in enumerate(sizes)]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    nnz = np.cumsum([0] + [p[1].shape[0] for p in parts])
+    rowptr = np.concatenate([[0]] + [p[0][1:] + z for p, z in zip(parts, nnz)]).astype(np.int32)
+    col = np.concatenate([p[1] + o for p, o in zip(parts, off)]).astype(np.int32)
+    return parts, off, rowptr, col, np.concatenate([p[2] for p in parts]), np.concatenate([p[3] for p in parts])
+
+
+@pytest.mark.parametrize("sizes,row", [
+    ([1], 1), ([1, 2, 63, 64, 65, 130], 8), ([700, 5, 20000, 513, 1], 15), ([40000, 70000, 3000] + [65] * 61, 15),
+    ([131073, 900, 131072, 17], 15), ([500, 9000, 27], 27), ([300, 40], 28),
+])
+def test_resident_batch(hk, oracle, sizes, row):
+    """Systems of 1 row to more than one workgroup takes, several lists deep; a zero
+    right-hand side and a NaN each end their system only."""
+    print("[case] batch", sizes[:6], row, flush=True)
+    parts, off, rowptr, col, val, b = block_diagonal(sizes, row, 17)
+    b = b.copy()
+    zero = nan = -1
+    if len(sizes) > 3:
+        zero, nan = 1, 3
+        b[off[zero]:off[zero + 1]] = 0
+        b[off[nan]] = np.nan
+    A = hk.CSR(dev(rowptr), dev(col), dev(val))
+    for tol, k in ((0.0, 2), (1e-12, 400)):
+        x, infos = hk.blockdiag_solve(A, off, dev(b), tol=tol, max_iter=k)
+        x = x.cpu().numpy()
+        for s, (rp, c, v, _) in enumerate(parts):
+            bs, xs, info = b[off[s]:off[s + 1]], x[off[s]:off[s + 1]], infos[s]
+            if s == zero:
+                assert info["status"] == hk.HK_OK and info["iters"] == 0 and np.all(xs == 0), info
+            elif s == nan:
+                assert info["status"] == hk.HK_NONFINITE, info
+            elif tol:
+                assert info["status"] == hk.HK_OK and info["relres_true"] <= 1.05e-12, (s, info)
+                r = oracle.residual(rp, c, v, bs, xs)
+                assert np.linalg.norm(r) <= 1.05e-12 * np.linalg.norm(bs)
+            elif sizes[s] > 4:
+                xo, oi = oracle.bicgstab(rp, c, v, bs, tol=0.0, maxit=k)
+                assert info["status"] == oi["status"] == hk.HK_NOT_CONVERGED and info["iters"] == k, (s, info, oi)
+                assert np.linalg.norm(xs - xo) <= 1e-11 * np.linalg.norm(xo), s
+                assert abs(info["relres_true"] - oi["relres_true"]) <= 1e-11, (s, info, oi)
