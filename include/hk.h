@@ -325,6 +325,11 @@ int hk_krylov_solve_mixed(hk_csr A, const void* d_b, void* d_x, double inner_tol
  * launches write only the call's workspace and X.  A nonzero opts->shape
  * must be a candidate (HK_EINVAL otherwise) and is used as is.  Every
  * infos[j].shape holds the shape used, shape_tuned whether it was timed.
+ * Where a system of more than 512 rows fits the registers of the device (the
+ * limits of hk_krylov_solve), no shape is given and no barrier times are asked
+ * for, groups of workgroups that keep the rows in registers solve one system
+ * after the other instead, still in one cooperative launch; the interleaved
+ * launch in the shape reported takes over if that one times out.
  */
 int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_col,
                    const double* d_K, const double* d_M, int32_t nsys, const double* kappa,

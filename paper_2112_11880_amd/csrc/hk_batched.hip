@@ -1810,6 +1810,23 @@ struct Arena {
   }
 };
 
+// An arena with memory of its own, given back at the end of the call.
+struct DevArena : Arena {
+  size_t bytes = 0;
+  ~DevArena() {
+    if (base) (void)hipFree(base);
+  }
+  int alloc(size_t n, const char* who) {
+    if (hipMalloc((void**)&base, n) != hipSuccess) {
+      base = nullptr;
+      (void)hipGetLastError();
+      HK_FAIL(HK_ENOMEM, "%s: hipMalloc(%zu)", who, n);
+    }
+    bytes = n;
+    return HK_OK;
+  }
+};
+
 // Workgroups per CU of the persistent kernels (one and two measured the same).
 constexpr int kCoopPerCu = 2;
 static int coop_grid(const void* kernel, int* grid) {
@@ -1951,6 +1968,18 @@ static const void* bd_kernel(const std::array<int, 4>& sh) {
   return nullptr;
 }
 
+// how the systems of a resident launch ended
+static void batch_ends(const std::vector<ResBatchEnd>& ends, int nsys, BatchState* hs) {
+  for (int k = 0; k < nsys; ++k) {
+    hs->status[k] = ends[k].status;
+    hs->bd[k] = ends[k].bd;
+    hs->iters[k] = ends[k].iters;
+    hs->bb[k] = ends[k].bb;
+    hs->rr[k] = ends[k].rr;
+    hs->rr_true[k] = ends[k].rr_true;
+  }
+}
+
 static bool shape_given(const hk_solve_opts* o) {
   return o->shape[0] || o->shape[1] || o->shape[2] || o->shape[3];
 }
@@ -1982,40 +2011,28 @@ extern "C" int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, c
   (void)hk_csr_destroy(A);
   int dev = 0;
   HK_HIP(hipGetDevice(&dev));
-  // the largest grid of any candidate sizes the partials
-  int gmax = 0;
-  for (const auto& sh : kSweepShapes) {
-    for (const void* k : {sweep_kernel(sh), sweep_tail_kernel(sh, 2), sweep_tail_kernel(sh, 4)}) {
-      if (!k) continue;
-      int g = 0;
-      rc = coop_grid(k, &g);
-      if (rc != HK_OK) return rc;
-      gmax = std::max(gmax, g);
-    }
-  }
-  const size_t vec = (size_t)n * kSys;
-  Arena ar;
-  const size_t bytes = 6 * a256(16 * vec) + 2 * a256(8 * n) + a256(16 * kSys) +
-                       a256(8 * 4 * (size_t)gmax * kSys) + a256(sizeof(BatchState)) + a256(sizeof(GridBar)) +
-                       a256(8 * 4 * (size_t)kXcds * kSys) + a256(64);
-  if (hipMalloc((void**)&ar.base, bytes) != hipSuccess) HK_FAIL(HK_ENOMEM, "hk_sweep_solve: hipMalloc(%zu)", bytes);
+  const PlanKey key{dev, n, nnz, max_row, nsys};
+  std::array<int, 4> shape = forced;
+  const int tuned = shape_given(opts) ? 0 : 1;
+  bool have_shape = !tuned || g_sweep_plans.get(key, &shape);
+  // the resident solve of the systems (hk_resident.hip), where they fit; the
+  // barrier stamps are those of the interleaved launch, and a shape given is its
+  ResSweepPlan rp;
+  const bool resident = tuned && !opts->d_history && resident_sweep_plan(dev, n, nnz, max_row, nsys, &rp);
+  DevArena ar;
+  const int64_t area = (n + 63) / 64 * 64;  // whole cache lines
+  const size_t set_words = kSumSets * kSumSetWords, nwords = resident ? rp.groups * set_words + 32 : 0;
+  rc = ar.alloc(2 * a256(8 * (size_t)n) + a256(16 * kSys) + a256(64) +
+                (resident ? a256(16 * 3 * kRing * (size_t)area * rp.groups) + a256(8 * nwords) +
+                                a256(sizeof(ResBatchEnd) * kSys) + a256(4 * (kSys + 1)) : 0),
+                "hk_sweep_solve");
+  if (rc != HK_OK) return rc;
   SweepArgs a{};
   a.n = (int)n; a.nsys = nsys; a.rowptr = d_rowptr; a.col = d_col; a.K = d_K; a.M = d_M;
-  a.R = ar.take<double2>(vec); a.RH = ar.take<double2>(vec); a.PH = ar.take<double2>(vec);
-  a.V = ar.take<double2>(vec); a.SH = ar.take<double2>(vec); a.T = ar.take<double2>(vec);
   double* kd = ar.take<double>(n);
   double* md = ar.take<double>(n);
   double2* kap = ar.take<double2>(kSys);
-  a.partials = ar.take<double>(4 * (size_t)gmax * kSys);
-  a.st = ar.take<BatchState>(1);
-  a.bar = ar.take<GridBar>(1);
-  // per-XCD-group sums of the reducing barriers
-  double* gpart = ar.take<double>(4 * (size_t)kXcds * kSys);
   int* flag = ar.take<int>(16);
-  if (ar.off > bytes) {
-    (void)hipFree(ar.base);
-    HK_FAIL(HK_EINVAL, "hk_sweep_solve: workspace layout exceeds its allocation");
-  }
   a.kd = kd; a.md = md; a.kap = kap;
   a.B = (const double2*)d_B; a.X = (double2*)d_X;
   std::vector<double2> hk(kSys, make_double2(0, 0));
@@ -2034,13 +2051,41 @@ extern "C" int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, c
   }
   if (e == hipSuccess) e = hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) {
-    (void)hipFree(ar.base);
-    HK_FAIL(HK_EHIP, "hk_sweep_solve: %s", hipGetErrorString(e));
-  }
-  if (hflag) {
-    (void)hipFree(ar.base);
-    HK_FAIL(HK_EINVAL, "hk_sweep_solve: zero diagonal entry for some system (Jacobi undefined)");
+  if (e != hipSuccess) HK_FAIL(HK_EHIP, "hk_sweep_solve: %s", hipGetErrorString(e));
+  if (hflag) HK_FAIL(HK_EINVAL, "hk_sweep_solve: zero diagonal entry for some system (Jacobi undefined)");
+  // the interleaved launch's part of the workspace
+  DevArena big;
+  double* gpart = nullptr;  // per-XCD-group sums of the reducing barriers
+  auto need_big = [&]() -> int {
+    if (big.base) return HK_OK;
+    // the largest grid of any candidate sizes the partials
+    int gmax = 0;
+    for (const auto& sh : kSweepShapes) {
+      for (const void* k : {sweep_kernel(sh), sweep_tail_kernel(sh, 2), sweep_tail_kernel(sh, 4)}) {
+        if (!k) continue;
+        int g = 0;
+        const int rc2 = coop_grid(k, &g);
+        if (rc2 != HK_OK) return rc2;
+        gmax = std::max(gmax, g);
+      }
+    }
+    const size_t vec = (size_t)n * kSys;
+    const int rc2 = big.alloc(6 * a256(16 * vec) + a256(8 * 4 * (size_t)gmax * kSys) + a256(sizeof(BatchState)) +
+                                  a256(sizeof(GridBar)) + a256(8 * 4 * (size_t)kXcds * kSys),
+                              "hk_sweep_solve");
+    if (rc2 != HK_OK) return rc2;
+    a.R = big.take<double2>(vec); a.RH = big.take<double2>(vec); a.PH = big.take<double2>(vec);
+    a.V = big.take<double2>(vec); a.SH = big.take<double2>(vec); a.T = big.take<double2>(vec);
+    a.partials = big.take<double>(4 * (size_t)gmax * kSys);
+    a.st = big.take<BatchState>(1);
+    a.bar = big.take<GridBar>(1);
+    gpart = big.take<double>(4 * (size_t)kXcds * kSys);
+    if (big.off > big.bytes) HK_FAIL(HK_EINVAL, "hk_sweep_solve: workspace layout exceeds its allocation");
+    return HK_OK;
+  };
+  if (!resident || !have_shape) {
+    rc = need_big();
+    if (rc != HK_OK) return rc;
   }
   const unsigned long long spin = barrier_spin_limit();
   // one persistent launch of shape sh: fresh state and barrier, then the kernel
@@ -2097,45 +2142,92 @@ extern "C" int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, c
     *ab = hb.abort != 0;
     return e2;
   };
-  std::array<int, 4> shape = forced;
-  int tuned = 0;
-  const PlanKey key{dev, n, nnz, max_row, nsys};
-  if (!shape_given(opts)) {
-    tuned = 1;
-    if (!g_sweep_plans.get(key, &shape)) {
-      float best = -1;
-      EventPair ev;
-      e = ev.create();
-      for (const auto& sh : kSweepShapes) {
-        float ms = -1;
-        for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {
-          float t = 0;
-          e = launch(sh, 0.0, kTuneIters, &ev);
-          if (e == hipSuccess) e = hipEventElapsedTime(&t, ev.e0, ev.e1);
-          ms = rep == 0 ? t : std::min(ms, t);
-        }
-        bool ab = false;
-        if (e == hipSuccess) e = aborted(&ab);
-        if (e != hipSuccess || ab) {
-          (void)hipFree(ar.base);
-          if (ab) HK_FAIL(HK_EHIP, "hk_sweep_solve: grid barrier timed out");
-          HK_FAIL(HK_EHIP, "hk_sweep_solve: trial launch: %s", hipGetErrorString(e));
-        }
-        if (best < 0 || ms < best) {
-          best = ms;
-          shape = sh;
-        }
+  if (!have_shape) {
+    float best = -1;
+    EventPair ev;
+    e = ev.create();
+    for (const auto& sh : kSweepShapes) {
+      float ms = -1;
+      for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {
+        float t = 0;
+        e = launch(sh, 0.0, kTuneIters, &ev);
+        if (e == hipSuccess) e = hipEventElapsedTime(&t, ev.e0, ev.e1);
+        ms = rep == 0 ? t : std::min(ms, t);
       }
-      g_sweep_plans.put(key, shape);
+      bool ab = false;
+      if (e == hipSuccess) e = aborted(&ab);
+      if (ab) HK_FAIL(HK_EHIP, "hk_sweep_solve: grid barrier timed out");
+      if (e != hipSuccess) HK_FAIL(HK_EHIP, "hk_sweep_solve: trial launch: %s", hipGetErrorString(e));
+      if (best < 0 || ms < best) {
+        best = ms;
+        shape = sh;
+      }
     }
+    g_sweep_plans.put(key, shape);
+  }
+  BatchState hs{};
+  if (resident) {
+    ResSweepArgs ra{};
+    double2* const pub = ar.take<double2>(3 * kRing * (size_t)area * rp.groups);
+    unsigned long long* const words = ar.take<unsigned long long>(nwords);
+    ra.end = ar.take<ResBatchEnd>(kSys);
+    int* const order = ar.take<int>(kSys + 1);
+    if (ar.off > ar.bytes) HK_FAIL(HK_EINVAL, "hk_sweep_solve: workspace layout exceeds its allocation");
+    ra.src.n = (int)n;
+    ra.src.rowptr = d_rowptr;
+    ra.src.col = d_col;
+    ra.src.K = d_K;
+    ra.src.M = d_M;
+    ra.src.kd = kd;
+    ra.src.md = md;
+    ra.src.b = (const double2*)d_B;
+    ra.src.pub = pub;
+    ra.src.stride = (long long)area * rp.groups;
+    ra.src.tol = opts->tol;
+    ra.src.maxit = opts->max_iter;
+    ra.src.gs.words = words;
+    ra.src.gs.abort = (int*)(words + rp.groups * set_words);
+    ra.src.gs.spin_limit = spin;
+    ra.kap = kap;
+    ra.order = order;
+    ra.next = order + kSys;
+    ra.nsys = nsys;
+    ra.area = area;
+    ra.X = (double2*)d_X;
+    // the systems of larger shifts, which take more iterations as a rule, first
+    std::array<int, kSys + 1> ho{};
+    for (int j = 0; j < nsys; ++j) ho[j] = j;
+    std::stable_sort(ho.begin(), ho.begin() + nsys, [&](int p, int q) {
+      return std::hypot(hk[p].x, hk[p].y) > std::hypot(hk[q].x, hk[q].y);
+    });
+    ho[kSys] = rp.groups;
+    std::vector<ResBatchEnd> ends(kSys);
+    int ab = 0;
+    e = hipMemcpyAsync(order, ho.data(), sizeof(ho), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = resident_reset(words, rp.groups * set_words, ra.src.gs.abort, s);
+    const hipError_t le = e == hipSuccess ? resident_sweep_launch(rp, ra, s) : e;
+    if (e == hipSuccess && le == hipSuccess) {
+      e = hipMemcpyAsync(ends.data(), ra.end, sizeof(ResBatchEnd) * nsys, hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess) e = hipMemcpyAsync(&ab, ra.src.gs.abort, sizeof(int), hipMemcpyDeviceToHost, s);
+    }
+    const hipError_t se = hipStreamSynchronize(s);  // the order lives on this frame
+    if (e == hipSuccess) e = se;
+    if (e != hipSuccess) HK_FAIL(HK_EHIP, "hk_sweep_solve: %s", hipGetErrorString(e));
+    if (le == hipSuccess && !ab) {
+      batch_ends(ends, nsys, &hs);
+      fill_infos(hs, nsys, infos);
+      set_shape(infos, nsys, shape, tuned);
+      return worst_status(infos, nsys);
+    }
+    (void)hipGetLastError();  // not run, or timed out: the interleaved launch starts over
+    rc = need_big();
+    if (rc != HK_OK) return rc;
   }
   e = launch(shape, opts->tol, opts->max_iter, nullptr);
-  BatchState hs{};
   GridBar hb{};
   if (e == hipSuccess) e = hipMemcpyAsync(&hs, a.st, sizeof(hs), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipMemcpyAsync(&hb, a.bar, sizeof(hb), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)hipFree(ar.base);
   if (e != hipSuccess) HK_FAIL(HK_EHIP, "hk_sweep_solve: %s", hipGetErrorString(e));
   if (hb.abort) HK_FAIL(HK_EHIP, "hk_sweep_solve: grid barrier timed out");
   fill_infos(hs, nsys, infos);
@@ -2190,7 +2282,7 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
   const size_t bytes = 16 * vstride * nvec + 2 * a256(16 * (size_t)n) + 3 * a256(4 * (size_t)nt_max) +
                        3 * a256(4 * (kSys + 1)) + a256(8 * 4 * (size_t)gmax * kSys) +
                        a256(sizeof(BatchState)) + a256(sizeof(GridBar)) + a256(8 * 4 * (size_t)kXcds * kSys) +
-                       a256(64) + (resident ? a256(8 * (2 * nsys * set_words + 32)) +
+                       a256(64) + (resident ? a256(8 * (nsys * set_words + 32)) +
                        a256(sizeof(ResBatchSystem) * kSys) + a256(sizeof(ResBatchEnd) * kSys) +
                        a256(4 * rp.job_ptr.size()) + 2 * a256(4 * njobs) : 0);
   if (A->bws_bytes < bytes) {
@@ -2233,7 +2325,7 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
   ResBatchEnd* d_ends = nullptr;
   int *d_jptr = nullptr, *d_jsys = nullptr, *d_jrank = nullptr;
   if (resident) {
-    words = ar.take<unsigned long long>(2 * nsys * set_words + 32);
+    words = ar.take<unsigned long long>(nsys * set_words + 32);
     d_sys = ar.take<ResBatchSystem>(kSys);
     d_ends = ar.take<ResBatchEnd>(kSys);
     d_jptr = ar.take<int>(rp.job_ptr.size());
@@ -2357,9 +2449,8 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
     ra.base.tol = opts->tol;
     ra.base.maxit = opts->max_iter;
     ra.base.gs.words = words;
-    ra.base.gs.abort = (int*)(words + 2 * nsys * set_words);
+    ra.base.gs.abort = (int*)(words + nsys * set_words);
     ra.base.gs.spin_limit = spin;
-    ra.words2 = words + nsys * set_words;
     ra.sys = d_sys;
     ra.job_ptr = d_jptr;
     ra.job_sys = d_jsys;
@@ -2372,7 +2463,7 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
     if (e == hipSuccess) e = hipMemcpyAsync(d_jptr, rp.job_ptr.data(), 4 * rp.job_ptr.size(), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(d_jsys, rp.job_sys.data(), 4 * njobs, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(d_jrank, rp.job_rank.data(), 4 * njobs, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = resident_reset(words, 2 * nsys * set_words, ra.base.gs.abort, s);
+    if (e == hipSuccess) e = resident_reset(words, nsys * set_words, ra.base.gs.abort, s);
     const hipError_t le = e == hipSuccess ? resident_batch_launch(rp, ra, s) : e;
     if (e == hipSuccess && le == hipSuccess) {
       e = hipMemcpyAsync(ends.data(), d_ends, sizeof(ResBatchEnd) * nsys, hipMemcpyDeviceToHost, s);
@@ -2382,14 +2473,7 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
     if (e == hipSuccess) e = se;
     if (e != hipSuccess) HK_FAIL(HK_EHIP, "hk_blockdiag_solve: %s", hipGetErrorString(e));
     if (le == hipSuccess && !ab) {
-      for (int k = 0; k < nsys; ++k) {
-        hs.status[k] = ends[k].status;
-        hs.bd[k] = ends[k].bd;
-        hs.iters[k] = ends[k].iters;
-        hs.bb[k] = ends[k].bb;
-        hs.rr[k] = ends[k].rr;
-        hs.rr_true[k] = ends[k].rr_true;
-      }
+      batch_ends(ends, nsys, &hs);
       fill_infos(hs, nsys, infos);
       set_shape(infos, nsys, shape, tuned);
       return worst_status(infos, nsys);

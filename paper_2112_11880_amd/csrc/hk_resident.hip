@@ -53,8 +53,8 @@ template <class R, int EL, int RPT, int NT> struct ResBiLds {
 // BiCGStab on the rows [r0, rend) of this workgroup, number `rank` of the `size`
 // that solve the system: D x is left in lds.y.  Returns true if the kernel must
 // stop.
-template <class R, int E, int EL, int RPT, int NT>
-__device__ __forceinline__ bool res_bicgstab(const ResArgs<R>& A, const GridSum& gs, int size, int rank,
+template <class R, int E, int EL, int RPT, int NT, class Src>
+__device__ __forceinline__ bool res_bicgstab(const Src& A, const GridSum& gs, int size, int rank, unsigned& epoch,
                                              const ResMap<RPT, NT>& m, ResBiLds<R, EL, RPT, NT>& lds, ResEnd& end) {
   using V = cplx<R>;
   // the rows' gathered r, kept from the v product for the t product where
@@ -68,7 +68,6 @@ __device__ __forceinline__ bool res_bicgstab(const ResArgs<R>& A, const GridSum&
   // read for the last time before the iteration's second barrier, so of the
   // third barriers of any kRing iterations in a row one drops the caches.
   auto pub = [&](int i, long long at_it) { return A.pub + (kRing * i + (int)(at_it & (kRing - 1))) * A.stride; };
-  unsigned epoch = 0;
   double sum2[2] = {0, 0};
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
@@ -77,9 +76,9 @@ __device__ __forceinline__ bool res_bicgstab(const ResArgs<R>& A, const GridSum&
     M.load(i, row, has, m.r0, m.shift, A);
     V bi = czero<V>(), ri = czero<V>(), yi = czero<V>();
     if (has) {
-      bi = A.b[row];
+      bi = A.rhs(row);
       ri = A.x0 ? A.r0[row] : bi;
-      if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
+      if (A.x0) yi = cdiv(A.x0[row], A.inv_diag(row));
       publish(pub(0, 1), m.pub(i), ri);
       publish(pub(1, 1), m.pub(i), czero<V>());
     }
@@ -228,21 +227,54 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
   if (*A.flag) return;
   const ResMap<RPT, NT> m(A.n, A.rows);
   ResEnd e;
-  if (res_bicgstab<R, E, EL, RPT, NT>(A, A.gs, gridDim.x, blockIdx.x, m, lds, e)) return;
+  unsigned epoch = 0;
+  if (res_bicgstab<R, E, EL, RPT, NT>(A, A.gs, gridDim.x, blockIdx.x, epoch, m, lds, e)) return;
 #pragma unroll
   for (int i = 0; i < RPT; ++i)
     if (m.has(i)) A.y[m.row(i)] = lds.y[i * NT + threadIdx.x];
   res_publish_state(A.st, e.status, e.bd, e.rr, e.bb, e.iter, e.iters_done);
 }
 
+// What follows the solve of one of several systems: x = D^-1 y, published and
+// stored by put(row, x), and the true residual ||b - A x||, whose place is end.
+// Returns true if the kernel must stop.
+template <int RPT, int NT, class Src, class Lds, class Put>
+__device__ __forceinline__ bool res_finish(const Src& A, const GridSum& gs, int size, int rank, unsigned& epoch,
+                                           const ResMap<RPT, NT>& m, Lds& lds, const ResEnd& e, ResBatchEnd* end,
+                                           Put&& put) {
+  using V = double2;
+  V* const px = A.pub;  // r's first place: all of its readers are done
+  double rt[1] = {0};
+  __syncthreads();
+  if (group_sum<1, NT>(gs, size, rank, epoch, true, rt, lds.sums.sums)) return true;
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    if (!m.has(i)) continue;
+    const V x = cmul(A.inv_diag(m.row(i)), lds.y[i * NT + threadIdx.x]);
+    put(m.row(i), x);
+    publish(px, m.pub(i), x);
+  }
+  if (group_sum<1, NT>(gs, size, rank, epoch, true, rt, lds.sums.sums)) return true;
+  rt[0] = 0;
+#pragma unroll 1
+  for (int i = 0; i < RPT; ++i) {
+    if (!m.has(i)) continue;
+    const int row = m.row(i), p1 = A.rowptr[row + 1];
+    V r = A.rhs(row);
+    for (int p = A.rowptr[row]; p < p1; ++p) r = cfnma(A.entry(p), px[A.col[p] + m.shift], r);
+    rt[0] += nrm2d(r);
+  }
+  if (group_sum<1, NT>(gs, size, rank, epoch, false, rt, lds.sums.sums)) return true;
+  if (rank == 0 && threadIdx.x == 0) *end = ResBatchEnd{e.status, e.bd, e.rr, e.bb, rt[0], e.iters_done};
+  return false;
+}
+
 // Systems of a block-diagonal matrix, each solved by as many workgroups as its
 // rows need.  A workgroup works through the list of its systems (jobs), whose
 // order is one order over all systems: the first unfinished one finds all its
-// workgroups done with what comes before it, so every wait ends.  After a
-// solve its workgroups publish x and sum the true residual's norm.
+// workgroups done with what comes before it, so every wait ends.
 template <int E, int EL, int RPT, int NT>
 __global__ __launch_bounds__(NT) void k_res_batch(ResBatchArgs B) {
-  using V = double2;
   __shared__ ResBiLds<double, EL, RPT, NT> lds;
   const ResArgs<double>& A = B.base;
   const int l = xcd_block(blockIdx.x, gridDim.x);
@@ -253,42 +285,51 @@ __global__ __launch_bounds__(NT) void k_res_batch(ResBatchArgs B) {
     gs.words += (size_t)sys * kSumSets * kSumSetWords;
     const ResMap<RPT, NT> m(S.row0 + rank * S.rows, S.row0 + rank * S.rows + S.rows, S.row1, S.shift);
     ResEnd e;
-    __syncthreads();
-    if (res_bicgstab<double, E, EL, RPT, NT>(A, gs, S.size, rank, m, lds, e)) return;
-    // x = D^-1 y, and ||b - A x||^2
-    V* const px = A.pub;  // r's first place: all of its readers are done
-    double rt[1] = {0};
     unsigned epoch = 0;
-    gs.words = B.words2 + (size_t)sys * kSumSets * kSumSetWords;
     __syncthreads();
-    if (group_sum<1, NT>(gs, S.size, rank, epoch, true, rt, lds.sums.sums)) return;
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-      if (!m.has(i)) continue;
-      const V x = cmul(A.dinv[m.row(i)], lds.y[i * NT + threadIdx.x]);
-      B.X[m.row(i)] = x;
-      publish(px, m.pub(i), x);
-    }
-    if (group_sum<1, NT>(gs, S.size, rank, epoch, true, rt, lds.sums.sums)) return;
-    rt[0] = 0;
-#pragma unroll 1
-    for (int i = 0; i < RPT; ++i) {
-      if (!m.has(i)) continue;
-      const int row = m.row(i), p1 = A.rowptr[row + 1];
-      V r = A.b[row];
-      for (int p = A.rowptr[row]; p < p1; ++p) r = cfnma(A.val[p], px[A.col[p] + S.shift], r);
-      rt[0] += nrm2d(r);
-    }
-    if (group_sum<1, NT>(gs, S.size, rank, epoch, false, rt, lds.sums.sums)) return;
-    if (rank == 0 && threadIdx.x == 0) {
-      ResBatchEnd& o = B.end[sys];
-      o.status = e.status;
-      o.bd = e.bd;
-      o.rr = e.rr;
-      o.bb = e.bb;
-      o.rr_true = rt[0];
-      o.iters = e.iters_done;
-    }
+    if (res_bicgstab<double, E, EL, RPT, NT>(A, gs, S.size, rank, epoch, m, lds, e)) return;
+    if (res_finish<RPT, NT>(A, gs, S.size, rank, epoch, m, lds, e, B.end + sys, [&](int row, double2 x) { B.X[row] = x; }))
+      return;
+  }
+}
+
+// The systems of a sweep, whose matrices K - kappa_j M are formed where the rows
+// are loaded.  Each group of workgroups solves one system at a time and takes
+// the next one from the queue: its first workgroup draws the number, a sum over
+// the group hands it to the others.  The bits of a system's solution do not
+// depend on the group.  A group's published vectors have places of their own, in
+// whole cache lines, which its next system uses again: between the last reads
+// of one system (before the sum that ends res_finish) and the first of the next
+// lies the first barrier of its solve, which drops the caches.
+// The interleaved launch (k_sweep) streams 20 vectors of all systems through HBM
+// per iteration and meets at five barriers: 87 us per iteration for 32 systems of
+// 4,913 rows and for 3, 173 for 4 of 110,160, 553 for 64 of 117,649.  Here one
+// system's iteration takes 10 to 20 us and several run at a time: 14.9 -> 2.9 ms
+// and 13.6 -> 2.0 ms the call, 86.9 -> 19.6, 304 -> 291.
+template <int E, int EL, int RPT, int NT>
+__global__ __launch_bounds__(NT) void k_res_sweep(ResSweepArgs B) {
+  __shared__ ResBiLds<double, EL, RPT, NT> lds;
+  ResSweepSource A = B.src;
+  const int l = xcd_block(blockIdx.x, gridDim.x), group = l / B.size, rank = l - group * B.size;
+  const ResMap<RPT, NT> m(rank * A.rows, rank * A.rows + A.rows, A.n, (int)(group * B.area));
+  GridSum gs = A.gs;
+  gs.words += (size_t)group * kSumSets * kSumSetWords;
+  unsigned epoch = 0;
+  for (int q = group; q < B.nsys;) {
+    const int sys = __builtin_amdgcn_readfirstlane(B.order[q]);
+    A.j = sys;
+    A.kappa = uni(B.kap[sys]);
+    ResEnd e;
+    __syncthreads();
+    if (res_bicgstab<double, E, EL, RPT, NT>(A, gs, B.size, rank, epoch, m, lds, e)) return;
+    if (res_finish<RPT, NT>(A, gs, B.size, rank, epoch, m, lds, e, B.end + sys,
+                            [&](int row, double2 x) { B.X[(size_t)row * kSweepLanes + sys] = x; }))
+      return;
+    double next[1] = {0};
+    if (rank == 0 && threadIdx.x == 0) next[0] = (double)atomicAdd(B.next, 1);
+    __syncthreads();
+    if (group_sum<1, NT>(gs, B.size, rank, epoch, false, next, lds.sums.sums)) return;
+    q = __builtin_amdgcn_readfirstlane((int)next[0]);
   }
 }
 
@@ -599,12 +640,8 @@ bool resident_batch_plan(const hk_csr_s* A, int nsys, const int64_t* row_off, Re
   return best >= 0;
 }
 
-hipError_t resident_batch_launch(const ResBatchPlan& plan, ResBatchArgs args, hipStream_t s) {
-  const void* kern = nullptr;
-#define HK_RES(EE, EL, PP) \
-  if (plan.entries == EE && plan.rpt == PP) kern = (const void*)k_res_batch<EE, EL, PP, 512>;
-  HK_RES(8, 0, 1) HK_RES(8, 2, 2) HK_RES(15, 0, 1) HK_RES(15, 6, 2) HK_RES(27, 13, 1)
-#undef HK_RES
+// kern with `grid` workgroups of 512 threads, all of them resident.
+template <class Args> static hipError_t res_coop_launch(const void* kern, int grid, Args& args, hipStream_t s) {
   if (!kern) return hipErrorInvalidConfiguration;
   int per = 0, cus = 0, coop = 0, dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -612,9 +649,62 @@ hipError_t resident_batch_launch(const ResBatchPlan& plan, ResBatchArgs args, hi
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, 512, 0);
   if (e != hipSuccess) return e;
-  if (!coop || plan.grid > per * cus) return hipErrorInvalidConfiguration;
+  if (!coop || grid > per * cus) return hipErrorInvalidConfiguration;
   void* kargs[] = {&args};
-  return hipLaunchCooperativeKernel(kern, dim3(plan.grid), dim3(512), kargs, 0, s);
+  return hipLaunchCooperativeKernel(kern, dim3(grid), dim3(512), kargs, 0, s);
+}
+
+hipError_t resident_batch_launch(const ResBatchPlan& plan, ResBatchArgs args, hipStream_t s) {
+  const void* kern = nullptr;
+#define HK_RES(EE, EL, PP) \
+  if (plan.entries == EE && plan.rpt == PP) kern = (const void*)k_res_batch<EE, EL, PP, 512>;
+  HK_RES(8, 0, 1) HK_RES(8, 2, 2) HK_RES(15, 0, 1) HK_RES(15, 6, 2) HK_RES(27, 13, 1)
+#undef HK_RES
+  return res_coop_launch(kern, plan.grid, args, s);
+}
+
+// Rows per thread: whichever gets through the systems in less time, taken in
+// rounds of one system per group.
+bool resident_sweep_plan(int device, int64_t n, int64_t nnz, int max_row, int nsys, ResSweepPlan* plan) {
+  // a system of one workgroup stays with the interleaved launch, which is also
+  // the one that records barrier times: at that size a call with the record
+  // and one without have always given the same bits
+  if (n <= 512 || nnz <= 0 || max_row > kResEntries[2]) return false;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const int G = std::min(cus, kSumBlocks), cl = res_class(max_row);
+  double best = -1;
+  for (int rpt = 1; rpt <= kResMax[0][cl]; ++rpt) {
+    const int64_t least = (n + 512 * rpt - 1) / (512 * rpt);
+    if (least > G) continue;
+    ResSweepPlan p;
+    p.entries = kResEntries[cl];
+    p.rpt = rpt;
+    p.rows = (int)(((n + least - 1) / least + 63) / 64 * 64);
+    p.size = (int)((n + p.rows - 1) / p.rows);
+    p.groups = std::min(G / p.size, nsys);
+    const double t = (double)((nsys + p.groups - 1) / p.groups) * res_iteration_us(p.size, rpt);
+    if (best < 0 || t < best) {
+      best = t;
+      *plan = p;
+    }
+  }
+  return best >= 0;
+}
+
+hipError_t resident_sweep_launch(const ResSweepPlan& plan, ResSweepArgs args, hipStream_t s) {
+  const void* kern = nullptr;
+#define HK_RES(EE, EL, PP) \
+  if (plan.entries == EE && plan.rpt == PP) kern = (const void*)k_res_sweep<EE, EL, PP, 512>;
+  HK_RES(8, 0, 1) HK_RES(8, 2, 2) HK_RES(15, 0, 1) HK_RES(15, 6, 2) HK_RES(27, 13, 1)
+#undef HK_RES
+  args.src.rows = plan.rows;
+  args.size = plan.size;
+  args.groups = plan.groups;
+  return res_coop_launch(kern, plan.size * plan.groups, args, s);
 }
 
 template <class R> static const void* res_kernel(const ResShape& sh, int method) {

@@ -21,6 +21,7 @@ namespace hk {
 // these are.  Dropping them at every barrier cost 1.1 us of each at 256
 // workgroups.
 constexpr int kRing = 4;
+constexpr int kSweepLanes = 64;  // columns of a sweep's right-hand sides
 
 template <class R> struct ResArgs {
   using V = cplx<R>;
@@ -41,9 +42,18 @@ template <class R> struct ResArgs {
   double tol;
   long long maxit;
   double* history;
+  // entry p of A, with column c: of Ahat; the right-hand side's row
+  __device__ __forceinline__ V entry(int p) const { return val[p]; }
+  __device__ __forceinline__ V scaled(int p, int c) const;
+  __device__ __forceinline__ V rhs(int row) const { return b[row]; }
+  __device__ __forceinline__ V inv_diag(int row) const { return dinv[row]; }
 };
 
 // ---------------------------------------------------------- device helpers
+
+template <class R> __device__ __forceinline__ cplx<R> ResArgs<R>::scaled(int p, int c) const {
+  return cmul(val[p], dinv[c]);
+}
 
 template <class V> struct Pair { V u, v; };
 
@@ -119,7 +129,7 @@ template <class V, int E, int EL, int RPT, int NT> struct ResRows {
     for (int k = 0; k < E; ++k) {
       const int p = len > 0 ? s + min(k, len - 1) : 0;
       const int cc = A.col[p];
-      const V q = cmul(A.val[p], A.dinv[cc]);
+      const V q = A.scaled(p, cc);
       V v = k < len ? q : czero<V>();
       if (k % 4 == 3) here(v);
       if (k < ER) a[i][k] = v;
@@ -229,8 +239,7 @@ struct ResBatchEnd {
   long long iters;
 };
 struct ResBatchArgs {
-  ResArgs<double> base;       // gs.words: kSumSets * kSumSetWords for each system, and so are words2
-  unsigned long long* words2;
+  ResArgs<double> base;       // gs.words: kSumSets * kSumSetWords for each system
   const ResBatchSystem* sys;
   // workgroup l (in XCD order) has jobs job_ptr[l] .. job_ptr[l + 1]: system and rank in it
   const int *job_ptr, *job_sys, *job_rank;
@@ -247,6 +256,39 @@ struct ResBatchPlan {
 };
 bool resident_batch_plan(const hk_csr_s* A, int nsys, const int64_t* row_off, ResBatchPlan* plan);
 hipError_t resident_batch_launch(const ResBatchPlan& plan, ResBatchArgs args, hipStream_t s);
+
+// The systems (K - kappa_j M) x_j = b_j of a sweep (complex128 BiCGStab, K and M
+// real): `groups` runs of `size` workgroups of `rows` rows take one system after
+// the other from a queue, order[0 .. nsys), until it is empty.
+struct ResSweepSource : ResArgs<double> {
+  const double *K, *M, *kd, *md;  // values and diagonals
+  double2 kappa;
+  int j;  // b and x: column j of n x 64
+  __device__ __forceinline__ double2 of(double k, double m) const {
+    return make_double2(fma(-kappa.x, m, k), -kappa.y * m);
+  }
+  __device__ __forceinline__ double2 entry(int p) const { return of(K[p], M[p]); }
+  __device__ __forceinline__ double2 inv_diag(int row) const {
+    return cdiv(make_double2(1, 0), make_double2(kd[row] - kappa.x * md[row], -kappa.y * md[row]));
+  }
+  __device__ __forceinline__ double2 scaled(int p, int c) const { return cmul(entry(p), inv_diag(c)); }
+  __device__ __forceinline__ double2 rhs(int row) const { return b[(size_t)row * kSweepLanes + j]; }
+};
+struct ResSweepArgs {
+  ResSweepSource src;          // gs.words: kSumSets * kSumSetWords for each group
+  const double2* kap;
+  const int* order;
+  int* next;                   // the queue's front, `groups` at launch
+  int nsys, size, groups;
+  long long area;              // elements of a published vector of one group
+  double2* X;
+  ResBatchEnd* end;
+};
+struct ResSweepPlan {
+  int entries = 0, rpt = 0, rows = 0, size = 0, groups = 0;
+};
+bool resident_sweep_plan(int device, int64_t n, int64_t nnz, int max_row, int nsys, ResSweepPlan* plan);
+hipError_t resident_sweep_launch(const ResSweepPlan& plan, ResSweepArgs args, hipStream_t s);
 
 // The barrier words at the front of the scratch emptied, the launch itself:
 // kern with sh's grid and the argument struct at kargs[0], whose GridSum is gs.

@@ -211,3 +211,38 @@ def test_resident_batch(hk, oracle, sizes, row):
                 assert info["status"] == oi["status"] == hk.HK_NOT_CONVERGED and info["iters"] == k, (s, info, oi)
                 assert np.linalg.norm(xs - xo) <= 1e-11 * np.linalg.norm(xo), s
                 assert abs(info["relres_true"] - oi["relres_true"]) <= 1e-11, (s, info, oi)
+
+
+@pytest.mark.parametrize("n,row,nsys", [
+    (512, 15, 3), (513, 15, 3), (1000, 8, 64), (9000, 15, 33), (20011, 15, 5), (70001, 15, 7), (131073, 15, 3),
+    (140000, 8, 2), (40000, 27, 5), (131073, 27, 2), (3000, 28, 3)])
+def test_resident_sweep(hk, oracle, n, row, nsys):
+    """Sweeps on both sides of the limits: one system per group of workgroups, more systems than groups,
+    one and two rows per thread, and systems that do not fit.  Off the diagonal the scaled rows sum to less
+    than 1/2 as above."""
+    rowptr, col, val, _ = dominant(n, row, n + row)
+    rng = np.random.default_rng(n)
+    diag = col == np.repeat(np.arange(n), np.diff(rowptr))
+    K, M = np.where(diag, 1.0, val.real), np.where(diag, 0.2, val.imag)
+    kap = [complex(0.1 + 0.4 * j / nsys, 0.01 * (j + 1)) for j in range(nsys)]
+    B = np.zeros((n, 64), dtype=np.complex128)
+    for j in range(nsys):
+        B[:, j] = crandn(rng, n)
+    B[:, nsys - 1] = 0
+    args = (dev(rowptr), dev(col), dev(K), dev(M), kap, dev(B))
+    for its in (3, 0):
+        print("resident sweep", n, row, nsys, its, flush=True)
+        X, infos = hk.sweep_solve(*args, tol=1e-14, max_iter=its)
+        Xh = X.cpu().numpy()
+        for j in range(nsys):
+            xo, oi = oracle.bicgstab(rowptr, col, K - kap[j] * M, B[:, j], tol=1e-14, maxit=its)
+            assert infos[j]["iters"] == oi["iters"] and infos[j]["status"] == oi["status"], (its, j, infos[j], oi)
+            assert np.linalg.norm(Xh[:, j] - xo) <= 1e-11 * np.linalg.norm(xo), (its, j)
+            if j < nsys - 1:
+                r = oracle.residual(rowptr, col, K - kap[j] * M, B[:, j], Xh[:, j])
+                assert abs(np.linalg.norm(r) / np.linalg.norm(B[:, j]) - infos[j]["relres_true"]) <= 1e-12
+        assert np.all(Xh[:, nsys:] == 0)
+    X, infos = hk.sweep_solve(*args, tol=1e-10)
+    X2, _ = hk.sweep_solve(*args, tol=1e-10)
+    assert all(i["status"] == 0 and i["relres_true"] <= 1e-9 for i in infos)
+    assert torch.equal(torch.view_as_real(X), torch.view_as_real(X2))
