@@ -2020,10 +2020,8 @@ extern "C" int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, c
   ResSweepPlan rp;
   const bool resident = tuned && !opts->d_history && resident_sweep_plan(dev, n, nnz, max_row, nsys, &rp);
   DevArena ar;
-  const int64_t area = (n + 63) / 64 * 64;  // whole cache lines
-  const size_t set_words = kSumSets * kSumSetWords, nwords = resident ? rp.groups * set_words + 32 : 0;
   rc = ar.alloc(2 * a256(8 * (size_t)n) + a256(16 * kSys) + a256(64) +
-                (resident ? a256(16 * 3 * kRing * (size_t)area * rp.groups) + a256(8 * nwords) +
+                (resident ? a256(16 * rp.pub()) + a256(16 * rp.own()) + 256 + a256(8 * (rp.words() + 32)) +
                                 a256(sizeof(ResBatchEnd) * kSys) + a256(4 * (kSys + 1)) : 0),
                 "hk_sweep_solve");
   if (rc != HK_OK) return rc;
@@ -2168,8 +2166,9 @@ extern "C" int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, c
   BatchState hs{};
   if (resident) {
     ResSweepArgs ra{};
-    double2* const pub = ar.take<double2>(3 * kRing * (size_t)area * rp.groups);
-    unsigned long long* const words = ar.take<unsigned long long>(nwords);
+    double2* const pub = ar.take<double2>(rp.pub());
+    ra.own = ar.take<double2>(rp.own());
+    unsigned long long* const words = ar.take<unsigned long long>(rp.words() + 32);
     ra.end = ar.take<ResBatchEnd>(kSys);
     int* const order = ar.take<int>(kSys + 1);
     if (ar.off > ar.bytes) HK_FAIL(HK_EINVAL, "hk_sweep_solve: workspace layout exceeds its allocation");
@@ -2182,17 +2181,15 @@ extern "C" int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, c
     ra.src.md = md;
     ra.src.b = (const double2*)d_B;
     ra.src.pub = pub;
-    ra.src.stride = (long long)area * rp.groups;
     ra.src.tol = opts->tol;
     ra.src.maxit = opts->max_iter;
     ra.src.gs.words = words;
-    ra.src.gs.abort = (int*)(words + rp.groups * set_words);
+    ra.src.gs.abort = (int*)(words + rp.words());
     ra.src.gs.spin_limit = spin;
     ra.kap = kap;
     ra.order = order;
     ra.next = order + kSys;
     ra.nsys = nsys;
-    ra.area = area;
     ra.X = (double2*)d_X;
     // the systems of larger shifts, which take more iterations as a rule, first
     std::array<int, kSys + 1> ho{};
@@ -2200,11 +2197,11 @@ extern "C" int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, c
     std::stable_sort(ho.begin(), ho.begin() + nsys, [&](int p, int q) {
       return std::hypot(hk[p].x, hk[p].y) > std::hypot(hk[q].x, hk[q].y);
     });
-    ho[kSys] = rp.groups;
+    ho[kSys] = rp.slots > 1 ? 0 : rp.groups;
     std::vector<ResBatchEnd> ends(kSys);
     int ab = 0;
     e = hipMemcpyAsync(order, ho.data(), sizeof(ho), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = resident_reset(words, rp.groups * set_words, ra.src.gs.abort, s);
+    if (e == hipSuccess) e = resident_reset(words, rp.words(), ra.src.gs.abort, s);
     const hipError_t le = e == hipSuccess ? resident_sweep_launch(rp, ra, s) : e;
     if (e == hipSuccess && le == hipSuccess) {
       e = hipMemcpyAsync(ends.data(), ra.end, sizeof(ResBatchEnd) * nsys, hipMemcpyDeviceToHost, s);

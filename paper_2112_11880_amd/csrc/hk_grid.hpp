@@ -391,6 +391,126 @@ __device__ __forceinline__ bool grid_sum_many(const GridSum& gs, unsigned long l
   return stop != 0;
 }
 
+// ---------------------------------------- the same for the sums of several solves
+//
+// Up to 2 NP sums.  A workgroup's words fill a row of 16 NP bytes, kWideReps
+// times; the threads read all rows in order, 16 bytes a lane, each thread the
+// same pair of sums of NT / NP rows apart, so that a wave is left with 64 / NP
+// partial sums of a pair to add.  (group_sum gives a thread one workgroup's words
+// and the wave a full reduction for every sum.)
+constexpr int kWideReps = 4;
+
+// a + (a of the other half) in the lower 32 lanes, the same of b in the upper;
+// with HALF = 16 in the even and odd rows of 16 lanes: two values' sums step on
+// in one register.
+template <int HALF> __device__ __forceinline__ double fold(double a, double b) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
+  unsigned r[2][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const unsigned u = (unsigned)(x >> (32 * h)), v = (unsigned)(y >> (32 * h));
+    if constexpr (HALF == 32) {
+      const auto t = __builtin_amdgcn_permlane32_swap(u, v, false, false);
+      r[0][h] = t[0];
+      r[1][h] = t[1];
+    } else {
+      const auto t = __builtin_amdgcn_permlane16_swap(u, v, false, false);
+      r[0][h] = t[0];
+      r[1][h] = t[1];
+    }
+  }
+  return __longlong_as_double((long long)(((unsigned long long)r[0][1] << 32) | r[0][0])) +
+         __longlong_as_double((long long)(((unsigned long long)r[1][1] << 32) | r[1][0]));
+}
+// Sums of four values over the wave, in lanes 15 (a), 31 (c), 47 (b) and 63 (d):
+// 21 instructions where four wave_sum63 take 72.
+__device__ __forceinline__ double wave_sums4(double a, double b, double c, double d) {
+  double v = fold<16>(fold<32>(a, b), fold<32>(c, d));
+  v = dpp_add<0x111>(v);
+  v = dpp_add<0x112>(v);
+  v = dpp_add<0x114>(v);
+  return dpp_add<0x118>(v);
+}
+template <int NP> struct WideSum {
+  static constexpr size_t kSetWords = (size_t)kWideReps * kSumBlocks * NP * 2;
+  static constexpr size_t kWords = kSumSets * kSetWords;
+};
+
+// waves[c * W + w], c < nv: the workgroup's partial sums by wave, written before
+// the call; parts[c * W + w] on return: partial totals, to be added over w.
+// Otherwise as group_sum without INV.
+template <int NP, int NT>
+__device__ __forceinline__ bool group_sum_wide(const GridSum& gs, unsigned long long* words, int size, int rank,
+                                               unsigned& epoch, int nv, const double* waves, double* parts) {
+  constexpr int W = NT / kWave, kRows = NT / NP, U = (kSumBlocks + kRows - 1) / kRows;
+  static_assert(kWideReps * NP <= NT && kWave % NP == 0, "one store per thread, pairs within a wave");
+  const int np = (nv + 1) / 2;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // addresses are not worth registers from call to call
+  const int pair = tid % NP;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's published elements
+  __syncthreads();
+  unsigned long long* set = words + (epoch % kSumSets) * WideSum<NP>::kSetWords;
+  unsigned long long* old = words + ((epoch + kSumSets - 1) % kSumSets) * WideSum<NP>::kSetWords;
+  auto at_pair = [&](int rep, int b) { return ((rep * kSumBlocks + b) * NP + pair) * 16; };
+  if (tid < kWideReps * NP && pair < np) {
+    double s[2] = {0, 0};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int c = 2 * pair + h;
+      if (c < nv)
+        for (int j = 0; j < W; ++j) s[h] += waves[c * W + j];
+    }
+    const nu2 mine = {sum_word(s[0]), sum_word(s[1])};
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(ni4, mine), pub_rsrc(set), at_pair(tid / NP, rank),
+                                           0, kAuxSc1);
+  }
+  bool ok = true;
+  double tot[2] = {0, 0};
+  if (pair < np) {
+    const int rep = rank % kWideReps, row = tid / NP;
+    const unsigned long long t0 = wall_clock64();
+    auto fetch = [&](int b) {
+      return __builtin_bit_cast(nu2, __builtin_amdgcn_raw_buffer_load_b128(pub_rsrc(set), at_pair(rep, b), 0, kAuxSc1));
+    };
+    nu2 q[U];
+    for (int spins = 0;; ++spins) {
+      bool all = true;
+      asm volatile("" ::: "memory");  // loaded anew in every turn
+#pragma unroll
+      for (int u = 0; u < U; ++u) q[u] = fetch(min(row + u * kRows, size - 1));
+#pragma unroll
+      for (int u = 0; u < U; ++u) all = all && q[u][0] != kSumEmpty && q[u][1] != kSumEmpty;
+      if (all) break;
+      if (sum_give_up(gs, t0, spins)) { ok = false; break; }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = row + u * kRows < size;
+      tot[0] += in ? __longlong_as_double((long long)q[u][0]) : 0.0;
+      tot[1] += in ? __longlong_as_double((long long)q[u][1]) : 0.0;
+    }
+  }
+#pragma unroll
+  for (int d = NP; d < kWave; d *= 2) {
+    tot[0] += __shfl_xor(tot[0], d);
+    tot[1] += __shfl_xor(tot[1], d);
+  }
+  if (tid % kWave < NP) {
+    const int w = tid / kWave;
+    parts[(2 * pair) * W + w] = tot[0];
+    parts[(2 * pair + 1) * W + w] = tot[1];
+  }
+  const int stop = __syncthreads_or(!ok);
+  if (tid < kWideReps * NP) {
+    const nu2 empty = {kSumEmpty, kSumEmpty};
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(ni4, empty), pub_rsrc(old), at_pair(tid / NP, rank),
+                                           0, kAuxSc1);
+  }
+  ++epoch;
+  return stop != 0;
+}
+
 // Host: the spin limit of a launch, kSpinLimitTicks unless the environment
 // variable HK_BARRIER_SPIN_TICKS holds a positive count (tests use a tiny
 // one to drive the abort path).

@@ -663,8 +663,20 @@ hipError_t resident_batch_launch(const ResBatchPlan& plan, ResBatchArgs args, hi
   return res_coop_launch(kern, plan.grid, args, s);
 }
 
-// Rows per thread: whichever gets through the systems in less time, taken in
-// rounds of one system per group.
+// Time of one iteration of `slots` systems at a time in us, as measured: 26 and 43
+// with 3 and 6 slots of 59 workgroups, 33 with 4 of 216, 31 and 45 with 3 and 6 of
+// 230.
+static double many_iteration_us(int size, int slots) { return 12 + 0.02 * size + 4.6 * slots; }
+
+// Rows per thread, or systems at a time: whichever gets through the systems in
+// less time, taken in rounds of one system per group, or as long as the slots
+// are full (each is filled again as soon as it is free).  64 systems of 117,649
+// rows: 291 ms with two rows per thread (two groups of one system), 212 with six
+// slots; two systems are faster with a group each (20 us per iteration against
+// 29).
+size_t ResSweepPlan::words() const {
+  return (size_t)groups * (kSumSets * kSumSetWords + (slots > 1 ? resident_many_words(slots) : 0));
+}
 bool resident_sweep_plan(int device, int64_t n, int64_t nnz, int max_row, int nsys, ResSweepPlan* plan) {
   // a system of one workgroup stays with the interleaved launch, which is also
   // the one that records barrier times: at that size a call with the record
@@ -686,10 +698,21 @@ bool resident_sweep_plan(int device, int64_t n, int64_t nnz, int max_row, int ns
     p.rows = (int)(((n + least - 1) / least + 63) / 64 * 64);
     p.size = (int)((n + p.rows - 1) / p.rows);
     p.groups = std::min(G / p.size, nsys);
-    const double t = (double)((nsys + p.groups - 1) / p.groups) * res_iteration_us(p.size, rpt);
-    if (best < 0 || t < best) {
-      best = t;
-      *plan = p;
+    p.area = (n + 63) / 64 * 64;  // whole cache lines
+    auto take = [&](double us) {
+      const int at_a_time = p.groups * p.slots;
+      const double rounds = p.slots > 1 ? std::max(1.0, (double)nsys / at_a_time) : (nsys + at_a_time - 1) / at_a_time;
+      const double t = rounds * us;
+      if (best < 0 || t < best) {
+        best = t;
+        *plan = p;
+      }
+    };
+    take(res_iteration_us(p.size, rpt));
+    if (rpt == 1 && cl <= 1) {
+      p.entries = 15;
+      p.slots = std::min((nsys + p.groups - 1) / p.groups, kManySlots);
+      if (p.slots > 1) take(many_iteration_us(p.size, p.slots));
     }
   }
   return best >= 0;
@@ -701,9 +724,13 @@ hipError_t resident_sweep_launch(const ResSweepPlan& plan, ResSweepArgs args, hi
   if (plan.entries == EE && plan.rpt == PP) kern = (const void*)k_res_sweep<EE, EL, PP, 512>;
   HK_RES(8, 0, 1) HK_RES(8, 2, 2) HK_RES(15, 0, 1) HK_RES(15, 6, 2) HK_RES(27, 13, 1)
 #undef HK_RES
+  if (plan.slots > 1) kern = resident_many_kernel(plan.entries, plan.slots);
   args.src.rows = plan.rows;
+  args.src.stride = plan.area * plan.groups;
   args.size = plan.size;
-  args.groups = plan.groups;
+  args.slots = plan.slots;
+  args.area = plan.area;
+  args.wide = args.src.gs.words + (size_t)plan.groups * kSumSets * kSumSetWords;
   return res_coop_launch(kern, plan.size * plan.groups, args, s);
 }
 

@@ -258,18 +258,18 @@ bool resident_batch_plan(const hk_csr_s* A, int nsys, const int64_t* row_off, Re
 hipError_t resident_batch_launch(const ResBatchPlan& plan, ResBatchArgs args, hipStream_t s);
 
 // The systems (K - kappa_j M) x_j = b_j of a sweep (complex128 BiCGStab, K and M
-// real): `groups` runs of `size` workgroups of `rows` rows take one system after
-// the other from a queue, order[0 .. nsys), until it is empty.
+// real): `groups` runs of `size` workgroups of `rows` rows take the systems from
+// a queue, order[0 .. nsys), until it is empty.
 struct ResSweepSource : ResArgs<double> {
   const double *K, *M, *kd, *md;  // values and diagonals
   double2 kappa;
   int j;  // b and x: column j of n x 64
-  __device__ __forceinline__ double2 of(double k, double m) const {
+  static __device__ __forceinline__ double2 of(double k, double m, double2 kappa) {
     return make_double2(fma(-kappa.x, m, k), -kappa.y * m);
   }
-  __device__ __forceinline__ double2 entry(int p) const { return of(K[p], M[p]); }
+  __device__ __forceinline__ double2 entry(int p) const { return of(K[p], M[p], kappa); }
   __device__ __forceinline__ double2 inv_diag(int row) const {
-    return cdiv(make_double2(1, 0), make_double2(kd[row] - kappa.x * md[row], -kappa.y * md[row]));
+    return cdiv(make_double2(1, 0), of(kd[row], md[row], kappa));
   }
   __device__ __forceinline__ double2 scaled(int p, int c) const { return cmul(entry(p), inv_diag(c)); }
   __device__ __forceinline__ double2 rhs(int row) const { return b[(size_t)row * kSweepLanes + j]; }
@@ -279,14 +279,26 @@ struct ResSweepArgs {
   const double2* kap;
   const int* order;
   int* next;                   // the queue's front, `groups` at launch
-  int nsys, size, groups;
-  long long area;              // elements of a published vector of one group
+  int nsys, size, slots;       // slots: systems a group works on at a time
+  long long area;              // elements of a published vector of one system
+  double2* own;                // slots > 1: what the slots keep per row
+  unsigned long long* wide;    // and the words of group_sum_wide, all kSumEmpty at launch
   double2* X;
   ResBatchEnd* end;
 };
 struct ResSweepPlan {
-  int entries = 0, rpt = 0, rows = 0, size = 0, groups = 0;
+  int entries = 0, rpt = 0, rows = 0, size = 0, groups = 0, slots = 1;
+  int64_t area = 0;
+  // elements of the published vectors and of the slots' own ones; barrier words
+  size_t pub() const { return (size_t)area * groups * (slots > 1 ? (2 * kRing + 1) * slots : 3 * kRing); }
+  size_t own() const { return slots > 1 ? (size_t)area * groups * 2 * slots : 0; }
+  size_t words() const;
 };
+constexpr int kManySlots = 6;  // what registers and LDS take
+// hk_resident_sweep.hip: the kernel for `slots` > 1, the words of a group's
+// group_sum_wide
+const void* resident_many_kernel(int entries, int slots);
+size_t resident_many_words(int slots);
 bool resident_sweep_plan(int device, int64_t n, int64_t nnz, int max_row, int nsys, ResSweepPlan* plan);
 hipError_t resident_sweep_launch(const ResSweepPlan& plan, ResSweepArgs args, hipStream_t s);
 

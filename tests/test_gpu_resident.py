@@ -215,7 +215,9 @@ def test_resident_batch(hk, oracle, sizes, row):
 
 @pytest.mark.parametrize("n,row,nsys", [
     (512, 15, 3), (513, 15, 3), (1000, 8, 64), (9000, 15, 33), (20011, 15, 5), (70001, 15, 7), (131073, 15, 3),
-    (140000, 8, 2), (40000, 27, 5), (131073, 27, 2), (3000, 28, 3)])
+    (140000, 8, 2), (40000, 27, 5), (131073, 27, 2), (3000, 28, 3),
+    # several systems at a time in a group: 2 to 8, fewer and more than the queue holds
+    (60001, 15, 4), (40001, 15, 64), (131072, 15, 2), (100003, 15, 19), (33000, 8, 13)])
 def test_resident_sweep(hk, oracle, n, row, nsys):
     """Sweeps on both sides of the limits: one system per group of workgroups, more systems than groups,
     one and two rows per thread, and systems that do not fit.  Off the diagonal the scaled rows sum to less
