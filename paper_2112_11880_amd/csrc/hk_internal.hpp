@@ -104,6 +104,7 @@ struct ResShape {
   int threads = 0;  // threads per workgroup
   int rows = 0;     // rows per workgroup
   int grid = 0;     // workgroups
+  int packed = 0;   // all on one XCD
 };
 // The shape for A's pattern with values of precision prec (0 complex128, 1
 // complex64).

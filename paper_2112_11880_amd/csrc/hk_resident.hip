@@ -8,8 +8,8 @@
 // of such a system is bound by its eight launches and by the chains of
 // dependent loads in each -- 28 us on 4,913 rows, 46-52 us on 117,649, where
 // its bytes alone would take 0.3 and 9 us.  Here an iteration is three (TFQMR:
-// two) barriers that also sum, grid_sum in hk_grid.hpp, and between them
-// row-local arithmetic and the products' gathers: 9.6 us on 4,913 rows, 13.3 on
+// two) barriers that also sum, group_sum in hk_grid.hpp, and between them
+// row-local arithmetic and the products' gathers: 7 us on 4,913 rows (one XCD), 13.3 on
 // 117,649 (3 us per barrier, 2-3 per gather of two vectors, which bound it now),
 // TFQMR on 70,224 rows of 27 entries 66 -> 14.6 us, complex64 BiCGStab on 279,496
 // rows 60 -> 21.8 us.
@@ -51,10 +51,10 @@ template <class R, int EL, int RPT, int NT> struct ResBiLds {
 };
 
 // BiCGStab on the rows [r0, rend) of this workgroup, number `rank` of the `size`
-// that solve the system: D x is left in lds.y.  Returns true if the kernel must
-// stop.
-template <class R, int E, int EL, int RPT, int NT, class Src>
-__device__ __forceinline__ bool res_bicgstab(const Src& A, const GridSum& gs, int size, int rank, unsigned& epoch,
+// that solve the system: D x is left in lds.y.  LOC: they may find that they
+// share an XCD.  Returns true if the kernel must stop.
+template <class R, int E, int EL, int RPT, int NT, bool LOC, class Src>
+__device__ __forceinline__ bool res_bicgstab(const Src& A, GridSum& gs, int size, int rank, unsigned& epoch,
                                              const ResMap<RPT, NT>& m, ResBiLds<R, EL, RPT, NT>& lds, ResEnd& end) {
   using V = cplx<R>;
   // the rows' gathered r, kept from the v product for the t product where
@@ -68,7 +68,8 @@ __device__ __forceinline__ bool res_bicgstab(const Src& A, const GridSum& gs, in
   // read for the last time before the iteration's second barrier, so of the
   // third barriers of any kRing iterations in a row one drops the caches.
   auto pub = [&](int i, long long at_it) { return A.pub + (kRing * i + (int)(at_it & (kRing - 1))) * A.stride; };
-  double sum2[2] = {0, 0};
+  double sum2[4] = {0, 0, 0, 0};
+  same_xcd_sums(sum2[2], sum2[3]);
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
     const int row = m.row(i), l = i * NT + threadIdx.x;
@@ -79,8 +80,8 @@ __device__ __forceinline__ bool res_bicgstab(const Src& A, const GridSum& gs, in
       bi = A.rhs(row);
       ri = A.x0 ? A.r0[row] : bi;
       if (A.x0) yi = cdiv(A.x0[row], A.inv_diag(row));
-      publish(pub(0, 1), m.pub(i), ri);
-      publish(pub(1, 1), m.pub(i), czero<V>());
+      publish(gs, pub(0, 1), m.pub(i), ri);
+      publish(gs, pub(1, 1), m.pub(i), czero<V>());
     }
     r[i] = ri;
     q[i] = p[i] = v[i] = t[i] = czero<V>();
@@ -89,7 +90,8 @@ __device__ __forceinline__ bool res_bicgstab(const Src& A, const GridSum& gs, in
     sum2[0] += nrm2d(bi);
     sum2[1] += nrm2d(ri);
   }
-  if (group_sum<2, NT>(gs, size, rank, epoch, true, sum2, lds.sums.sums)) return true;
+  if (group_sum<4, NT>(gs, size, rank, epoch, true, sum2, lds.sums.sums)) return true;
+  if (LOC) gs.local = same_xcd(size, sum2[2], sum2[3]);
   const bool first = rank == 0 && threadIdx.x == 0;
   const double bb = uni(sum2[0]), theta2 = uni(A.tol * A.tol * bb);
   double rr = uni(sum2[1]);
@@ -115,7 +117,7 @@ __device__ __forceinline__ bool res_bicgstab(const Src& A, const GridSum& gs, in
               return cfma(be, x.v, x.u);
             });
         if (m.has(i)) {
-          publish(pv, m.pub(i), v[i]);
+          publish(gs, pv, m.pub(i), v[i]);
           dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
         }
       }
@@ -188,8 +190,8 @@ __device__ __forceinline__ bool res_bicgstab(const Src& A, const GridSum& gs, in
       r[i] = cfnma(om, t[i], s);
       q[i] = cfnma(om, v[i], p[i]);
       if (m.has(i)) {
-        publish(pub(0, it + 1), m.pub(i), r[i]);
-        publish(pub(1, it + 1), m.pub(i), q[i]);
+        publish(gs, pub(0, it + 1), m.pub(i), r[i]);
+        publish(gs, pub(1, it + 1), m.pub(i), q[i]);
         xr[0] += nrm2d(r[i]);
         dotc_acc(s_rh[l], r[i], xr[1], xr[2]);
       }
@@ -225,10 +227,14 @@ template <class R, int E, int EL, int RPT, int NT>
 __global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
   __shared__ ResBiLds<R, EL, RPT, NT> lds;
   if (*A.flag) return;
-  const ResMap<RPT, NT> m(A.n, A.rows);
+  const ResPlace at(A.packed);
+  if (at.idle) return;
+  const ResMap<RPT, NT> m(A.n, A.rows, at.at);
+  GridSum gs = A.gs;
+  gs.local = 0;
   ResEnd e;
   unsigned epoch = 0;
-  if (res_bicgstab<R, E, EL, RPT, NT>(A, A.gs, gridDim.x, blockIdx.x, epoch, m, lds, e)) return;
+  if (res_bicgstab<R, E, EL, RPT, NT, NT == 256>(A, gs, at.size, at.rank, epoch, m, lds, e)) return;
 #pragma unroll
   for (int i = 0; i < RPT; ++i)
     if (m.has(i)) A.y[m.row(i)] = lds.y[i * NT + threadIdx.x];
@@ -252,7 +258,7 @@ __device__ __forceinline__ bool res_finish(const Src& A, const GridSum& gs, int 
     if (!m.has(i)) continue;
     const V x = cmul(A.inv_diag(m.row(i)), lds.y[i * NT + threadIdx.x]);
     put(m.row(i), x);
-    publish(px, m.pub(i), x);
+    publish(gs, px, m.pub(i), x);
   }
   if (group_sum<1, NT>(gs, size, rank, epoch, true, rt, lds.sums.sums)) return true;
   rt[0] = 0;
@@ -287,7 +293,7 @@ __global__ __launch_bounds__(NT) void k_res_batch(ResBatchArgs B) {
     ResEnd e;
     unsigned epoch = 0;
     __syncthreads();
-    if (res_bicgstab<double, E, EL, RPT, NT>(A, gs, S.size, rank, epoch, m, lds, e)) return;
+    if (res_bicgstab<double, E, EL, RPT, NT, true>(A, gs, S.size, rank, epoch, m, lds, e)) return;
     if (res_finish<RPT, NT>(A, gs, S.size, rank, epoch, m, lds, e, B.end + sys, [&](int row, double2 x) { B.X[row] = x; }))
       return;
   }
@@ -310,7 +316,9 @@ template <int E, int EL, int RPT, int NT>
 __global__ __launch_bounds__(NT) void k_res_sweep(ResSweepArgs B) {
   __shared__ ResBiLds<double, EL, RPT, NT> lds;
   ResSweepSource A = B.src;
-  const int l = xcd_block(blockIdx.x, gridDim.x), group = l / B.size, rank = l - group * B.size;
+  const ResGroup at(B);
+  if (at.idle) return;
+  const int group = at.group, rank = at.rank;
   const ResMap<RPT, NT> m(rank * A.rows, rank * A.rows + A.rows, A.n, (int)(group * B.area));
   GridSum gs = A.gs;
   gs.words += (size_t)group * kSumSets * kSumSetWords;
@@ -321,7 +329,7 @@ __global__ __launch_bounds__(NT) void k_res_sweep(ResSweepArgs B) {
     A.kappa = uni(B.kap[sys]);
     ResEnd e;
     __syncthreads();
-    if (res_bicgstab<double, E, EL, RPT, NT>(A, gs, B.size, rank, epoch, m, lds, e)) return;
+    if (res_bicgstab<double, E, EL, RPT, NT, true>(A, gs, B.size, rank, epoch, m, lds, e)) return;
     if (res_finish<RPT, NT>(A, gs, B.size, rank, epoch, m, lds, e, B.end + sys,
                             [&](int row, double2 x) { B.X[(size_t)row * kSweepLanes + sys] = x; }))
       return;
@@ -342,7 +350,12 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
   __shared__ ResLds<NT> lds;
   __shared__ V s_rh[RPT * NT], s_y[RPT * NT], s_d[RPT * NT], s_lv[EL > 0 ? RPT * EL * NT : 1];
   if (*A.flag) return;
-  const ResMap<RPT, NT> m(A.n, A.rows);
+  const ResPlace at_place(A.packed);
+  if (at_place.idle) return;
+  const int size = at_place.size, rank = at_place.rank;
+  const ResMap<RPT, NT> m(A.n, A.rows, at_place.at);
+  GridSum gs = A.gs;
+  gs.local = 0;
   ResRows<V, E, EL, RPT, NT> M;
   M.lv = s_lv;
   V y1[RPT], v[RPT], u1[RPT], w[RPT], y2[RPT], u2[RPT];
@@ -352,7 +365,8 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
   // barriers
   auto pub = [&](int i, long long at_k) { return A.pub + (kRing * i + (int)(at_k & (kRing - 1))) * A.stride; };
   unsigned epoch = 0;
-  double sum2[2] = {0, 0};
+  double sum2[4] = {0, 0, 0, 0};
+  same_xcd_sums(sum2[2], sum2[3]);
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
     const int row = m.row(i), l = i * NT + threadIdx.x;
@@ -363,7 +377,7 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
       bi = A.b[row];
       ri = A.x0 ? A.r0[row] : bi;
       if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
-      publish(pub(0, 1), m.pub(i), ri);
+      publish(gs, pub(0, 1), m.pub(i), ri);
     }
     y1[i] = w[i] = ri;
     v[i] = u1[i] = y2[i] = u2[i] = czero<V>();
@@ -373,8 +387,9 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
     sum2[0] += nrm2d(bi);
     sum2[1] += nrm2d(ri);
   }
-  if (grid_sum<2, NT>(A.gs, epoch, true, sum2, lds.sums)) return;
-  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  if (group_sum<4, NT>(gs, size, rank, epoch, true, sum2, lds.sums)) return;
+  if (NT == 256) gs.local = same_xcd(size, sum2[2], sum2[3]);
+  const bool first = rank == 0 && threadIdx.x == 0;
   const double bb = uni(sum2[0]), theta2 = uni(A.tol * A.tol * bb);
   double rr = uni(sum2[1]), tau = uni(sqrt(rr)), theta = 0;
   V rho = make_double2(rr, 0), alpha = czero<V>(), eta2 = czero<V>(), coef1 = czero<V>();
@@ -417,11 +432,11 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
           i, [&](int, unsigned c) { return at(py1, c); }, [&](int, V x) { return x; });
       v[i] = u1[i];
       if (m.has(i)) {
-        publish(pub(1, 1), m.pub(i), v[i]);
+        publish(gs, pub(1, 1), m.pub(i), v[i]);
         dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
       }
     }
-    if (grid_sum<2, NT>(A.gs, epoch, false, sg, lds.sums)) return;
+    if (group_sum<2, NT>(gs, size, rank, epoch, false, sg, lds.sums)) return;
     sigma_step(sg);
   }
   while (status == S_RUN) {
@@ -440,14 +455,14 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
           [&](int, const Pair<V>& x) { return cfnma(alpha, x.v, x.u); });
       w[i] = cfnma(alpha, u2[i], w[i]);
       if (m.has(i)) {
-        publish(pw, m.pub(i), w[i]);
-        publish(py2, m.pub(i), y2[i]);
+        publish(gs, pw, m.pub(i), w[i]);
+        publish(gs, py2, m.pub(i), y2[i]);
         hs[0] += w1;
         hs[1] += nrm2d(w[i]);
         dotc_acc(s_rh[i * NT + threadIdx.x], w[i], hs[2], hs[3]);
       }
     }
-    if (grid_sum<4, NT>(A.gs, epoch, (k & (kRing - 1)) == 0, hs, lds.sums)) return;
+    if (group_sum<4, NT>(gs, size, rank, epoch, (k & (kRing - 1)) == 0, hs, lds.sums)) return;
     const V eta1 = half_step(hs[0], 2 * k - 1);
     const V coef2 = uni(cdiv(cmul(make_double2(theta * theta, 0), eta1), alpha));
     done = k;
@@ -497,12 +512,12 @@ __global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
           [&](int, const Pair<V>& x) { return cfma(beta, x.u, x.v); });
       v[i] = cfma(beta, cfma(beta, v[i], u2[i]), u1[i]);
       if (m.has(i)) {
-        publish(pub(0, k + 1), m.pub(i), y1[i]);
-        publish(pub(1, k + 1), m.pub(i), v[i]);
+        publish(gs, pub(0, k + 1), m.pub(i), y1[i]);
+        publish(gs, pub(1, k + 1), m.pub(i), v[i]);
         dotc_acc(s_rh[i * NT + threadIdx.x], v[i], sg[0], sg[1]);
       }
     }
-    if (grid_sum<2, NT>(A.gs, epoch, ((k + 1) & (kRing - 1)) == 0, sg, lds.sums)) return;
+    if (group_sum<2, NT>(gs, size, rank, epoch, ((k + 1) & (kRing - 1)) == 0, sg, lds.sums)) return;
     ++k;
     sigma_step(sg);
   }
@@ -564,13 +579,21 @@ ResShape resident_shape(const hk_csr_s* A, int prec) {
   sh.entries = kResEntries[cl];
   sh.rpt = rpt;
   sh.threads = threads;
+  // on one XCD, two workgroups of 256 threads on each of its CUs at most: 4,913
+  // rows (20 workgroups) 9.3 -> 7.1 us per iteration, set-up included
+  sh.packed = threads == 256 && sh.grid <= 2 * (cus / kXcds) && sh.grid > 1;
   return sh;
 }
 
 // Time of one BiCGStab iteration in us, as measured: the barriers grow with the
-// workgroups (9.6 us at 20, 13.3 at 230), a second row per thread costs the
+// workgroups (9.6 us at 20, 13.3 at 230; on one XCD, whose groups share an L2, 7
+// at 10 and 15 with two rows per thread at 30), a second row per thread costs the
 // gathers again.
-static double res_iteration_us(int size, int rpt) { return 9.3 + 0.0175 * size + 6.5 * (rpt - 1); }
+static double res_iteration_us(int size, int rpt, bool local) {
+  return local ? 6.7 + 0.03 * size + 7.5 * (rpt - 1) : 9.3 + 0.0175 * size + 6.5 * (rpt - 1);
+}
+// Workgroups of a grid of G that share an XCD, consecutive in XCD order.
+static int res_span(int G) { return G % kXcds == 0 ? G / kXcds : G; }
 
 // Each system is given to the run of workgroups that is free first, the large
 // ones first; with one or two rows per thread, whichever ends earlier (the
@@ -582,7 +605,7 @@ bool resident_batch_plan(const hk_csr_s* A, int nsys, const int64_t* row_off, Re
     (void)hipGetLastError();
     return false;
   }
-  const int G = std::min(cus, kSumBlocks), cl = res_class(A->max_row);
+  const int G = std::min(cus, kSumBlocks), cl = res_class(A->max_row), span = res_span(G);
   std::vector<int> order(nsys);
   for (int k = 0; k < nsys; ++k) order[k] = k;
   auto rows_of = [&](int k) { return row_off[k + 1] - row_off[k]; };
@@ -593,7 +616,6 @@ bool resident_batch_plan(const hk_csr_s* A, int nsys, const int64_t* row_off, Re
     ResBatchPlan p;
     p.entries = kResEntries[cl];
     p.rpt = rpt;
-    p.grid = G;
     p.sys.resize(nsys);
     std::vector<double> free_at(G, 0.0);
     std::vector<std::vector<std::pair<int, int>>> jobs(G);
@@ -612,12 +634,15 @@ bool resident_batch_plan(const hk_csr_s* A, int nsys, const int64_t* row_off, Re
       s.size = (int)((rows_of(k) + s.rows - 1) / s.rows);
       int at = 0;
       double when = -1;
+      // on one XCD where it fits
+      const bool local = s.size <= span;
       for (int l = 0; l + s.size <= G; ++l) {
+        if (local && l / span != (l + s.size - 1) / span) continue;
         double t = 0;
         for (int q = l; q < l + s.size; ++q) t = std::max(t, free_at[q]);
         if (when < 0 || t < when) { when = t; at = l; }
       }
-      const double t = when + std::cbrt((double)rows_of(k)) * res_iteration_us(s.size, rpt);
+      const double t = when + std::cbrt((double)rows_of(k)) * res_iteration_us(s.size, rpt, local);
       for (int q = 0; q < s.size; ++q) {
         free_at[at + q] = t;
         jobs[at + q].push_back({k, q});
@@ -666,7 +691,9 @@ hipError_t resident_batch_launch(const ResBatchPlan& plan, ResBatchArgs args, hi
 // Time of one iteration of `slots` systems at a time in us, as measured: 26 and 43
 // with 3 and 6 slots of 59 workgroups, 33 with 4 of 216, 31 and 45 with 3 and 6 of
 // 230.
-static double many_iteration_us(int size, int slots) { return 12 + 0.02 * size + 4.6 * slots; }
+static double many_iteration_us(int size, int slots, bool local) {
+  return (local ? 7 : 12) + 0.02 * size + 4.6 * slots;
+}
 
 // Rows per thread, or systems at a time: whichever gets through the systems in
 // less time, taken in rounds of one system per group, or as long as the slots
@@ -687,7 +714,7 @@ bool resident_sweep_plan(int device, int64_t n, int64_t nnz, int max_row, int ns
     (void)hipGetLastError();
     return false;
   }
-  const int G = std::min(cus, kSumBlocks), cl = res_class(max_row);
+  const int G = std::min(cus, kSumBlocks), cl = res_class(max_row), xcd = res_span(G);
   double best = -1;
   for (int rpt = 1; rpt <= kResMax[0][cl]; ++rpt) {
     const int64_t least = (n + 512 * rpt - 1) / (512 * rpt);
@@ -697,22 +724,32 @@ bool resident_sweep_plan(int device, int64_t n, int64_t nnz, int max_row, int ns
     p.rpt = rpt;
     p.rows = (int)(((n + least - 1) / least + 63) / 64 * 64);
     p.size = (int)((n + p.rows - 1) / p.rows);
-    p.groups = std::min(G / p.size, nsys);
     p.area = (n + 63) / 64 * 64;  // whole cache lines
-    auto take = [&](double us) {
-      const int at_a_time = p.groups * p.slots;
-      const double rounds = p.slots > 1 ? std::max(1.0, (double)nsys / at_a_time) : (nsys + at_a_time - 1) / at_a_time;
-      const double t = rounds * us;
-      if (best < 0 || t < best) {
-        best = t;
-        *plan = p;
+    // over the whole chip, and with every group on one XCD
+    for (int span : {G, xcd}) {
+      if (p.size > span || (span == G && p.size <= 1)) continue;
+      const bool local = span == xcd && xcd < G;
+      p.entries = kResEntries[cl];
+      p.slots = 1;
+      p.groups = std::min(G / span * (span / p.size), nsys);
+      p.grid = local ? G : p.size * p.groups;
+      p.span = local ? span : p.grid;
+      auto take = [&](double us) {
+        const int at_a_time = p.groups * p.slots;
+        const double rounds = p.slots > 1 ? std::max(1.0, (double)nsys / at_a_time) : (nsys + at_a_time - 1) / at_a_time;
+        const double t = rounds * us;
+        if (best < 0 || t < best) {
+          best = t;
+          *plan = p;
+        }
+      };
+      take(res_iteration_us(p.size, rpt, local));
+      if (rpt == 1 && cl <= 1) {
+        p.entries = 15;
+        p.slots = std::min((nsys + p.groups - 1) / p.groups, kManySlots);
+        if (p.slots > 1) take(many_iteration_us(p.size, p.slots, local));
       }
-    };
-    take(res_iteration_us(p.size, rpt));
-    if (rpt == 1 && cl <= 1) {
-      p.entries = 15;
-      p.slots = std::min((nsys + p.groups - 1) / p.groups, kManySlots);
-      if (p.slots > 1) take(many_iteration_us(p.size, p.slots));
+      if (xcd == G) break;
     }
   }
   return best >= 0;
@@ -724,14 +761,16 @@ hipError_t resident_sweep_launch(const ResSweepPlan& plan, ResSweepArgs args, hi
   if (plan.entries == EE && plan.rpt == PP) kern = (const void*)k_res_sweep<EE, EL, PP, 512>;
   HK_RES(8, 0, 1) HK_RES(8, 2, 2) HK_RES(15, 0, 1) HK_RES(15, 6, 2) HK_RES(27, 13, 1)
 #undef HK_RES
-  if (plan.slots > 1) kern = resident_many_kernel(plan.entries, plan.slots);
+  if (plan.slots > 1) kern = resident_many_kernel(plan);
   args.src.rows = plan.rows;
   args.src.stride = plan.area * plan.groups;
   args.size = plan.size;
   args.slots = plan.slots;
   args.area = plan.area;
   args.wide = args.src.gs.words + (size_t)plan.groups * kSumSets * kSumSetWords;
-  return res_coop_launch(kern, plan.size * plan.groups, args, s);
+  args.span = plan.span;
+  args.groups = plan.groups;
+  return res_coop_launch(kern, plan.grid, args, s);
 }
 
 template <class R> static const void* res_kernel(const ResShape& sh, int method) {
@@ -762,19 +801,21 @@ hipError_t resident_launch_kernel(const void* kern, const ResShape& sh, void** k
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, sh.threads, 0);
   if (e != hipSuccess) return e;
-  if (!coop || sh.grid > per * cus || sh.grid > kSumBlocks || sh.rows > sh.rpt * sh.threads)
+  const int grid = sh.packed ? sh.grid * kXcds : sh.grid;
+  if (!coop || grid > per * cus || sh.grid > kSumBlocks || sh.rows > sh.rpt * sh.threads)
     return hipErrorInvalidConfiguration;
   gs->words = static_cast<unsigned long long*>(scratch);
   gs->abort = resident_abort(scratch);
   gs->spin_limit = barrier_spin_limit();
   e = resident_reset(gs->words, kResWords + kResMany, gs->abort, s);
   if (e != hipSuccess) return e;
-  return hipLaunchCooperativeKernel(kern, dim3(sh.grid), dim3(sh.threads), kargs, 0, s);
+  return hipLaunchCooperativeKernel(kern, dim3(grid), dim3(sh.threads), kargs, 0, s);
 }
 
 template <class R>
 hipError_t resident_launch(const ResShape& sh, int method, ResArgs<R> args, void* scratch, hipStream_t s) {
   args.rows = sh.rows;
+  args.packed = sh.packed;
   void* kargs[] = {&args};
   return resident_launch_kernel(res_kernel<R>(sh, method), sh, kargs, &args.gs, scratch, s);
 }

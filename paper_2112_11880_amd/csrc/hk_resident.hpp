@@ -26,6 +26,7 @@ constexpr int kSweepLanes = 64;  // columns of a sweep's right-hand sides
 template <class R> struct ResArgs {
   using V = cplx<R>;
   int n, rows;             // rows per workgroup: a multiple of 64
+  int packed;              // the launch has kXcds times the workgroups: see ResPlace
   const int* rowptr;
   const int* col;
   const V* val;
@@ -177,12 +178,27 @@ template <int NT> struct ResLds {
   double sums[kSumWords * (NT / kWave + 4)];
 };
 
+// This workgroup's number of the `size` that solve a system: in the sums, and
+// (at) among the rows.  A packed launch has kXcds times as many, of which every
+// kXcds-th works: workgroups go to the XCDs in turn, so these share one, and with
+// it the L2 that they publish to (same_xcd makes sure).
+struct ResPlace {
+  int size, rank, at;
+  bool idle;
+  __device__ __forceinline__ explicit ResPlace(int packed) {
+    idle = packed && blockIdx.x % kXcds != 0;
+    size = packed ? gridDim.x / kXcds : gridDim.x;
+    rank = packed ? blockIdx.x / kXcds : blockIdx.x;
+    at = packed ? rank : xcd_block(blockIdx.x, gridDim.x);
+  }
+};
+
 // The row this thread works on as its i-th, and whether there is one.
 template <int RPT, int NT> struct ResMap {
   int r0, rend;
   int shift = 0;  // row r is element r + shift of the published vectors
-  __device__ __forceinline__ ResMap(int n, int rows) {
-    r0 = xcd_block(blockIdx.x, gridDim.x) * rows;
+  __device__ __forceinline__ ResMap(int n, int rows, int at) {
+    r0 = at * rows;
     rend = min(r0 + rows, n);
   }
   __device__ __forceinline__ ResMap(int from, int to, int end, int sh) : r0(from), rend(min(to, end)), shift(sh) {}
@@ -280,14 +296,26 @@ struct ResSweepArgs {
   const int* order;
   int* next;                   // the queue's front, `groups` at launch
   int nsys, size, slots;       // slots: systems a group works on at a time
+  int span, groups;            // groups lie within `span` workgroups in XCD order
   long long area;              // elements of a published vector of one system
   double2* own;                // slots > 1: what the slots keep per row
   unsigned long long* wide;    // and the words of group_sum_wide, all kSumEmpty at launch
   double2* X;
   ResBatchEnd* end;
 };
+// The group of this workgroup and its rank there.
+struct ResGroup {
+  int group, rank;
+  bool idle;
+  __device__ __forceinline__ explicit ResGroup(const ResSweepArgs& B) {
+    const int l = xcd_block(blockIdx.x, gridDim.x), per = B.span / B.size, i = l % B.span;
+    group = l / B.span * per + i / B.size;
+    rank = i % B.size;
+    idle = i / B.size >= per || group >= B.groups;
+  }
+};
 struct ResSweepPlan {
-  int entries = 0, rpt = 0, rows = 0, size = 0, groups = 0, slots = 1;
+  int entries = 0, rpt = 0, rows = 0, size = 0, groups = 0, slots = 1, grid = 0, span = 0;
   int64_t area = 0;
   // elements of the published vectors and of the slots' own ones; barrier words
   size_t pub() const { return (size_t)area * groups * (slots > 1 ? (2 * kRing + 1) * slots : 3 * kRing); }
@@ -297,7 +325,7 @@ struct ResSweepPlan {
 constexpr int kManySlots = 6;  // what registers and LDS take
 // hk_resident_sweep.hip: the kernel for `slots` > 1, the words of a group's
 // group_sum_wide
-const void* resident_many_kernel(int entries, int slots);
+const void* resident_many_kernel(const ResSweepPlan& plan);
 size_t resident_many_words(int slots);
 bool resident_sweep_plan(int device, int64_t n, int64_t nnz, int max_row, int nsys, ResSweepPlan* plan);
 hipError_t resident_sweep_launch(const ResSweepPlan& plan, ResSweepArgs args, hipStream_t s);

@@ -89,13 +89,19 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
   auto pub = [&](int i, unsigned c) { return A.pub + (kRing * i + (int)(c & (kRing - 1))) * A.stride; };
   if (*A.flag) return;
   const int ell = L.ell, lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
-  const ResMap<RPT, NT> m(A.n, A.rows);
+  const ResPlace at_place(A.packed);
+  if (at_place.idle) return;
+  const int size = at_place.size, rank = at_place.rank;
+  const ResMap<RPT, NT> m(A.n, A.rows, at_place.at);
+  GridSum gs = A.gs;
+  gs.local = 0;
   ResRows<V, E, EL, RPT, NT> M;
   M.lv = s_lv;
   V r0[RPT], u0[RPT], u1[RPT], un[RPT], rn[RPT];
   unsigned epoch = 0, many_calls = 0;
   unsigned np = 0;  // number of the newest r and u
-  double sum2[2] = {0, 0};
+  double sum2[4] = {0, 0, 0, 0};
+  same_xcd_sums(sum2[2], sum2[3]);
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
     const int row = m.row(i), l = i * NT + threadIdx.x;
@@ -106,8 +112,8 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
       bi = A.b[row];
       ri = A.x0 ? A.r0[row] : bi;
       if (A.x0) yi = cdiv(A.x0[row], A.dinv[row]);
-      publish(pub(0, 0), m.pub(i), ri);
-      publish(pub(1, 0), m.pub(i), czero<V>());
+      publish(gs, pub(0, 0), m.pub(i), ri);
+      publish(gs, pub(1, 0), m.pub(i), czero<V>());
     }
     r0[i] = ri;
     u0[i] = u1[i] = un[i] = rn[i] = czero<V>();
@@ -116,8 +122,9 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
     sum2[0] += nrm2d(bi);
     sum2[1] += nrm2d(ri);
   }
-  if (grid_sum<2, NT>(A.gs, epoch, true, sum2, lds.sums)) return;
-  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  if (group_sum<4, NT>(gs, size, rank, epoch, true, sum2, lds.sums)) return;
+  if (NT == 256) gs.local = same_xcd(size, sum2[2], sum2[3]);
+  const bool first = rank == 0 && threadIdx.x == 0;
   const double bb = uni(sum2[0]), theta2 = uni(A.tol * A.tol * bb);
   double rr = uni(sum2[1]);
   V rho = make_double2(1, 0), alpha = czero<V>(), omega = make_double2(1, 0), beta = czero<V>();
@@ -167,11 +174,11 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
             i, [&](int, unsigned c) { return Pair<V>{at(pr, c), at(pu, c)}; },
             [&](int, const Pair<V>& x) { return cfnma(beta, x.v, x.u); });
         if (m.has(i)) {
-          publish(pu2, m.pub(i), un[i]);
+          publish(gs, pu2, m.pub(i), un[i]);
           dotc_acc(s_rt[i * NT + threadIdx.x], un[i], sg[0], sg[1]);
         }
       }
-      if (grid_sum<2, NT>(A.gs, epoch, false, sg, lds.sums)) return;
+      if (group_sum<2, NT>(gs, size, rank, epoch, false, sg, lds.sums)) return;
       const V gam = uni(make_double2(sg[0], sg[1]));
       if (!cfinite(gam)) {
         status = HK_NONFINITE;
@@ -196,7 +203,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
             i, [&](int, unsigned c) { return Pair<V>{at(pr, c), at(static_cast<const V*>(pu2), c)}; },
             [&](int, const Pair<V>& x) { return cfnma(alpha, x.v, x.u); });
         if (m.has(i)) {
-          if (j + 1 < ell) publish(pr2, m.pub(i), rn[i]);
+          if (j + 1 < ell) publish(gs, pr2, m.pub(i), rn[i]);
           rs[0] += nrm2d(r0[i]);
           dotc_acc(s_rt[l], rn[i], rs[1], rs[2]);
         }
@@ -205,7 +212,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
         sum2[0] = rs[0];
         break;
       }
-      if (grid_sum<3, NT>(A.gs, epoch, ((np + 1) & 1) == 0, rs, lds.sums)) return;
+      if (group_sum<3, NT>(gs, size, rank, epoch, ((np + 1) & 1) == 0, rs, lds.sums)) return;
       ++np;
       rr = uni(rs[0]);
       stop_r();
@@ -302,7 +309,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
       }
     }
     put(2 * nz, sum2[0]);
-    if (grid_sum_many<NT>(A.gs, L.many, many_calls, 2 * nz + 1, s_many, s_tot)) return;
+    if (grid_sum_many<NT>(gs, size, rank, L.many, many_calls, 2 * nz + 1, s_many, s_tot)) return;
     rr = uni(s_tot[2 * nz]);
     stop_r();
     if (status != S_RUN) break;
@@ -348,13 +355,13 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
       r0[i] = r;
       u0[i] = u;
       if (m.has(i)) {
-        publish(pub(0, np + 2), m.pub(i), r);
-        publish(pub(1, np + 2), m.pub(i), u);
+        publish(gs, pub(0, np + 2), m.pub(i), r);
+        publish(gs, pub(1, np + 2), m.pub(i), u);
         mr[0] += nrm2d(r);
         dotc_acc(s_rt[l], r, mr[1], mr[2]);
       }
     }
-    if (grid_sum<3, NT>(A.gs, epoch, true, mr, lds.sums)) return;
+    if (group_sum<3, NT>(gs, size, rank, epoch, true, mr, lds.sums)) return;
     np += 2;
     rr = uni(mr[0]);
     done = k;
@@ -388,6 +395,7 @@ hipError_t resident_l_launch(const ResShape& sh, ResLArgs args, void* scratch, h
   HK_RES(27, 13, 1, 256) HK_RES(27, 13, 1, 512)
 #undef HK_RES
   args.base.rows = sh.rows;
+  args.base.packed = sh.packed;
   args.many = resident_many(scratch);
   void* kargs[] = {&args};
   return resident_launch_kernel(kern, sh, kargs, &args.base.gs, scratch, s);

@@ -39,7 +39,7 @@ template <int G> struct MultiLds {
   unsigned run, half;  // slots that iterate; that end with y += alpha p
 };
 
-template <int E, int G, int NT>
+template <int E, int G, int NT, bool LOC>
 __global__ __launch_bounds__(NT) void k_res_sweep_many(ResSweepArgs B) {
   using V = double2;
   constexpr int W = NT / kWave, NP = G <= 4 ? 8 : 16;  // up to four sums per slot
@@ -47,12 +47,15 @@ __global__ __launch_bounds__(NT) void k_res_sweep_many(ResSweepArgs B) {
   __shared__ MultiLds<G> L;
   __shared__ double s_waves[4 * G * W], s_parts[2 * NP * W], s_sums[kSumWords * (W + 4)];
   const ResSweepSource& A = B.src;
-  const int l = xcd_block(blockIdx.x, gridDim.x), group = l / B.size, rank = l - group * B.size;
+  const ResGroup place(B);
+  if (place.idle) return;
+  const int group = place.group, rank = place.rank;
   const ResMap<1, NT> m(rank * A.rows, rank * A.rows + A.rows, A.n, 0);
   const bool has = m.has(0);
   const int row = m.row(0), slots = B.slots;
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave, tid = threadIdx.x;
   GridSum gs = A.gs;
+  gs.local = 0;
   gs.words += (size_t)group * kSumSets * kSumSetWords;
   unsigned long long* const wide = B.wide + (size_t)group * WideSum<NP>::kWords;
   unsigned epoch = 0, wepoch = 0;
@@ -147,12 +150,14 @@ __global__ __launch_bounds__(NT) void k_res_sweep_many(ResSweepArgs B) {
         if (has) {
           const V x = cmul(own(DINV, g), at_y(g));
           B.X[(size_t)row * kSweepLanes + L.sys[g]] = x;
-          publish(pubs + ((size_t)2 * kRing * slots + g) * B.area, fresh(at_row), x);
+          publish(gs, pubs + ((size_t)2 * kRing * slots + g) * B.area, fresh(at_row), x);
         }
       }
-      double from[1] = {0};
+      double from[3] = {0, 0, 0};
+      same_xcd_sums(from[1], from[2]);
       if (rank == 0 && tid == 0 && open) from[0] = (double)atomicAdd(B.next, __popc(open));
-      if (group_sum<1, NT>(gs, B.size, rank, epoch, true, from, s_sums)) return;
+      if (group_sum<3, NT>(gs, B.size, rank, epoch, true, from, s_sums)) return;
+      if (LOC) gs.local = same_xcd(B.size, from[1], from[2]);
       int q = __builtin_amdgcn_readfirstlane((int)from[0]);
       unsigned fresh_ones = 0;
       // two sums per slot: the residual of its last system, ||b||^2 of its next
@@ -230,7 +235,7 @@ __global__ __launch_bounds__(NT) void k_res_sweep_many(ResSweepArgs B) {
     for (int g = 0; g < G; ++g) {
       if (!(run >> g & 1)) continue;
       p[g] = cfma(L.beta[g], cfnma(L.omega[g], at_v(g), p[g]), r[g]);
-      if (has) publish(pub(0, turn, g), fresh(at_row), cmul(m1[g], p[g]));
+      if (has) publish(gs, pub(0, turn, g), fresh(at_row), cmul(m1[g], p[g]));
     }
     // both vectors' places were last read before the barriers of the turn before
     {
@@ -276,7 +281,7 @@ __global__ __launch_bounds__(NT) void k_res_sweep_many(ResSweepArgs B) {
     for (int g = 0; g < G; ++g) {
       if (!(run >> g & 1)) continue;
       r[g] = cfnma(L.alpha[g], at_v(g), r[g]);
-      if (has) publish(pub(1, turn, g), fresh(at_row), cmul(m1[g], r[g]));
+      if (has) publish(gs, pub(1, turn, g), fresh(at_row), cmul(m1[g], r[g]));
     }
     {
       double none[1] = {0};
@@ -376,9 +381,12 @@ __global__ __launch_bounds__(NT) void k_res_sweep_many(ResSweepArgs B) {
   }
 }
 
-const void* resident_many_kernel(int entries, int slots) {
-  if (entries != 15) return nullptr;
-  return slots <= 3 ? (const void*)k_res_sweep_many<15, 3, 512> : (const void*)k_res_sweep_many<15, 6, 512>;
+const void* resident_many_kernel(const ResSweepPlan& p) {
+  if (p.entries != 15) return nullptr;
+  const bool local = p.span < p.grid;
+  if (p.slots <= 3)
+    return local ? (const void*)k_res_sweep_many<15, 3, 512, true> : (const void*)k_res_sweep_many<15, 3, 512, false>;
+  return local ? (const void*)k_res_sweep_many<15, 6, 512, true> : (const void*)k_res_sweep_many<15, 6, 512, false>;
 }
 size_t resident_many_words(int slots) { return slots <= 3 ? WideSum<8>::kWords : WideSum<16>::kWords; }
 
