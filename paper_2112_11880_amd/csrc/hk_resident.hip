@@ -616,6 +616,7 @@ bool resident_batch_plan(const hk_csr_s* A, int nsys, const int64_t* row_off, Re
     ResBatchPlan p;
     p.entries = kResEntries[cl];
     p.rpt = rpt;
+    p.grid = G;
     p.sys.resize(nsys);
     std::vector<double> free_at(G, 0.0);
     std::vector<std::vector<std::pair<int, int>>> jobs(G);
