@@ -245,7 +245,12 @@ typedef struct {
  * info->shape reports the fused products' launch shape {lanes per row (64:
  * row blocks), rows per lane group or per wave, waves per workgroup, paired
  * layout}, and info->shape_tuned whether the solver timed it; a cooperative
- * solve reports {1, rows per thread, waves per workgroup, 0}.
+ * solve reports {1, rows per thread, waves per workgroup, 0}.  Where 64 rows in
+ * a row have their entries at few distances col - row (meshes; at most 1.1
+ * values kept per entry), the products of the other solves read the solver's
+ * copy of the matrix in slices of 64 rows, {2, 64, waves per workgroup, 0}; the
+ * handle keeps the distances from the first such solve on.  A handle whose
+ * launch shape was set keeps to that shape.
  * Returns info->status (>= 0) or an error.  x always holds the last iterate.
  */
 int hk_krylov_solve(hk_csr A, const void* d_b, void* d_x, const hk_solve_opts* opts,

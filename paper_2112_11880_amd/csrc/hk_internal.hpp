@@ -52,6 +52,16 @@ struct SpmvPlan {
   int pairs = 0;    // row-block fused solver kernels: paired-entry layout (16-bit column stream only)
 };
 
+// The pattern in slices (hk_slice.hpp): slice k has the distances off[ptr[k]] ..
+// off[ptr[k + 1]] (device); `values` in all.
+struct SliceStore {
+  bool tried = false;
+  int* ptr = nullptr;
+  int* off = nullptr;
+  int count = 0;
+  int64_t values = 0;
+};
+
 }  // namespace hk
 
 // The opaque matrix handle.
@@ -85,6 +95,8 @@ struct hk_csr_s {
   // workspace of the batched solve (device), kept like the solver's
   void* bws = nullptr;
   size_t bws_bytes = 0;
+  // for the solvers' products of systems that do not fit the registers
+  hk::SliceStore slices;
   // pinned host words the solver reads its status through
   int* pinned = nullptr;
 };

@@ -46,6 +46,7 @@
 #include "hk_internal.hpp"
 #include "hk_resident.hpp"
 #include "hk_solver.hpp"
+#include "hk_slice.hpp"
 #include "hk_spmv.hpp"
 
 namespace hk {
@@ -247,6 +248,42 @@ __global__ __launch_bounds__(NW * kWave) void k_spmv_dot_rb(int n, int ntiles, c
   }
   __syncthreads();
   block_sum<NV, double, NW>(part, reinterpret_cast<double*>(lds));
+  store_block_partials<NV>(part, partials);
+}
+
+// The same on slices: a wave per slice.
+template <int NW, class R, int DOT>
+__global__ __launch_bounds__(NW * kWave) void k_spmv_dot_sl(int n, int nslices, int ntiles, const int* __restrict__ ptr,
+                                                            const int* __restrict__ off,
+                                                            const cplx<R>* __restrict__ val,
+                                                            const cplx<R>* __restrict__ x, cplx<R>* __restrict__ y,
+                                                            const cplx<R>* __restrict__ w,
+                                                            const SolveState* __restrict__ st, double* partials) {
+  using V = cplx<R>;
+  constexpr int NV = DOT == 1 ? 2 : 4;
+  __shared__ double lds[NV * NW];
+  if (st->status != S_RUN) return;
+  double part[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) part[k] = 0;
+  for (int tb = blockIdx.x; tb < ntiles; tb += gridDim.x) {
+    const int slice = __builtin_amdgcn_readfirstlane(tile_of(tb, ntiles) * NW + (int)threadIdx.x / kWave);
+    if (slice >= nslices) continue;
+    const int r = slice * kWave + (int)(threadIdx.x & (kWave - 1));
+    const V wr = w[r < n ? r : n - 1];
+    const V acc = slice_row<V>(slice, n, ptr, off, val, x);
+    if (r < n) {
+      y[r] = acc;
+      if (DOT == 1) {
+        dotc_acc(wr, acc, part[0], part[1]);
+      } else {
+        part[0] += nrm2d(acc);
+        dotc_acc(acc, wr, part[1], part[2]);
+        part[3] += nrm2d(wr);
+      }
+    }
+  }
+  block_sum<NV, double, NW>(part, lds);
   store_block_partials<NV>(part, partials);
 }
 
@@ -518,9 +555,12 @@ static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 // The workspace layout is written once, as a sequence of take(bytes) calls;
 // work_bytes runs it with a counting take, carve with one that hands out
 // addresses, so the size and the layout cannot disagree.
+// Values of Ahat: A's with one padding entry (paired-entry products), or slices.
+static size_t ahat_elements(const hk_csr_s* A) { return (size_t)std::max<int64_t>(A->nnz + 1, A->slices.values); }
+
 template <class R, class Take> static Work<R> layout(Take take, const hk_csr_s* A) {
   using V = cplx<R>;
-  const int64_t n = A->n, nnz = A->nnz;
+  const int64_t n = A->n;
   const bool res = resident_shape(A, sizeof(R) == 4 ? 1 : 0).entries != 0;
   Work<R> w;
   w.y = (V*)take(sizeof(V) * n);
@@ -533,7 +573,7 @@ template <class R, class Take> static Work<R> layout(Take take, const hk_csr_s* 
   w.dinv = (V*)take(sizeof(V) * n);
   w.u = (V*)take(sizeof(V) * n);
   w.d = (V*)take(sizeof(V) * n);
-  w.ahat = (V*)take(sizeof(V) * (nnz + 1));  // one padding entry (paired-entry products)
+  w.ahat = (V*)take(sizeof(V) * ahat_elements(A));
   w.partials = (double*)take(sizeof(double) * 4 * partial_slots(n));
   w.pub = (V*)take(res ? kResVecs * kRing * align_up(sizeof(V) * n) : 0);
   w.res = (void*)take(res ? resident_scratch_bytes() : 0);
@@ -566,11 +606,41 @@ static int ensure_ws(void** ws, size_t* have, size_t need, hipStream_t s) {
   return HK_OK;
 }
 
+static SpmvPlan slice_plan() {
+  SpmvPlan p;
+  p.L = kSliceL;
+  p.U = kWave;
+  p.nw = kSliceWaves;
+  return p;
+}
+
+// The fused products' shape where none was fixed or tuned: slices if the handle
+// has them, else its CSR shape.
+static SpmvPlan default_dot_plan(const hk_csr_s* A) {
+  if (A->slices.values > 0 && !A->plan_fixed) return slice_plan();
+  SpmvPlan p = A->plan;
+  p.nw = 0;
+  return p;
+}
+
+// Ahat = A D^-1 in the layout of plan p.
+template <class V>
+static hipError_t fill_ahat(const hk_csr_s* A, const SpmvPlan& p, const V* val, const V* dinv, V* ahat, hipStream_t s) {
+  if (p.L == kSliceL) return slices_fill<V>(A, val, dinv, ahat, s);
+  launch_scale_cols<V>(A->nnz, A->col, val, dinv, ahat, s);
+  return hipGetLastError();
+}
+
 // Tiles of the fused SpMV+dot launches for launch shape p, and for
 // row-block shapes the waves per workgroup: p.nw when set, else the fewest
 // of 2, 4, 8 that keep the tiles within kMaxGrid.
 static int dot_tiles(const hk_csr_s* A, const SpmvPlan& p, int* nw_out) {
   int nw = 0;
+  if (p.L == kSliceL) {
+    nw = p.nw;
+    if (nw_out) *nw_out = nw;
+    return (A->slices.count + nw - 1) / nw;
+  }
   int64_t tiles = spmv_tiles(A, p.L, p.U);
   if (p.L == kRowBlockL) {
     if (p.nw == 2 || p.nw == 4 || p.nw == 8) {
@@ -601,6 +671,18 @@ static hipError_t launch_spmv_dot(const hk_csr_s* A, const SpmvPlan& p, int dot,
   const int grid = dot_grid(A, p);
   const int L = p.L, U = p.U;
   const int n = (int)A->n;
+#define HK_SDSL_CASE(NWW)                                                                                       \
+  if (L == kSliceL && nw == NWW) {                                                                              \
+    if (dot == 1)                                                                                               \
+      hipLaunchKernelGGL((k_spmv_dot_sl<NWW, R, 1>), dim3(grid), dim3(NWW * kWave), 0, s, n, A->slices.count,   \
+                         ntiles, A->slices.ptr, A->slices.off, val, x, y, w, wk.st, wk.partials);               \
+    else                                                                                                        \
+      hipLaunchKernelGGL((k_spmv_dot_sl<NWW, R, 2>), dim3(grid), dim3(NWW * kWave), 0, s, n, A->slices.count,   \
+                         ntiles, A->slices.ptr, A->slices.off, val, x, y, w, wk.st, wk.partials);               \
+    return hipGetLastError();                                                                                   \
+  }
+  HK_SDSL_CASE(2) HK_SDSL_CASE(4) HK_SDSL_CASE(8)
+#undef HK_SDSL_CASE
 #define HK_SD_CASE(LL, UU)                                                                          \
   if (L == LL && U == UU) {                                                                         \
     if (dot == 1)                                                                                   \
@@ -676,6 +758,14 @@ static int tune_dot(const hk_csr_s* A, const Work<R>& wk, SpmvPlan* out, hipStre
           if ((A->n + (int64_t)nw * U - 1) / ((int64_t)nw * U) <= kMaxGrid || nw == 8) cands.push_back(p);
         }
   }
+  if (A->slices.values > 0)
+    for (int grid : {0, 2048})
+      for (int nw : {2, 4, 8}) {
+        SpmvPlan p = slice_plan();
+        p.nw = nw;
+        p.grid = grid;
+        cands.push_back(p);
+      }
   SolveState run{};
   run.status = S_RUN;
   HK_HIP(hipMemcpyAsync(wk.st, &run, sizeof(run), hipMemcpyHostToDevice, s));
@@ -931,18 +1021,16 @@ static int bicgstab(hk_csr_s* A, const cplx<R>* val, const cplx<R>* b, cplx<R>* 
     const int rc = resident_solve<R>(A, HK_BICGSTAB, val, b, x, o, wk, info, &ran, s);
     if (rc != HK_OK || ran) return rc;
   }
-  launch_scale_cols<V>(A->nnz, A->col, val, wk.dinv, wk.ahat, s);
-  HK_CHECK_LAUNCH();
   // fused-product shape: one fixed by hk_csr_set_solver_plan or tuned (on
   // the first solve of a tuned handle), else the handle's CSR shape
-  SpmvPlan dp = A->plan;
-  dp.nw = 0;
+  SpmvPlan dp = default_dot_plan(A);
   SpmvPlan& cached = A->dot_plan[sizeof(R) == 4 ? 1 : 0];
   if (!cached.tuned && A->plan.tuned) {
     int rc = tune_dot<R>(A, wk, &cached, s);
     if (rc != HK_OK) return rc;
   }
   if (cached.tuned) dp = cached;
+  HK_HIP(fill_ahat<V>(A, dp, val, wk.dinv, wk.ahat, s));
   const int gs = dot_grid(A, dp);
   SolveState init{};
   init.history = o.d_history;
@@ -1074,6 +1162,32 @@ __global__ __launch_bounds__(NW * kWave) void k_fused_rb(int n, int ntiles, cons
   store_block_partials<NV>(part, partials);
 }
 
+template <class E, int NW>
+__global__ __launch_bounds__(NW * kWave) void k_fused_sl(int n, int nslices, int ntiles, const int* __restrict__ ptr,
+                                                         const int* __restrict__ off,
+                                                         const typename E::V* __restrict__ val,
+                                                         const typename E::V* __restrict__ x, E e,
+                                                         const SolveState* __restrict__ st, double* partials) {
+  using V = typename E::V;
+  constexpr int NV = E::NV;
+  __shared__ double lds[NV * NW];
+  if (!E::active(st)) return;
+  const typename E::Sc sc = E::scalars(st);
+  double part[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) part[k] = 0;
+  for (int tb = blockIdx.x; tb < ntiles; tb += gridDim.x) {
+    const int slice = __builtin_amdgcn_readfirstlane(tile_of(tb, ntiles) * NW + (int)threadIdx.x / kWave);
+    if (slice >= nslices) continue;
+    const int r = slice * kWave + (int)(threadIdx.x & (kWave - 1));
+    const typename E::Pre pre = e.load(r < n ? r : n - 1);
+    const V acc = slice_row<V>(slice, n, ptr, off, val, x);
+    if (r < n) e.apply(r, pre, acc, sc, part);
+  }
+  block_sum<NV, double, NW>(part, lds);
+  store_block_partials<NV>(part, partials);
+}
+
 template <class E>
 static hipError_t launch_fused(const hk_csr_s* A, const SpmvPlan& p, const typename E::V* val,
                                const typename E::V* x, const E& e, const SolveState* st, double* partials,
@@ -1082,6 +1196,14 @@ static hipError_t launch_fused(const hk_csr_s* A, const SpmvPlan& p, const typen
   const int ntiles = dot_tiles(A, p, &nw);
   const int grid = dot_grid(A, p);
   const int n = (int)A->n;
+#define HK_FSL(NWW)                                                                                         \
+  if (p.L == kSliceL && nw == NWW) {                                                                        \
+    hipLaunchKernelGGL((k_fused_sl<E, NWW>), dim3(grid), dim3(NWW * kWave), 0, s, n, A->slices.count, ntiles, \
+                       A->slices.ptr, A->slices.off, val, x, e, st, partials);                              \
+    return hipGetLastError();                                                                               \
+  }
+  HK_FSL(2) HK_FSL(4) HK_FSL(8)
+#undef HK_FSL
 #define HK_FLG(LL, UU)                                                                               \
   if (p.L == LL && p.U == UU) {                                                                      \
     hipLaunchKernelGGL((k_fused_lg<E, LL, UU>), dim3(grid), dim3(kBlock), 0, s, n, ntiles, A->rowptr, \
@@ -1361,16 +1483,14 @@ static int tfqmr(hk_csr_s* A, const double2* val, const double2* b, double2* x, 
     const int rc = resident_solve<R>(A, HK_TFQMR, val, b, x, o, wk, info, &ran, s);
     if (rc != HK_OK || ran) return rc;
   }
-  launch_scale_cols<V>(A->nnz, A->col, val, wk.dinv, wk.ahat, s);
-  HK_CHECK_LAUNCH();
-  SpmvPlan dp = A->plan;
-  dp.nw = 0;
+  SpmvPlan dp = default_dot_plan(A);
   SpmvPlan& cached = A->dot_plan[0];
   if (!cached.tuned && A->plan.tuned) {
     int rc = tune_dot<R>(A, wk, &cached, s);
     if (rc != HK_OK) return rc;
   }
   if (cached.tuned) dp = cached;
+  HK_HIP(fill_ahat<V>(A, dp, val, wk.dinv, wk.ahat, s));
   const int gs = dot_grid(A, dp);
   SolveState init{};
   init.history = o.d_history;
@@ -1463,7 +1583,7 @@ template <class R> static size_t bl_partial_doubles(int64_t n) {
 // One layout for sizing and carving, as for the BiCGStab/TFQMR workspace.
 template <class R, class Take> static BlWork<R> bl_layout(Take take, const hk_csr_s* A, int ell) {
   using V = cplx<R>;
-  const int64_t n = A->n, nnz = A->nnz;
+  const int64_t n = A->n;
   const bool res = resident_shape(A, 0).entries != 0;
   BlWork<R> w{};
   w.y = (V*)take(sizeof(V) * n);
@@ -1475,7 +1595,7 @@ template <class R, class Take> static BlWork<R> bl_layout(Take take, const hk_cs
   }
   w.pub = (V*)take(res ? 2 * kRing * align_up(sizeof(V) * n) : 0);
   w.res = (void*)take(res ? resident_scratch_bytes() : 0);
-  w.ahat = (V*)take(sizeof(V) * (nnz + 1));  // one padding entry (paired-entry products)
+  w.ahat = (V*)take(sizeof(V) * ahat_elements(A));
   w.partials = (double*)take(sizeof(double) * bl_partial_doubles<R>(n));
   w.st = (SolveState*)take(sizeof(SolveState));
   w.flag = (int*)take(64);
@@ -1874,10 +1994,7 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
     });
     if (rc != HK_OK || ran) return rc;
   }
-  launch_scale_cols<V>(A->nnz, A->col, val, wk.dinv, wk.ahat, s);
-  HK_CHECK_LAUNCH();
-  SpmvPlan dp = A->plan;
-  dp.nw = 0;
+  SpmvPlan dp = default_dot_plan(A);
   SpmvPlan& cached = A->dot_plan[0];
   if (!cached.tuned && A->plan.tuned) {
     // the workspace vectors serve as tuning operands before the solve starts
@@ -1892,6 +2009,7 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
     if (rc != HK_OK) return rc;
   }
   if (cached.tuned) dp = cached;
+  HK_HIP(fill_ahat<V>(A, dp, val, wk.dinv, wk.ahat, s));
   const int gs = dot_grid(A, dp);
   SolveState init{};
   init.history = o.d_history;
@@ -1973,13 +2091,19 @@ static int ensure_pinned(hk_csr_s* A) {
 // workgroup, paired layout} of precision slot prec (0 complex128, 1
 // complex64), or the handle's CSR shape when none was fixed or tuned.
 static void report_shape(const hk_csr_s* A, int prec, hk_solve_info* info) {
-  const SpmvPlan& d = A->dot_plan[prec].tuned ? A->dot_plan[prec] : A->plan;
+  const SpmvPlan d = A->dot_plan[prec].tuned ? A->dot_plan[prec] : default_dot_plan(A);
   info->shape[0] = d.L;
   info->shape[1] = d.U;
   info->shape[2] = d.nw;
   info->shape[3] = d.pairs;
   info->shape_tuned = d.tuned == 1 ? 1 : 0;
   info->pad = 0;
+}
+
+// Slices for a system whose solve will stream its matrix.
+static int want_slices(hk_csr_s* A, int prec, hipStream_t s) {
+  if (A->plan_fixed || resident_shape(A, prec).entries != 0) return HK_OK;
+  return slices_prepare(A, s);
 }
 
 static int check_opts(const hk_solve_opts* o, const char* who) {
@@ -2009,6 +2133,8 @@ extern "C" int hk_krylov_solve(hk_csr A, const void* d_b, void* d_x, const hk_so
   rc = ensure_pinned(A);
   if (rc != HK_OK) return rc;
   for (int k = 0; k < 4; ++k) info->shape[k] = 0;  // a resident solve reports its own
+  rc = want_slices(A, A->dtype == HK_C64 ? 1 : 0, s);
+  if (rc != HK_OK) return rc;
   if (A->dtype == HK_C64) {
     if (opts->method != HK_BICGSTAB) HK_FAIL(HK_EINVAL, "hk_krylov_solve: complex64 solves use BiCGStab only");
     rc = ensure_ws(&A->ws32, &A->ws32_bytes, work_bytes<float>(A), s);
@@ -2049,6 +2175,8 @@ extern "C" int hk_krylov_solve_mixed(hk_csr A, const void* d_b, void* d_x, doubl
   // complex64 workspace + r (c128) + r32, d32 (c64) + norm scratch
   const size_t extra = align_up(16 * n) + 2 * align_up(8 * n) + align_up(64);
   rc = ensure_pinned(A);
+  if (rc != HK_OK) return rc;
+  rc = want_slices(A, 1, s);
   if (rc != HK_OK) return rc;
   rc = ensure_ws(&A->ws32, &A->ws32_bytes, work_bytes<float>(A) + extra, s);
   if (rc != HK_OK) return rc;

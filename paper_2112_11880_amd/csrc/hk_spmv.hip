@@ -369,7 +369,7 @@ extern "C" int hk_csr_create(hk_csr* out, int64_t n, int64_t nnz, const int32_t*
 extern "C" int hk_csr_destroy(hk_csr A) {
   if (!A) return HK_OK;
   int rc = HK_OK;
-  if (A->ws || A->ws32 || A->val32 || A->col16 || A->bws) {
+  if (A->ws || A->ws32 || A->val32 || A->col16 || A->bws || A->slices.ptr) {
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(A->device);
@@ -377,6 +377,8 @@ extern "C" int hk_csr_destroy(hk_csr A) {
     if (A->ws) (void)hipFree(A->ws);
     if (A->ws32) (void)hipFree(A->ws32);
     if (A->bws) (void)hipFree(A->bws);
+    if (A->slices.ptr) (void)hipFree(A->slices.ptr);
+    if (A->slices.off) (void)hipFree(A->slices.off);
     if (A->val32) (void)hipFree(A->val32);
     if (A->col16) (void)hipFree(A->col16);
     (void)hipSetDevice(cur);

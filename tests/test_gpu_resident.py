@@ -250,6 +250,47 @@ def test_resident_sweep(hk, oracle, n, row, nsys):
     assert torch.equal(torch.view_as_real(X), torch.view_as_real(X2))
 
 
+def banded(n, dist, seed):
+    """Rows with entries at the given distances (clipped at the ends), a few of them left out."""
+    rng = np.random.default_rng(seed)
+    d = np.array(sorted(set(dist) | {0}))
+    col = np.arange(n)[:, None] + d[None, :]
+    keep = (col >= 0) & (col < n) & ((rng.random(col.shape) < 0.99) | (d == 0)[None, :])
+    rowptr = np.zeros(n + 1, dtype=np.int32)
+    rowptr[1:] = np.cumsum(keep.sum(1))
+    cols = col[keep].astype(np.int32)
+    val = crandn(rng, cols.shape[0]) / (4.0 * len(d))
+    val[cols == np.repeat(np.arange(n), keep.sum(1))] = 1.0 + 0.125 * rng.standard_normal(n)
+    return rowptr, cols, val, crandn(rng, n)
+
+
+@pytest.mark.parametrize("n,ndist", [(300007, 15), (262208, 15), (290000, 11), (150001, 27), (40000, 28), (64 * 500 + 1, 33)])
+@pytest.mark.parametrize("method", ["bicgstab", "tfqmr", "bicgstab_l", "c64"])
+def test_sliced_products(hk, oracle, n, ndist, method):
+    """Systems that do not fit the registers and have few distances col - row per 64 rows: the first
+    iterates with the sliced products, in a last slice of 1 to 64 rows, whole fives of distances and not."""
+    rng = np.random.default_rng(ndist)
+    rowptr, col, val, b = banded(n, [0, 1, -1, 70, -70] + list(rng.choice(np.r_[-3000:-100, 100:3000], ndist - 5, replace=False)), n)
+    print("[case] slices", n, ndist, method, flush=True)
+    its = 2 if method == "bicgstab_l" else 3
+    if method == "c64":
+        v32, b32 = val.astype(np.complex64), b.astype(np.complex64)
+        x, info = hk.krylov_solve(hk.CSR(dev(rowptr), dev(col), dev(v32)), dev(b32), tol=0.0, max_iter=its)
+        xo, oi = oracle.bicgstab_c64(rowptr, col, v32, b32, tol=0.0, maxit=its)
+        assert np.linalg.norm(x.cpu().numpy() - xo) <= 1e-5 * np.linalg.norm(xo)
+        assert info["shape"][0] == (2 if ndist > 27 else 1)
+        return
+    A = hk.CSR(dev(rowptr), dev(col), dev(val))
+    kw = {"ell": 2} if method == "bicgstab_l" else {}
+    xo, oi = getattr(oracle, method)(rowptr, col, val, b, tol=0.0, maxit=its, **kw)
+    x, info = hk.krylov_solve(A, dev(b), tol=0.0, max_iter=its, method=method, **kw)
+    assert info["shape"] == [2, 64, 4, 0] and info["iters"] == oi["iters"], info
+    assert np.linalg.norm(x.cpu().numpy() - xo) <= 1e-10 * np.linalg.norm(xo)
+    A.set_plan(64, 32)
+    y, info = hk.krylov_solve(A, dev(b), tol=0.0, max_iter=its, method=method, **kw)
+    assert info["shape"][0] == 64 and np.linalg.norm(y.cpu().numpy() - xo) <= 1e-10 * np.linalg.norm(xo)
+
+
 def test_resident_batch_and_sweep_are_taken(hk):
     """Without a shape given, the batch and the sweep take the resident launches: their sums run in
     another order than those of the launch in the shape reported, so some bits differ."""
