@@ -246,7 +246,7 @@ typedef struct {
  * row blocks), rows per lane group or per wave, waves per workgroup, paired
  * layout}, and info->shape_tuned whether the solver timed it; a cooperative
  * solve reports {1, rows per thread, waves per workgroup, 0}.  Where 64 rows in
- * a row have their entries at few distances col - row (meshes; at most 1.1
+ * a row have their entries at few distances col - row (meshes; at most 1.25
  * values kept per entry), the products of the other solves read the solver's
  * copy of the matrix in slices of 64 rows, {2, 64, waves per workgroup, 0}; the
  * handle keeps the distances from the first such solve on.  A handle whose

@@ -7,9 +7,11 @@
 namespace hk {
 
 // The slices read 16 bytes per value where the row blocks read 18 and the row
-// pointers: up to this many values per entry they are the fewer bytes (the box of
-// 192 x 96 x 96 cells has 1.03, one of 40 x 40 x 40 1.08).
-constexpr double kSliceMost = 1.1;
+// pointers, and go without the LDS: up to this many values per entry they were
+// faster throughout (a BiCGStab iteration, slices against row blocks: 1.03 values
+// per entry 257 and 290 us on 1.8M rows; flat boxes of 160 to 350 thousand rows with
+// 1.09 77 and 90, 1.17 71 and 84, 1.27 78.5 and 82.5).
+constexpr double kSliceMost = 1.25;
 constexpr int kSliceBlock = 4 * kWave;
 
 // The distances of one slice, ascending: f(number, distance, this lane's row has
