@@ -179,6 +179,9 @@ def bench_batched(hk, torch, np, dev, log, legs=("sweep", "uneven"), plain=True,
 PHASES = ("p_update", "v_product", "s_update", "t_product", "xr_update")
 
 
+PHASE_ITERS = 400  # iterations of the calls that record barrier times
+
+
 def barrier_phases(stamps, iters_all, nbytes, np):
     """Per-phase time of a batched solve's iterations while every system
     runs (iterations 2 .. the smallest iteration count), from the barrier
@@ -232,14 +235,17 @@ def _bench_sweep(hk, torch, np, dev, log, plain, max_iter, shape):
     hk.sweep_solve(rp, cl, Kd, Md, kap, B, tol=1e-8, max_iter=4, shape=shape)
     torch.cuda.synchronize()
     tune_sweep = time.perf_counter() - ts
-    stamps = torch.zeros(8 * (max_iter + 1), dtype=torch.float64, device=dev)
-    torch.cuda.synchronize()
     ts = time.perf_counter()
-    X, infos = hk.sweep_solve(rp, cl, Kd, Md, kap, B, tol=1e-8, max_iter=max_iter, shape=shape, stamps=stamps)
+    X, infos = hk.sweep_solve(rp, cl, Kd, Md, kap, B, tol=1e-8, max_iter=max_iter, shape=shape)
     torch.cuda.synchronize()
     t_sweep = time.perf_counter() - ts
     its = [i["iters"] for i in infos]
-    phases = sweep_phases(stamps.cpu().numpy(), min(its), int(c["n"]), int(c["col"].shape[0]), np)
+    # barrier times are those of the interleaved launch, which a call that
+    # asks for them takes
+    pk = min(max_iter, PHASE_ITERS)
+    stamps = torch.zeros(8 * (pk + 1), dtype=torch.float64, device=dev)
+    _, pinf = hk.sweep_solve(rp, cl, Kd, Md, kap, B, tol=1e-8, max_iter=pk, shape=shape, stamps=stamps)
+    phases = sweep_phases(stamps.cpu().numpy(), min(i["iters"] for i in pinf), int(c["n"]), int(c["col"].shape[0]), np)
     log(f"sweep 64 systems: {t_sweep:.3f} s, iters {min(its)}..{max(its)}, "
         f"worst relres {max(i['relres_true'] for i in infos):.2e}")
     g = torch.from_numpy(c["g"]).to(dev)
@@ -291,12 +297,15 @@ def _bench_uneven(hk, torch, np, dev, log, plain, max_iter, shape):
     hk.blockdiag_solve(A, offs, b, tol=1e-8, max_iter=4, shape=shape)
     torch.cuda.synchronize()
     tune_bd = time.perf_counter() - ts
-    stamps = torch.zeros(8 * (max_iter + 1), dtype=torch.float64, device=dev)
     ts = time.perf_counter()
-    _, infos = hk.blockdiag_solve(A, offs, b, tol=1e-8, max_iter=max_iter, shape=shape, stamps=stamps)
+    _, infos = hk.blockdiag_solve(A, offs, b, tol=1e-8, max_iter=max_iter, shape=shape)
     torch.cuda.synchronize()
     t_bd = time.perf_counter() - ts
     its = [i["iters"] for i in infos]
+    # (as in the sweep) the barrier times of the tiled launch
+    pk = min(max_iter, PHASE_ITERS)
+    stamps = torch.zeros(8 * (pk + 1), dtype=torch.float64, device=dev)
+    _, pinf = hk.blockdiag_solve(A, offs, b, tol=1e-8, max_iter=pk, shape=shape, stamps=stamps)
     log(f"uneven batch 32 systems: {t_bd:.3f} s, iters {min(its)}..{max(its)}")
     t_seq, it_seq = 0.0, []
     for sy in (systems if plain else ()):
@@ -312,7 +321,7 @@ def _bench_uneven(hk, torch, np, dev, log, plain, max_iter, shape):
         it_seq.append(inf["iters"])
     if plain:
         log(f"32 plain solves: {t_seq:.3f} s")
-    phases = uneven_phases(stamps.cpu().numpy(), min(its), offs[-1], nnz, np)
+    phases = uneven_phases(stamps.cpu().numpy(), min(i["iters"] for i in pinf), offs[-1], nnz, np)
     res["solve_uneven"] = {"systems": 32, "rows": offs[-1], "time_s": round(t_bd, 4), "phases": phases,
                            "shape": infos[0]["shape"], "shape_tuned": infos[0]["shape_tuned"],
                            "tune_s": round(tune_bd, 4), "iters_min": min(its), "iters_max": max(its),
