@@ -4,7 +4,7 @@
 //
 // As separate kernels a BiCG step on 232,897 rows took 75 us: two products of
 // 17.8, the passes over the r_i and u_i of 10.5 and 8.6, finalize launches of 4.7
-// each.  Here it takes 36 us: two barriers of 4, two gathers of two vectors for
+// each.  Here it takes 34 us: two barriers of 4, two gathers of two vectors for
 // two rows per thread of 6-7, the pass over the r_i and u_i.  With j the step,
 //   u_j = r_j - beta u_j:      u_{j+1} = Ahat u_j gathers the last r and u products
 //   r_j - alpha u_{j+1}:       r_{j+1} = Ahat r_j gathers the last r and the new u
@@ -86,6 +86,14 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
   // barrier, and where a cycle ends
   auto priv_r = [&](int q) { return L.vecs + 2 * q * A.stride; };
   auto priv_u = [&](int q) { return L.vecs + (2 * q + 1) * A.stride; };
+  // a scalar base and a 32-bit offset, formed anew: 64-bit addresses by q are kept
+  // and spilled (315 -> 238 and 46 -> 3 registers spilled with two and one rows of 15
+  // entries per thread, a cycle of 16 products 296 -> 274 us on 232,897 rows, 135 ->
+  // 123 on 117,649)
+  auto get_priv = [](const V* base, int row) { return at(base, fresh((unsigned)row * (unsigned)sizeof(V))); };
+  auto put_priv = [](V* base, int row, V v) {
+    *reinterpret_cast<V*>(reinterpret_cast<char*>(base) + fresh((unsigned)row * (unsigned)sizeof(V))) = v;
+  };
   auto pub = [&](int i, unsigned c) { return A.pub + (kRing * i + (int)(c & (kRing - 1))) * A.stride; };
   if (*A.flag) return;
   const int ell = L.ell, lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
@@ -241,24 +249,24 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
 #pragma unroll
           for (int s = 0; s < 4; ++s) {
             const int q = min(q0 + s, j);
-            rq[s] = priv_r(q)[row];
-            uq[s] = priv_u(q)[row];
+            rq[s] = get_priv(priv_r(q), row);
+            uq[s] = get_priv(priv_u(q), row);
           }
-          uq[4] = priv_u(min(q0 + 4, j))[row];  // used only where it is u_{q0+4}
+          uq[4] = get_priv(priv_u(min(q0 + 4, j)), row);  // used only where it is u_{q0+4}
 #pragma unroll
           for (int s = 0; s < 4; ++s) {
             const int q = q0 + s;
             if (q > j) break;
             const V rv = cfnma(alpha, q == j ? un[i] : uq[s + 1], rq[s]);
             const V uv = cfnma(beta, uq[s], rv);
-            priv_r(q)[row] = rv;
-            priv_u(q)[row] = uv;
+            put_priv(priv_r(q), row, rv);
+            put_priv(priv_u(q), row, uv);
             if (q == 1) u1[i] = uv;
           }
         }
         const V uv = cfnma(beta, un[i], rn[i]);
-        priv_r(j + 1)[row] = rn[i];
-        priv_u(j + 1)[row] = uv;
+        put_priv(priv_r(j + 1), row, rn[i]);
+        put_priv(priv_u(j + 1), row, uv);
         if (j == 0) u1[i] = uv;
       }
     }
@@ -274,8 +282,8 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
       for (int q = 1; q <= kLMax; ++q) {
         x[i][q] = uq[q] = czero<V>();
         if (q < ell && m.has(i)) {
-          x[i][q] = priv_r(q)[row];
-          uq[q] = priv_u(q)[row];
+          x[i][q] = get_priv(priv_r(q), row);
+          uq[q] = get_priv(priv_u(q), row);
         }
       }
 #pragma unroll
@@ -339,7 +347,7 @@ __global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
 #pragma unroll
       for (int q = 1; q <= kLMax; ++q) {
         uq[q] = czero<V>();
-        if (q < ell && m.has(i)) uq[q] = priv_u(q)[row];
+        if (q < ell && m.has(i)) uq[q] = get_priv(priv_u(q), row);
         if (q == ell) uq[q] = un[i];
       }
       V y = s_y[l], r = r0[i], u = u0[i];
