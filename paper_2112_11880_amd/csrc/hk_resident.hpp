@@ -138,19 +138,32 @@ template <class V, int E, int EL, int RPT, int NT> struct ResRows {
       c[i][k] = (unsigned)((k < len ? cc : rc) + shift) * (unsigned)sizeof(V);  // byte offset
     }
   }
+  // Entry k ends a four; `part` and `acc` are the sums of its four and of the
+  // row with av * xv added.
+  static __device__ __forceinline__ constexpr bool ends(int k) { return (k - (E - 1) / 2) % 4 == 0 || k == E - 1; }
+  static __device__ __forceinline__ void sum(int k, double2 av, double2 xv, double2& part, double2& acc) {
+    part = k == 0 || ends(k - 1) ? cmul(av, xv) : cfma(av, xv, part);
+    if (ends(k)) acc = k <= (E - 1) / 2 % 4 ? part : cadd(acc, part);
+  }
   // Sum over the row's entries of a_k comb(k, ld(k, column)), the loads of
   // kGroup entries at a time issued ahead of the previous group's arithmetic:
   // left alone the compiler issues every load of the row at once and spills
-  // the matrix.  complex64 rows are summed in double: with a float chain the
-  // refinement cycles of the mixed solve took up to twice the iterations of
-  // the kernels that sum a row's products over lanes (279,496 rows, second
-  // cycle: 606 against 400-425 on average), and the double one costs the same
-  // time, which the gathers set.
+  // the matrix.  The entries are summed four at a time, and a mesh row's middle
+  // one, its diagonal, ends its four (`sum`): the largest partial sums are then
+  // rounded every fourth entry.  One chain of multiply-adds over the row rounds
+  // them twice per entry; its error on a random vector was 2.7e-16 of 15 entries
+  // and 3.5e-16 of 27 against 1.5e-16 and 1.7e-16 with fours and 1.5e-16 to
+  // 2.1e-16 and 1.7e-16 to 2.5e-16 in the row-block products (16 to 64 rows per
+  // wave), and a BiCGStab(8) solve's true residual fell as much.  complex64
+  // rows are summed in double: with a float chain the refinement cycles of the
+  // mixed solve took up to twice the iterations of the kernels that sum a row's
+  // products over lanes (279,496 rows, second cycle: 606 against 400-425 on
+  // average), and the double one costs the same time, which the gathers set.
   template <class L, class C> __device__ __forceinline__ V dot(int i, L&& ld, C&& comb) const {
     constexpr int kBytes = E * RPT * (int)sizeof(V);
     constexpr int kGroup = kBytes <= 240 ? 4 : kBytes <= 440 ? 3 : 2, NG = (E + kGroup - 1) / kGroup;
     using X = decltype(ld(0, 0u));
-    double2 acc = make_double2(0, 0);
+    double2 acc = make_double2(0, 0), part = make_double2(0, 0);
     X x[2][kGroup];
 #pragma unroll
     for (int k = 0; k < kGroup; ++k)
@@ -165,10 +178,11 @@ template <class V, int E, int EL, int RPT, int NT> struct ResRows {
 #pragma unroll
       for (int k = 0; k < kGroup; ++k) {
         const int kk = g * kGroup + k;
-        if (kk < ER) acc = cfma(entry_d(a[i][kk]), to_d(comb(kk, x[g & 1][k])), acc);
-        else if (kk < E) acc = cfma(to_d(lv[(i * EL + kk - ER) * NT + threadIdx.x]), to_d(comb(kk, x[g & 1][k])), acc);
+        if (kk < ER) sum(kk, entry_d(a[i][kk]), to_d(comb(kk, x[g & 1][k])), part, acc);
+        else if (kk < E) sum(kk, to_d(lv[(i * EL + kk - ER) * NT + threadIdx.x]), to_d(comb(kk, x[g & 1][k])), part, acc);
       }
       here(acc);
+      if (!ends(min((g + 1) * kGroup, E) - 1)) here(part);
     }
     return vscal<V>(acc);
   }

@@ -23,9 +23,13 @@ namespace hk {
 constexpr int kSliceL = 2;
 constexpr int kSliceWaves = 4;
 
-// Sum of row 64 * slice + lane of values at val + 64 ptr[slice], in the order of
-// the columns; complex64 in double, whose conversions are free beside the
-// loads.  `ptr` and `off` are read by scalar loads.
+// Sum of row 64 * slice + lane of values at val + 64 ptr[slice]: in the order of
+// the columns, the entries of a step and of what precedes the diagonal summed by
+// themselves, which keeps the largest partial sums from being rounded at each
+// entry (as in the resident rows: 1.6e-16 of 15 entries on a random vector, 1.7e-16
+// of 27, against 2.7e-16 and 3.5e-16 in one chain); complex64 in double, whose
+// conversions are free beside the loads.  `ptr` and `off` are read by scalar
+// loads.
 template <class V>
 __device__ __forceinline__ V slice_row(int slice, int n, const int* __restrict__ ptr, const int* __restrict__ off,
                                        const V* __restrict__ val, const V* __restrict__ x) {
@@ -34,18 +38,32 @@ __device__ __forceinline__ V slice_row(int slice, int n, const int* __restrict__
   int j = __builtin_amdgcn_readfirstlane(ptr[slice]);
   const int end = __builtin_amdgcn_readfirstlane(ptr[slice + 1]);
   double2 acc = make_double2(0, 0);
-  auto col = [&](int k) { return min(max(r + off[k], 0), n - 1); };
-  auto add = [&](V a, V b) { acc = cfma(make_double2(a.x, a.y), make_double2(b.x, b.y), acc); };
+  auto col = [&](int d) { return min(max(r + d, 0), n - 1); };
+  auto wide = [](V v) { return make_double2(v.x, v.y); };
   for (; j + U <= end; j += U) {
+    int d[U];
     V a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) d[u] = off[j + u];
 #pragma unroll
     for (int u = 0; u < U; ++u) a[u] = ldnt(val + (size_t)(j + u) * kWave + l);
 #pragma unroll
-    for (int u = 0; u < U; ++u) b[u] = x[col(j + u)];
+    for (int u = 0; u < U; ++u) b[u] = x[col(d[u])];
+    double2 part = cmul(wide(a[0]), wide(b[0]));
 #pragma unroll
-    for (int u = 0; u < U; ++u) add(a[u], b[u]);
+    for (int u = 1; u < U; ++u) {
+      if (d[u - 1] == 0) {  // the same for the whole wave
+        acc = cadd(acc, part);
+        part = cmul(wide(a[u]), wide(b[u]));
+      } else {
+        part = cfma(wide(a[u]), wide(b[u]), part);
+      }
+    }
+    acc = cadd(acc, part);
   }
-  for (; j < end; ++j) add(ldnt(val + (size_t)j * kWave + l), x[col(j)]);
+  double2 rest = make_double2(0, 0);
+  for (; j < end; ++j) rest = cfma(wide(ldnt(val + (size_t)j * kWave + l)), wide(x[col(off[j])]), rest);
+  acc = cadd(acc, rest);
   return cmake<V>((decltype(V::x))acc.x, (decltype(V::x))acc.y);
 }
 
