@@ -240,7 +240,10 @@ typedef struct {
  * to 262,144 rows of at most 15, 131,072 of more; complex64: twice that)
  * instead runs as one cooperative launch on `stream`, check_every unused; a
  * handle whose launch shape was set (hk_csr_set_plan, hk_csr_set_solver_plan)
- * never does.  A zero
+ * never does, and BiCGStab(l) with l > 4 and a tolerance below 1e-10 only up
+ * to 32,768 rows: beyond, the digits of so small a tolerance depend on the
+ * order of the sums (solutions differ by up to some 1e-9), and such a solve
+ * keeps that of the row blocks.  A zero
  * diagonal entry with precond = 1, or an unknown method, gives HK_EINVAL.
  * info->shape reports the fused products' launch shape {lanes per row (64:
  * row blocks), rows per lane group or per wave, waves per workgroup, paired
@@ -250,7 +253,8 @@ typedef struct {
  * values kept per entry), the products of the other solves read the solver's
  * copy of the matrix in slices of 64 rows, {2, 64, waves per workgroup, 0}; the
  * handle keeps the distances from the first such solve on.  A handle whose
- * launch shape was set keeps to that shape.
+ * launch shape was set keeps to that shape, and the BiCGStab(l) solves named
+ * above to the handle's own or a tuned one.
  * Returns info->status (>= 0) or an error.  x always holds the last iterate.
  */
 int hk_krylov_solve(hk_csr A, const void* d_b, void* d_x, const hk_solve_opts* opts,

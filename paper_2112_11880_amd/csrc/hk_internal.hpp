@@ -88,8 +88,9 @@ struct hk_csr_s {
   void* ws32 = nullptr;
   size_t ws32_bytes = 0;
   // launch shapes of the solver's fused SpMV+dot kernels, tuned on the
-  // first solve of a tuned handle ([0] complex128, [1] complex64)
-  hk::SpmvPlan dot_plan[2];
+  // first solve of a tuned handle ([0] complex128, [1] complex64, [2]
+  // complex128 without the slices)
+  hk::SpmvPlan dot_plan[3];
   // a launch shape was set by the caller: the solvers use it and nothing else
   bool plan_fixed = false;
   // workspace of the batched solve (device), kept like the solver's

@@ -614,10 +614,28 @@ static SpmvPlan slice_plan() {
   return p;
 }
 
+// BiCGStab(l) of many steps per cycle to a tolerance near what it attains: the
+// last digits of its solution are those of the order of its sums.  To 1e-12 with
+// l = 8, two orders gave solutions of 120 to 300 systems of tetrahedra that differ
+// by (median, most) 1.2e-11 and 1.5e-10 at 2,000-4,000 rows, 1.3e-11 and 2.1e-10 at
+// 16,000-32,000, 2.8e-11 and 4.7e-10 at 32,000-64,000, 5.2e-11 and 3.5e-9 at
+// 64,000-130,000, 1.0e-10 and 9.1e-10 above (1.3e-9 once on 232,897 rows), the same
+// for two shapes of the row blocks and for row blocks and resident rows; l = 2, 4
+// and the other methods stayed within 2e-10 on 40 systems to 381,000 rows.  Above
+// the line these solves keep the row blocks, and with them the bits that they have
+// had (232,897 rows: 41 ms, resident 19); up to it the resident rows agree with
+// them to 2e-10 and are two to four times as fast.
+constexpr int64_t kOrderedRows = 32768;
+static bool keeps_order(const hk_csr_s* A, const hk_solve_opts& o) {
+  return o.method == HK_BICGSTAB_L && o.ell > 4 && o.tol < 1e-10 && A->n > kOrderedRows;
+}
+// Slot of such a solve's tuned shape.
+constexpr int kOrderedPlan = 2;
+
 // The fused products' shape where none was fixed or tuned: slices if the handle
-// has them, else its CSR shape.
-static SpmvPlan default_dot_plan(const hk_csr_s* A) {
-  if (A->slices.values > 0 && !A->plan_fixed) return slice_plan();
+// has them and the solve may use them, else its CSR shape.
+static SpmvPlan default_dot_plan(const hk_csr_s* A, bool slices = true) {
+  if (slices && A->slices.values > 0 && !A->plan_fixed) return slice_plan();
   SpmvPlan p = A->plan;
   p.nw = 0;
   return p;
@@ -744,7 +762,7 @@ static hipError_t launch_fin(const Work<R>& wk, int nb, double tol, long long ma
 // values do not matter for timing); the scalar state is set to running here,
 // left so by the F_TUNE finalize, and re-initialised by the solve afterwards.
 template <class R>
-static int tune_dot(const hk_csr_s* A, const Work<R>& wk, SpmvPlan* out, hipStream_t s) {
+static int tune_dot(const hk_csr_s* A, const Work<R>& wk, SpmvPlan* out, hipStream_t s, bool slices = true) {
   std::vector<SpmvPlan> cands;
   for (int grid : {0, 2048}) {
     for (int L : {4, 8, 16, 32})
@@ -758,7 +776,7 @@ static int tune_dot(const hk_csr_s* A, const Work<R>& wk, SpmvPlan* out, hipStre
           if ((A->n + (int64_t)nw * U - 1) / ((int64_t)nw * U) <= kMaxGrid || nw == 8) cands.push_back(p);
         }
   }
-  if (A->slices.values > 0)
+  if (slices && A->slices.values > 0)
     for (int grid : {0, 2048})
       for (int nw : {2, 4, 8}) {
         SpmvPlan p = slice_plan();
@@ -1982,7 +2000,8 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
   view.res = wk.res;
   view.st = wk.st;
   view.flag = wk.flag;
-  {
+  const bool ordered = keeps_order(A, o);
+  if (!ordered) {
     bool ran = false;
     const int rc = resident_solve<R>(A, val, b, x, o, view, info, &ran, s, [&](const ResShape& sh, ResArgs<R>& a) {
       ResLArgs l{};
@@ -1994,8 +2013,8 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
     });
     if (rc != HK_OK || ran) return rc;
   }
-  SpmvPlan dp = default_dot_plan(A);
-  SpmvPlan& cached = A->dot_plan[0];
+  SpmvPlan dp = default_dot_plan(A, !ordered);
+  SpmvPlan& cached = A->dot_plan[ordered ? kOrderedPlan : 0];
   if (!cached.tuned && A->plan.tuned) {
     // the workspace vectors serve as tuning operands before the solve starts
     Work<R> tv{};
@@ -2005,7 +2024,7 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
     tv.rh = wk.rt;
     tv.partials = wk.partials;
     tv.st = wk.st;
-    int rc = tune_dot<R>(A, tv, &cached, s);
+    int rc = tune_dot<R>(A, tv, &cached, s, !ordered);
     if (rc != HK_OK) return rc;
   }
   if (cached.tuned) dp = cached;
@@ -2089,9 +2108,9 @@ static int ensure_pinned(hk_csr_s* A) {
 // info->shape of the plain and mixed solves: the fused products' shape
 // {lanes per row (64: row blocks), rows per group or wave, waves per
 // workgroup, paired layout} of precision slot prec (0 complex128, 1
-// complex64), or the handle's CSR shape when none was fixed or tuned.
+// complex64, kOrderedPlan), or the handle's CSR shape when none was fixed or tuned.
 static void report_shape(const hk_csr_s* A, int prec, hk_solve_info* info) {
-  const SpmvPlan d = A->dot_plan[prec].tuned ? A->dot_plan[prec] : default_dot_plan(A);
+  const SpmvPlan d = A->dot_plan[prec].tuned ? A->dot_plan[prec] : default_dot_plan(A, prec != kOrderedPlan);
   info->shape[0] = d.L;
   info->shape[1] = d.U;
   info->shape[2] = d.nw;
@@ -2133,7 +2152,8 @@ extern "C" int hk_krylov_solve(hk_csr A, const void* d_b, void* d_x, const hk_so
   rc = ensure_pinned(A);
   if (rc != HK_OK) return rc;
   for (int k = 0; k < 4; ++k) info->shape[k] = 0;  // a resident solve reports its own
-  rc = want_slices(A, A->dtype == HK_C64 ? 1 : 0, s);
+  const bool ordered = keeps_order(A, *opts);
+  if (!ordered) rc = want_slices(A, A->dtype == HK_C64 ? 1 : 0, s);
   if (rc != HK_OK) return rc;
   if (A->dtype == HK_C64) {
     if (opts->method != HK_BICGSTAB) HK_FAIL(HK_EINVAL, "hk_krylov_solve: complex64 solves use BiCGStab only");
@@ -2156,7 +2176,7 @@ extern "C" int hk_krylov_solve(hk_csr A, const void* d_b, void* d_x, const hk_so
                             info, s);
   }
   if (rc != HK_OK) return rc;
-  if (info->shape[0] == 0) report_shape(A, A->dtype == HK_C64 ? 1 : 0, info);
+  if (info->shape[0] == 0) report_shape(A, ordered ? kOrderedPlan : A->dtype == HK_C64 ? 1 : 0, info);
   return info->status;
 }
 

@@ -412,7 +412,7 @@ extern "C" int hk_csr_set_plan(hk_csr A, int32_t L, int32_t U, int32_t grid) {
   if (!valid_shape(L, U) || grid < 0) HK_FAIL(HK_EINVAL, "hk_csr_set_plan: bad shape L=%d U=%d grid=%d", L, U, grid);
   A->plan.L = L; A->plan.U = U; A->plan.grid = grid; A->plan.tuned = 0;
   A->plan_fixed = true;
-  A->dot_plan[0] = A->dot_plan[1] = SpmvPlan{};  // the solvers' products follow the new shape
+  A->dot_plan[0] = A->dot_plan[1] = A->dot_plan[2] = SpmvPlan{};  // the solvers' products follow the new shape
   return HK_OK;
 }
 
@@ -427,7 +427,7 @@ extern "C" int hk_csr_set_solver_plan(hk_csr A, int32_t rows_per_wave, int32_t w
     HK_FAIL(HK_EINVAL, "hk_csr_set_solver_plan: the paired layout needs the 16-bit column stream");
   SpmvPlan p;
   p.L = kRowBlockL; p.U = rows_per_wave; p.nw = waves; p.grid = grid; p.pairs = paired; p.tuned = 2;
-  A->dot_plan[0] = A->dot_plan[1] = p;
+  A->dot_plan[0] = A->dot_plan[1] = A->dot_plan[2] = p;
   A->plan_fixed = true;
   return HK_OK;
 }

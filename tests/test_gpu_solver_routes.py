@@ -62,3 +62,33 @@ def test_row_sums_round_no_more_than_row_blocks(hk, elem, far, first):
     assert here["status"] == blocks["status"] == hk.HK_OK
     assert here["shape"][0] == first and blocks["shape"][:2] == [64, 32], (here, blocks)
     assert here["relres_true"] <= 1.15 * blocks["relres_true"], (here, blocks)
+
+
+@pytest.mark.parametrize("cells,l8", [((31, 31, 31), 1), ((32, 31, 31), 64), ((60, 45, 50), 64), ((76, 60, 58), 64)])
+def test_bicgstab_8_keeps_the_order_of_its_sums(hk, cells, l8):
+    """Above 32,768 rows BiCGStab(8) to less than 1e-10 gives the bits of the
+    kernels per phase in the handle's own shape, whether the system would fit the
+    registers (143,106 rows) or have its products on slices (277,123); a looser
+    tolerance and l = 4 take the faster routes."""
+    rowptr, col, val, b = mesh_system(cells)
+    n = b.shape[0]
+    print("[case] order of sums", n, flush=True)
+    A = hk.CSR(dev(rowptr), dev(col), dev(val))
+    other = 1 if n <= 262144 else 2
+    kw = dict(method="bicgstab_l", max_iter=4)
+    for ell, tol, first in ((4, 1e-12, other), (8, 1e-10, other), (8, 1e-12, l8), (8, 0.0, l8)):
+        x, info = hk.krylov_solve(A, dev(b), tol=tol, ell=ell, **kw)
+        assert info["shape"][0] == first, (ell, tol, info)
+    B = hk.CSR(A.rowptr, A.col, A.val)
+    p = A.plan()
+    B.set_plan(p["lanes_per_row"], p["rows_per_group"], p["grid"])
+    kw["max_iter"] = 400
+    x, info = hk.krylov_solve(A, dev(b), tol=1e-12, **kw)
+    y, _ = hk.krylov_solve(B, dev(b), tol=1e-12, **kw)
+    assert info["status"] == hk.HK_OK
+    assert torch.equal(x, y) == (l8 == 64)
+    assert torch.linalg.vector_norm(x - y) <= 1e-9 * torch.linalg.vector_norm(y)
+    T = hk.CSR(A.rowptr, A.col, A.val, autotune=True)
+    for method, tol in (("bicgstab", 1e-3), ("bicgstab_l", 1e-12)):  # the first may tune and keep slices
+        _, info = hk.krylov_solve(T, dev(b), tol=tol, method=method)
+    assert (info["shape"][0] == 1) if l8 == 1 else (info["shape"][0] not in (1, 2) and info["shape_tuned"]), info
