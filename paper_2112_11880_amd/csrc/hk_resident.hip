@@ -224,7 +224,7 @@ __device__ __forceinline__ bool res_bicgstab(const Src& A, GridSum& gs, int size
 }
 
 template <class R, int E, int EL, int RPT, int NT>
-__global__ __launch_bounds__(NT) void k_res_bicgstab(ResArgs<R> A) {
+__global__ __launch_bounds__(NT, kResWaves) void k_res_bicgstab(ResArgs<R> A) {
   __shared__ ResBiLds<R, EL, RPT, NT> lds;
   if (*A.flag) return;
   const ResPlace at(A.packed);
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(NT) void k_res_sweep(ResSweepArgs B) {
 // TFQMR (complex128).  Statuses, counts and updates at each exit are those of
 // the kernels in hk_solver.hip.
 template <int E, int EL, int RPT, int NT>
-__global__ __launch_bounds__(NT) void k_res_tfqmr(ResArgs<double> A) {
+__global__ __launch_bounds__(NT, kResWaves) void k_res_tfqmr(ResArgs<double> A) {
   using V = double2;
   __shared__ ResLds<NT> lds;
   __shared__ V s_rh[RPT * NT], s_y[RPT * NT], s_d[RPT * NT], s_lv[EL > 0 ? RPT * EL * NT : 1];

@@ -22,6 +22,11 @@ namespace hk {
 // workgroups.
 constexpr int kRing = 4;
 constexpr int kSweepLanes = 64;  // columns of a sweep's right-hand sides
+// Waves per SIMD that the single solves' kernels leave room for: two workgroups
+// of 256 threads per CU, which a packed launch of up to 64 workgroups counts on
+// (the compiler gives a 256-thread kernel more than 256 registers otherwise, and
+// BiCGStab(l) took 261 and 274 for rows of 15 and 27 entries).
+constexpr int kResWaves = 2;
 
 template <class R> struct ResArgs {
   using V = cplx<R>;

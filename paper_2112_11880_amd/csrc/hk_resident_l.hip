@@ -71,7 +71,7 @@ __device__ __forceinline__ bool gram_solve(const double* totals, int ell, double
 }
 
 template <int E, int EL, int RPT, int NT>
-__global__ __launch_bounds__(NT) void k_res_bicgstab_l(ResLArgs L) {
+__global__ __launch_bounds__(NT, kResWaves) void k_res_bicgstab_l(ResLArgs L) {
   using V = double2;
   constexpr int W = NT / kWave;
   __shared__ ResLds<NT> lds;

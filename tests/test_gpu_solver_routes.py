@@ -92,3 +92,16 @@ def test_bicgstab_8_keeps_the_order_of_its_sums(hk, cells, l8):
     for method, tol in (("bicgstab", 1e-3), ("bicgstab_l", 1e-12)):  # the first may tune and keep slices
         _, info = hk.krylov_solve(T, dev(b), tol=tol, method=method)
     assert (info["shape"][0] == 1) if l8 == 1 else (info["shape"][0] not in (1, 2) and info["shape_tuned"]), info
+
+
+@pytest.mark.parametrize("method,kw", [("bicgstab", {}), ("tfqmr", {}), ("bicgstab_l", {"ell": 2}), ("bicgstab_l", {"ell": 8})])
+@pytest.mark.parametrize("cells,elem", [((20, 19, 19), "p1"), ((20, 19, 19), "q1"), ((25, 23, 24), "p1"), ((25, 23, 24), "q1")])
+def test_packed_launch_has_room(hk, oracle, method, kw, cells, elem):
+    """8,400 and 15,600 rows: 33 and 61 workgroups of 256 threads on one XCD, two of
+    them on some of its 32 CUs.  Every method runs resident there."""
+    rowptr, col, val, b = mesh_system(cells, elem)
+    print("[case] packed", method, kw, b.shape[0], elem, flush=True)
+    x, info = hk.krylov_solve(hk.CSR(dev(rowptr), dev(col), dev(val)), dev(b), tol=1e-9, method=method, **kw)
+    assert info["status"] == hk.HK_OK and info["shape"] == [1, 1, 4, 0], info
+    r = oracle.residual(rowptr, col, val, b, x.cpu().numpy())
+    assert np.linalg.norm(r) <= 1.05e-9 * np.linalg.norm(b)
