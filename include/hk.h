@@ -365,7 +365,9 @@ int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, const int32_
  * shape is given and no barrier times are asked for, the systems are instead
  * solved side by side by workgroups that keep their rows in registers, still
  * in one cooperative launch; the tiled launch in the shape reported takes over
- * if that one times out.  The workspace is kept in the handle.
+ * if that one times out (a workgroup's wait for the others to come from their
+ * earlier systems counts only while no system is being solved).  The workspace is
+ * kept in the handle.
  */
 int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off, const void* d_b, void* d_x,
                        const hk_solve_opts* opts, hk_solve_info* infos, void* stream);

@@ -2315,8 +2315,8 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
   a.bar = ar.take<GridBar>(1);
   double* gpart = ar.take<double>(4 * (size_t)kXcds * kSys);
   int* flag = ar.take<int>(16);
-  // resident: the barrier words (two sets of sets per system, then the abort
-  // flag), the systems, their ends, the job lists
+  // resident: the barrier words (a set of sets per system, then the flags), the
+  // systems, their ends, the job lists
   unsigned long long* words = nullptr;
   ResBatchSystem* d_sys = nullptr;
   ResBatchEnd* d_ends = nullptr;
@@ -2447,6 +2447,7 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
     ra.base.maxit = opts->max_iter;
     ra.base.gs.words = words;
     ra.base.gs.abort = (int*)(words + nsys * set_words);
+    ra.running = ra.base.gs.abort + kResFlags / 2;  // on another line than the flag
     ra.base.gs.spin_limit = spin;
     ra.sys = d_sys;
     ra.job_ptr = d_jptr;

@@ -255,11 +255,12 @@ __device__ __forceinline__ bool sum_give_up(const GridSum& gs, unsigned long lon
 // totals, in every thread.  `epoch` starts at 0.  lds: room for
 // kSumWords * (NT / 64 + 4) doubles, used by nothing else.  With INV the
 // caller's caches drop what they hold.  Returns true if the kernel must stop
-// (a wait passed the limit here or elsewhere).  All threads of the workgroups
-// call it.
+// (a wait passed the limit here or elsewhere).  With `running` (a device count)
+// the others may come late, each from work of its own: the limit then counts only
+// while *running is 0.  All threads of the workgroups call it.
 template <int NV, int NT>
 __device__ __forceinline__ bool group_sum(const GridSum& gs, int size, int rank, unsigned& epoch, bool inv,
-                                          double (&v)[NV], double* lds) {
+                                          double (&v)[NV], double* lds, const int* running = nullptr) {
   static_assert(NV >= 1 && NV <= kSumWords && NT >= kSumBlocks, "sums and pollers");
   constexpr int W = NT / kWave, NP = (NV + 1) / 2;  // pairs of words
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
@@ -295,7 +296,7 @@ __device__ __forceinline__ bool group_sum(const GridSum& gs, int size, int rank,
   for (int k = 0; k < 2 * NP; ++k) part[k] = 0;
   if ((int)threadIdx.x < size) {
     const int off = at_word(rank % kSumReps, threadIdx.x);
-    const unsigned long long t0 = wall_clock64();
+    unsigned long long t0 = wall_clock64();
     nu2 q[NP];
     for (int spins = 0;; ++spins) {
       bool all = true;
@@ -306,6 +307,7 @@ __device__ __forceinline__ bool group_sum(const GridSum& gs, int size, int rank,
 #pragma unroll
       for (int k = 0; k < NV; ++k) all = all && q[k / 2][k % 2] != kSumEmpty;
       if (all) break;
+      if (running && (spins & 15) == 14 && ld_relaxed_i32(running) > 0) t0 = wall_clock64();
       if (sum_give_up(gs, t0, spins)) { ok = false; break; }
     }
 #pragma unroll

@@ -52,10 +52,13 @@ template <class R, int EL, int RPT, int NT> struct ResBiLds {
 
 // BiCGStab on the rows [r0, rend) of this workgroup, number `rank` of the `size`
 // that solve the system: D x is left in lds.y.  LOC: they may find that they
-// share an XCD.  Returns true if the kernel must stop.
+// share an XCD.  `running`, if any: the systems that all of their workgroups have
+// come to; the others of this one may still be at another.  Returns true if the
+// kernel must stop.
 template <class R, int E, int EL, int RPT, int NT, bool LOC, class Src>
 __device__ __forceinline__ bool res_bicgstab(const Src& A, GridSum& gs, int size, int rank, unsigned& epoch,
-                                             const ResMap<RPT, NT>& m, ResBiLds<R, EL, RPT, NT>& lds, ResEnd& end) {
+                                             const ResMap<RPT, NT>& m, ResBiLds<R, EL, RPT, NT>& lds, ResEnd& end,
+                                             int* running = nullptr) {
   using V = cplx<R>;
   // the rows' gathered r, kept from the v product for the t product where
   // the registers allow (15 fewer 16-byte gathers per row)
@@ -90,9 +93,10 @@ __device__ __forceinline__ bool res_bicgstab(const Src& A, GridSum& gs, int size
     sum2[0] += nrm2d(bi);
     sum2[1] += nrm2d(ri);
   }
-  if (group_sum<4, NT>(gs, size, rank, epoch, true, sum2, lds.sums.sums)) return true;
+  if (group_sum<4, NT>(gs, size, rank, epoch, true, sum2, lds.sums.sums, running)) return true;
   if (LOC) gs.local = same_xcd(size, sum2[2], sum2[3]);
   const bool first = rank == 0 && threadIdx.x == 0;
+  if (running && first) atomicAdd(running, 1);
   const double bb = uni(sum2[0]), theta2 = uni(A.tol * A.tol * bb);
   double rr = uni(sum2[1]);
   double2 rho = make_double2(rr, 0), beta = make_double2(0, 0), alpha, omega;
@@ -278,7 +282,10 @@ __device__ __forceinline__ bool res_finish(const Src& A, const GridSum& gs, int 
 // Systems of a block-diagonal matrix, each solved by as many workgroups as its
 // rows need.  A workgroup works through the list of its systems (jobs), whose
 // order is one order over all systems: the first unfinished one finds all its
-// workgroups done with what comes before it, so every wait ends.
+// workgroups done with what comes before it, so every wait ends.  A workgroup that
+// comes to a system early waits in its first barrier for whole solves of others,
+// as long as these take: the limit of that wait counts only while no system runs,
+// and one that runs has the limit at each of its own barriers.
 template <int E, int EL, int RPT, int NT>
 __global__ __launch_bounds__(NT) void k_res_batch(ResBatchArgs B) {
   __shared__ ResBiLds<double, EL, RPT, NT> lds;
@@ -293,9 +300,10 @@ __global__ __launch_bounds__(NT) void k_res_batch(ResBatchArgs B) {
     ResEnd e;
     unsigned epoch = 0;
     __syncthreads();
-    if (res_bicgstab<double, E, EL, RPT, NT, true>(A, gs, S.size, rank, epoch, m, lds, e)) return;
+    if (res_bicgstab<double, E, EL, RPT, NT, true>(A, gs, S.size, rank, epoch, m, lds, e, B.running)) return;
     if (res_finish<RPT, NT>(A, gs, S.size, rank, epoch, m, lds, e, B.end + sys, [&](int row, double2 x) { B.X[row] = x; }))
       return;
+    if (rank == 0 && threadIdx.x == 0) atomicAdd(B.running, -1);
   }
 }
 
@@ -534,7 +542,7 @@ constexpr size_t kResWords = kSumSets * kSumSetWords, kResMany = kManyWords;
 __global__ void k_res_reset(unsigned long long* words, size_t count, int* abort) {
   const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < count) words[i] = kSumEmpty;
-  if (i == 0) *abort = 0;
+  if (i < kResFlags) abort[i] = 0;
 }
 hipError_t resident_reset(unsigned long long* words, size_t count, int* abort, hipStream_t s) {
   hipLaunchKernelGGL(k_res_reset, dim3((unsigned)((count + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, words, count,

@@ -280,6 +280,7 @@ struct ResBatchArgs {
   const int *job_ptr, *job_sys, *job_rank;
   double2* X;
   ResBatchEnd* end;
+  int* running;  // systems that all of their workgroups have come to, 0 at launch
 };
 // Rows per thread (1 or 2), rows per workgroup and the job lists for systems of
 // the given rows; false if one does not fit.
@@ -353,7 +354,9 @@ hipError_t resident_sweep_launch(const ResSweepPlan& plan, ResSweepArgs args, hi
 // kern with sh's grid and the argument struct at kargs[0], whose GridSum is gs.
 hipError_t resident_launch_kernel(const void* kern, const ResShape& sh, void** kargs, GridSum* gs, void* scratch,
                                   hipStream_t s);
-// All of `count` barrier words empty, *abort (which may lie behind them) 0.
+// All of `count` barrier words empty, the kResFlags ints at abort (which may lie
+// behind them) 0.
+constexpr size_t kResFlags = 32;
 hipError_t resident_reset(unsigned long long* words, size_t count, int* abort, hipStream_t s);
 // The abort flag in the scratch (device address), and the words behind it.
 int* resident_abort(void* scratch);

@@ -105,3 +105,35 @@ def test_packed_launch_has_room(hk, oracle, method, kw, cells, elem):
     assert info["status"] == hk.HK_OK and info["shape"] == [1, 1, 4, 0], info
     r = oracle.residual(rowptr, col, val, b, x.cpu().numpy())
     assert np.linalg.norm(r) <= 1.05e-9 * np.linalg.norm(b)
+
+
+def block_diagonal(parts):
+    """One matrix of several systems (rowptr, col, val, b) and their row offsets."""
+    off = np.concatenate([[0], np.cumsum([p[3].shape[0] for p in parts])])
+    nnz = np.cumsum([0] + [p[1].shape[0] for p in parts])
+    rowptr = np.concatenate([[0]] + [p[0][1:] + z for p, z in zip(parts, nnz)]).astype(np.int32)
+    col = np.concatenate([p[1] + o for p, o in zip(parts, off)]).astype(np.int32)
+    return off, rowptr, col, np.concatenate([p[2] for p in parts]), np.concatenate([p[3] for p in parts])
+
+
+def test_batch_waits_for_earlier_systems(hk, monkeypatch):
+    """Systems of 99, 97, 89 and 61 workgroups (27 entries: one row per thread) on 256:
+    the second one never converges, and most workgroups of the fourth are free from
+    the start while eight of them solve the second, for some 0.2 s.  A barrier limit of
+    40 ms does not end that wait: the bits are those under the default limit, which the
+    tiled launch does not give."""
+    easy = [mesh_system(c, "q1", seed=k, kappa=complex(1.0, 0.01)) for k, c in enumerate([(36, 36, 36), (34, 35, 35), (30, 31, 30)])]
+    hard = mesh_system((36, 36, 35), "q1", seed=7, kappa=complex(500.0, 5.0))
+    off, rowptr, col, val, b = block_diagonal([easy[0], hard, easy[1], easy[2]])
+    assert [-(-(int(hi) - int(lo)) // 512) for lo, hi in zip(off, off[1:])] == [99, 97, 89, 61]
+    A = hk.CSR(dev(rowptr), dev(col), dev(val))
+    kw = dict(tol=1e-25, max_iter=20000)
+    print("[case] batch, default barrier limit", flush=True)
+    x, infos = hk.blockdiag_solve(A, off, dev(b), **kw)
+    assert infos[1]["iters"] > 8000 and all(infos[k]["status"] == hk.HK_OK and infos[k]["iters"] < 2000 for k in (0, 2, 3)), infos
+    print("[case] batch, 40 ms", flush=True)
+    monkeypatch.setenv("HK_BARRIER_SPIN_TICKS", "4000000")
+    y, late = hk.blockdiag_solve(A, off, dev(b), **kw)
+    assert torch.equal(x, y) and [i["iters"] for i in late] == [i["iters"] for i in infos]
+    z, _ = hk.blockdiag_solve(A, off, dev(b), shape=infos[0]["shape"], **kw)
+    assert not torch.equal(x, z)
