@@ -213,7 +213,8 @@ typedef struct {
   int64_t inner_iters;   /* mixed precision: total inner iterations; else 0 */
   int32_t shape[4];      /* launch shape of the solve's products (see each solve) */
   int32_t shape_tuned;   /* 1 if that shape was chosen by timing on the device */
-  int32_t pad;
+  int32_t resident;    /* rows per thread of the resident launch (matrix in registers) that
+                          gave the result; 0: the other launches did */
 } hk_solve_info;
 
 /*
@@ -338,7 +339,8 @@ int hk_krylov_solve_mixed(hk_csr A, const void* d_b, void* d_x, double inner_tol
  * limits of hk_krylov_solve), no shape is given and no barrier times are asked
  * for, groups of workgroups that keep the rows in registers solve one system
  * after the other instead, still in one cooperative launch; the interleaved
- * launch in the shape reported takes over if that one times out.
+ * launch in the shape reported takes over if that one times out (infos[j].resident
+ * says which gave the result).
  */
 int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_col,
                    const double* d_K, const double* d_M, int32_t nsys, const double* kappa,
@@ -367,7 +369,7 @@ int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, const int32_
  * in one cooperative launch; the tiled launch in the shape reported takes over
  * if that one times out (a workgroup's wait for the others to come from their
  * earlier systems counts only while no system is being solved).  The workspace is
- * kept in the handle.
+ * kept in the handle, and infos[k].resident says which launch gave the result.
  */
 int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off, const void* d_b, void* d_x,
                        const hk_solve_opts* opts, hk_solve_info* infos, void* stream);

@@ -1898,7 +1898,7 @@ static void set_shape(hk_solve_info* infos, int nsys, const std::array<int, 4>& 
   for (int j = 0; j < nsys; ++j) {
     for (int k = 0; k < 4; ++k) infos[j].shape[k] = sh[k];
     infos[j].shape_tuned = tuned;
-    infos[j].pad = 0;
+    infos[j].resident = 0;
   }
 }
 
@@ -2214,6 +2214,7 @@ extern "C" int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, c
       batch_ends(ends, nsys, &hs);
       fill_infos(hs, nsys, infos);
       set_shape(infos, nsys, shape, tuned);
+      for (int k = 0; k < nsys; ++k) infos[k].resident = rp.rpt;
       return worst_status(infos, nsys);
     }
     (void)hipGetLastError();  // not run, or timed out: the interleaved launch starts over
@@ -2474,6 +2475,7 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
       batch_ends(ends, nsys, &hs);
       fill_infos(hs, nsys, infos);
       set_shape(infos, nsys, shape, tuned);
+      for (int k = 0; k < nsys; ++k) infos[k].resident = rp.rpt;
       return worst_status(infos, nsys);
     }
     (void)hipGetLastError();  // not run, or timed out: the tiled launch starts over

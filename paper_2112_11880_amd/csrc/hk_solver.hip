@@ -998,7 +998,7 @@ static int resident_solve(hk_csr_s* A, const cplx<R>* val, const cplx<R>* b, cpl
   info->shape[2] = sh.threads / kWave;
   info->shape[3] = 0;
   info->shape_tuned = 0;
-  info->pad = 0;
+  info->resident = sh.rpt;
   return HK_OK;
 }
 
@@ -2116,7 +2116,7 @@ static void report_shape(const hk_csr_s* A, int prec, hk_solve_info* info) {
   info->shape[2] = d.nw;
   info->shape[3] = d.pairs;
   info->shape_tuned = d.tuned == 1 ? 1 : 0;
-  info->pad = 0;
+  info->resident = 0;
 }
 
 // Slices for a system whose solve will stream its matrix.
@@ -2291,6 +2291,7 @@ extern "C" int hk_krylov_solve_mixed(hk_csr A, const void* d_b, void* d_x, doubl
   if (inner_shape.shape[0] != 0) {  // the inner solves were resident
     for (int q = 0; q < 4; ++q) info->shape[q] = inner_shape.shape[q];
     info->shape_tuned = 0;
+    info->resident = inner_shape.resident;
   }
   return status;
 }

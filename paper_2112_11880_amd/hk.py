@@ -42,10 +42,10 @@ HK_MIXED_LITERAL_INNER = 1
 class SolveInfo(C.Structure):
     _fields_ = [("iters", C.c_int64), ("relres_rec", C.c_double), ("relres_true", C.c_double),
                 ("status", C.c_int32), ("breakdown", C.c_int32), ("inner_iters", C.c_int64),
-                ("shape", C.c_int32 * 4), ("shape_tuned", C.c_int32), ("pad", C.c_int32)]
+                ("shape", C.c_int32 * 4), ("shape_tuned", C.c_int32), ("resident", C.c_int32)]
 
     def as_dict(self):
-        d = {k: getattr(self, k) for k, _ in self._fields_ if k != "pad"}
+        d = {k: getattr(self, k) for k, _ in self._fields_}
         d["shape"] = list(self.shape)
         d["shape_tuned"] = bool(self.shape_tuned)
         return d

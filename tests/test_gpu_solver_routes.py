@@ -6,6 +6,9 @@ import pytest
 from synth import helmholtz as H
 from synth import hexahedra as HX
 
+from test_gpu_resident import block_diagonal as dominant_blocks
+from test_gpu_resident import dominant
+
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -137,3 +140,79 @@ def test_batch_waits_for_earlier_systems(hk, monkeypatch):
     assert torch.equal(x, y) and [i["iters"] for i in late] == [i["iters"] for i in infos]
     z, _ = hk.blockdiag_solve(A, off, dev(b), shape=infos[0]["shape"], **kw)
     assert not torch.equal(x, z)
+
+
+@pytest.mark.parametrize("sizes,row,rows_per_thread", [
+    ([1], 1, (1,)), ([1, 2, 63, 64, 65, 130], 8, (1, 2)), ([700, 5, 20000, 513, 1], 15, (1, 2)),
+    ([40000, 70000, 3000] + [65] * 61, 15, (1, 2)), ([131073, 900, 131072, 17], 15, (2,)), ([131073, 900, 131072, 17], 8, (2,)),
+    ([500, 9000, 27], 27, (1,)), ([300, 40], 28, (0,)), ([131073, 50], 27, (0,))])
+def test_batch_reports_its_launch(hk, sizes, row, rows_per_thread):
+    """Every form of the batch's resident launch runs where its systems fit (a refused
+    launch would leave the tiled one, and 0 here)."""
+    _, off, rowptr, col, val, b = dominant_blocks(sizes, row, 17)
+    A = hk.CSR(dev(rowptr), dev(col), dev(val))
+    print("[case] batch launch", sizes[:4], row, flush=True)
+    x, infos = hk.blockdiag_solve(A, off, dev(b), tol=0.0, max_iter=2)
+    assert all(i["resident"] in rows_per_thread for i in infos) and len({i["resident"] for i in infos}) == 1, infos
+    y, infos = hk.blockdiag_solve(A, off, dev(b), tol=0.0, max_iter=2, shape=infos[0]["shape"])
+    assert all(i["resident"] == 0 for i in infos)
+    assert torch.allclose(x, y, rtol=1e-9, atol=1e-10)
+
+
+@pytest.mark.parametrize("n,row,nsys,rows_per_thread", [
+    (512, 15, 3, (0,)), (513, 15, 3, (1, 2)), (1000, 8, 64, (1, 2)), (9000, 15, 33, (1, 2)), (20011, 15, 5, (1, 2)),
+    (70001, 15, 7, (1, 2)), (131073, 15, 3, (2,)), (140000, 8, 2, (2,)), (40000, 27, 5, (1,)), (131073, 27, 2, (0,)),
+    (3000, 28, 3, (0,)), (60001, 15, 4, (1, 2)), (40001, 15, 64, (1, 2)), (131072, 15, 2, (1, 2)), (100003, 15, 19, (1, 2)),
+    (33000, 8, 13, (1, 2))])
+def test_sweep_reports_its_launch(hk, n, row, nsys, rows_per_thread):
+    """The same for the sweep: one and two rows per thread, one and several systems at a time."""
+    rowptr, col, val, _ = dominant(n, row, n + row)
+    diag = col == np.repeat(np.arange(n), np.diff(rowptr))
+    K, M = np.where(diag, 1.0, val.real), np.where(diag, 0.2, val.imag)
+    B = np.zeros((n, 64), dtype=np.complex128)
+    B[:, :nsys] = np.random.default_rng(n).standard_normal((n, nsys))
+    args = (dev(rowptr), dev(col), dev(K), dev(M), [complex(0.1 + 0.4 * j / nsys, 0.01 * (j + 1)) for j in range(nsys)], dev(B))
+    print("[case] sweep launch", n, row, nsys, flush=True)
+    X, infos = hk.sweep_solve(*args, tol=1e-14, max_iter=2)
+    assert all(i["resident"] in rows_per_thread for i in infos) and len({i["resident"] for i in infos}) == 1, infos
+    Y, infos = hk.sweep_solve(*args, tol=1e-14, max_iter=2, shape=infos[0]["shape"])
+    assert all(i["resident"] == 0 for i in infos)
+    assert torch.allclose(X, Y, rtol=1e-9, atol=1e-10)
+
+
+def test_single_solves_report_their_launch(hk):
+    for n, row, here in ((5000, 15, 1), (140000, 15, 2), (5000, 28, 0)):
+        rowptr, col, val, b = dominant(n, row, n)
+        A = hk.CSR(dev(rowptr), dev(col), dev(val))
+        for method in ("bicgstab", "tfqmr", "bicgstab_l"):
+            print("[case] launch", method, n, row, flush=True)
+            assert hk.krylov_solve(A, dev(b), tol=1e-6, method=method)[1]["resident"] == here, (n, row, method)
+        assert hk.krylov_solve_mixed(A, dev(b), outer_tol=1e-8)[1]["resident"] == here, (n, row, "mixed")
+
+
+@pytest.mark.parametrize("n,nsys", [(5000, 2), (5000, 64)])
+def test_batched_time_out_in_a_resident_launch(hk, monkeypatch, n, nsys):
+    """With a limit of one tick the resident launch ends through its abort path, and
+    so does the launch that starts over; the next calls are resident again and
+    give the bits from before."""
+    rowptr, col, val, _ = dominant(n, 15, 9)
+    diag = col == np.repeat(np.arange(n), np.diff(rowptr))
+    K, M = np.where(diag, 1.0, val.real), np.where(diag, 0.2, val.imag)
+    B = np.zeros((n, 64), dtype=np.complex128)
+    B[:, :nsys] = np.random.default_rng(1).standard_normal((n, nsys))
+    args = (dev(rowptr), dev(col), dev(K), dev(M), [complex(0.1 + 0.001 * j, 0.01) for j in range(nsys)], dev(B))
+    _, off, rp, c, v, b = dominant_blocks([3000, 900, 20000], 15, 5)
+    A = hk.CSR(dev(rp), dev(c), dev(v))
+    X, _ = hk.sweep_solve(*args, tol=1e-12)
+    x, _ = hk.blockdiag_solve(A, off, dev(b), tol=1e-12)
+    monkeypatch.setenv("HK_BARRIER_SPIN_TICKS", "1")
+    print("[case] limit of one tick: sweep, batch", n, nsys, flush=True)
+    with pytest.raises(hk.HKError, match="timed out"):
+        hk.sweep_solve(*args, tol=1e-12)
+    with pytest.raises(hk.HKError, match="timed out"):
+        hk.blockdiag_solve(A, off, dev(b), tol=1e-12)
+    monkeypatch.delenv("HK_BARRIER_SPIN_TICKS")
+    Y, infos = hk.sweep_solve(*args, tol=1e-12)
+    assert all(i["resident"] for i in infos) and torch.equal(X, Y)
+    y, infos = hk.blockdiag_solve(A, off, dev(b), tol=1e-12)
+    assert all(i["resident"] for i in infos) and torch.equal(x, y)
