@@ -216,3 +216,96 @@ def test_batched_time_out_in_a_resident_launch(hk, monkeypatch, n, nsys):
     assert all(i["resident"] for i in infos) and torch.equal(X, Y)
     y, infos = hk.blockdiag_solve(A, off, dev(b), tol=1e-12)
     assert all(i["resident"] for i in infos) and torch.equal(x, y)
+
+
+METHODS = [("bicgstab", {}), ("tfqmr", {}), ("bicgstab_l", {"ell": 4})]
+
+
+@pytest.mark.parametrize("method,kw", METHODS)
+@pytest.mark.parametrize("route", [64, 16, 2])
+def test_kernels_per_phase_replay_graphs(hk, monkeypatch, method, kw, route):
+    """The recorded chunks of the kernels per phase, on row blocks, lane groups and
+    slices, give the bits of direct launches, with a chunk of 3 iterations and with
+    the default one."""
+    rowptr, col, val, b = mesh_system((30, 29, 30) if route == 2 else (7, 6, 6), "q1")
+    if route == 2:  # 28 entries at few distances: slices
+        rowptr, col, val = with_far_entries(rowptr, col, val, 9000, 1e-9 * abs(val).max())
+    A = hk.CSR(dev(rowptr), dev(col), dev(val))
+    if route != 2:
+        A.set_plan(route, 2 if route == 16 else 32)
+    for every in (3, 0):
+        got = []
+        for graphs in ("1", "0"):
+            monkeypatch.setenv("HK_SOLVE_GRAPHS", graphs)
+            print("[case] graph replay", method, route, every, graphs, flush=True)
+            got.append(hk.krylov_solve(A, dev(b), tol=1e-10, check_every=every, method=method, **kw))
+        (x, info), (y, direct) = got
+        assert info["status"] == hk.HK_OK and info["resident"] == 0 and info["shape"][0] == route, info
+        assert info == direct and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("method,kw", METHODS)
+@pytest.mark.parametrize("plan", [None, (64, 32), (16, 2)])
+def test_exits_on_every_route(hk, oracle, method, kw, plan):
+    """Breakdowns, non-finite and zero right-hand sides, an exact start, the cap and a
+    diagonal system, resident (no plan) and by the kernels per phase."""
+    def handle(rowptr, col, val):
+        A = hk.CSR(dev(np.asarray(rowptr, dtype=np.int32)), dev(np.asarray(col, dtype=np.int32)),
+                   dev(np.asarray(val, dtype=np.complex128)))
+        if plan:
+            A.set_plan(*plan)
+        return A
+
+    def solve(A, b, **more):
+        x, info = hk.krylov_solve(A, dev(np.asarray(b, dtype=np.complex128)), method=method, **kw, **more)
+        assert info["resident"] == (0 if plan else 1), info
+        return x.cpu().numpy(), info
+
+    print("[case] exits", method, plan, flush=True)
+    x, info = solve(handle([0, 2, 4], [0, 1, 0, 1], [1.0, -1.25, -1.25, 1.0]), [1.0, 2.0], tol=1e-12)
+    assert info["status"] == hk.HK_BREAKDOWN and hk.BD_NAMES[info["breakdown"]] == "sigma"
+    assert info["iters"] == 0 and np.all(x == 0)
+    if method == "bicgstab":
+        x, info = solve(handle([0, 3, 6, 9], list(range(3)) * 3, [1, 1, 0, 1, 1, -1, 1, -1, 1]), [1.0, 0, 0], tol=1e-14)
+        assert info["status"] == hk.HK_BREAKDOWN and hk.BD_NAMES[info["breakdown"]] == "omega"
+        assert info["iters"] == 1 and np.array_equal(x, np.array([1.0, 0, 0]))
+    with pytest.raises(hk.HKError, match="zero diagonal"):
+        solve(handle([0, 1, 2], [1, 0], [1.0, 1.0]), [1.0, 1.0])
+    rng = np.random.default_rng(2)
+    d, b = rng.standard_normal(40) + 3.0 + 1j * rng.standard_normal(40), rng.standard_normal(40) + 0j
+    x, info = solve(handle(np.arange(41), np.arange(40), d), b, tol=1e-12)
+    assert info["status"] == hk.HK_OK and info["iters"] == 1 and np.allclose(x, b / d, rtol=1e-14, atol=0)
+    rowptr, col, val, b = mesh_system((9, 8, 8))
+    A = handle(rowptr, col, val)
+    x, info = solve(A, np.zeros_like(b))
+    assert info["status"] == hk.HK_OK and info["iters"] == 0 and np.all(x == 0)
+    for bad in (np.nan, np.inf):
+        g = b.copy()
+        g[7] = bad
+        assert solve(A, g)[1]["status"] == hk.HK_NONFINITE
+    xo, _ = oracle.bicgstab(rowptr, col, val, b, tol=1e-12)
+    x, info = solve(A, b, x=dev(xo), tol=1e-8)
+    assert info["status"] == hk.HK_OK and info["iters"] == 0
+    x, info = solve(A, b, max_iter=2, tol=1e-14)
+    ref = getattr(oracle, method)(rowptr, col, val, b, tol=1e-14, maxit=2, **kw)[0]
+    assert info["status"] == hk.HK_NOT_CONVERGED and info["iters"] == 2
+    assert np.linalg.norm(x - ref) <= 1e-10 * np.linalg.norm(ref)
+    x, info, hist = hk.krylov_solve(A, dev(b), tol=1e-9, method=method, history=True, **kw)
+    h = hist.cpu().numpy()
+    assert info["status"] == hk.HK_OK and h.shape[0] == info["iters"] + 1
+    assert h[0] == pytest.approx(1.0) and h[-1] <= 1.0001e-9 and h[-1] == pytest.approx(info["relres_rec"])
+
+
+@pytest.mark.parametrize("n", [5000, 20000])
+def test_bicgstab_l_starts_over_after_a_time_out(hk, oracle, monkeypatch, n):
+    """A resident BiCGStab(l) whose barrier waits may take no time ends through its
+    abort path, and the kernels per phase solve from the caller's start."""
+    rowptr, col, val, b = dominant(n, 15, 9)
+    rng = np.random.default_rng(1)
+    x0 = rng.standard_normal(n) + 1j * rng.standard_normal(n)
+    monkeypatch.setenv("HK_BARRIER_SPIN_TICKS", "1")
+    print("[case] bicgstab_l, limit of one tick", n, flush=True)
+    x, info = hk.krylov_solve(hk.CSR(dev(rowptr), dev(col), dev(val)), dev(b), x=dev(x0), tol=1e-12, method="bicgstab_l", ell=2)
+    assert info["status"] == hk.HK_OK and info["resident"] == 0, info
+    r = oracle.residual(rowptr, col, val, b, x.cpu().numpy())
+    assert np.linalg.norm(r) <= 1.05e-12 * np.linalg.norm(b)
