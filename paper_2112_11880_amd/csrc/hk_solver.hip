@@ -756,13 +756,15 @@ static hipError_t launch_fin(const Work<R>& wk, int nb, double tol, long long ma
 // on A's pattern and keeps the fastest in *out (HIP events on stream s).
 // Row-block shapes are tried with 2, 4 and 8 waves per workgroup where the
 // tiles fit under kMaxGrid, and on the 16-bit column stream in both entry
-// layouts (the products read the solver's padded copy of the values); every
-// shape with one workgroup per tile and with 2,048 workgroups walking the
-// tiles (fewer partials for the finalize).  The workspace vectors serve as operands (their
-// values do not matter for timing); the scalar state is set to running here,
-// left so by the F_TUNE finalize, and re-initialised by the solve afterwards.
+// layouts (the products read Ahat, val D^-1, filled in here in the layout of the
+// shapes that follow); every shape with one workgroup per tile and with 2,048
+// workgroups walking the tiles (fewer partials for the finalize).  The workspace
+// vectors serve as operands (their values do not matter for timing); the scalar
+// state is set to running here, left so by the F_TUNE finalize, and re-initialised
+// by the solve afterwards.
 template <class R>
-static int tune_dot(const hk_csr_s* A, const Work<R>& wk, SpmvPlan* out, hipStream_t s, bool slices = true) {
+static int tune_dot(const hk_csr_s* A, const cplx<R>* val, const Work<R>& wk, SpmvPlan* out, hipStream_t s,
+                    bool slices = true) {
   std::vector<SpmvPlan> cands;
   for (int grid : {0, 2048}) {
     for (int L : {4, 8, 16, 32})
@@ -793,9 +795,13 @@ static int tune_dot(const hk_csr_s* A, const Work<R>& wk, SpmvPlan* out, hipStre
   SpmvPlan best = cands[0];
   float best_ms = 1e30f;
   int rc = HK_OK;
+  bool filled[2] = {false, false};  // the candidates on slices come last
   for (const SpmvPlan& p : cands) {
     const int g = dot_grid(A, p);
     hipError_t err = hipSuccess;
+    bool& have = filled[p.L == kSliceL];
+    if (!have) err = fill_ahat<cplx<R>>(A, p, val, wk.dinv, wk.ahat, s);
+    have = true;
     const int reps = 5;
     for (int it = 0; it < reps + 1 && err == hipSuccess; ++it) {
       if (it == 1) err = hipEventRecord(e0, s);
@@ -1044,7 +1050,7 @@ static int bicgstab(hk_csr_s* A, const cplx<R>* val, const cplx<R>* b, cplx<R>* 
   SpmvPlan dp = default_dot_plan(A);
   SpmvPlan& cached = A->dot_plan[sizeof(R) == 4 ? 1 : 0];
   if (!cached.tuned && A->plan.tuned) {
-    int rc = tune_dot<R>(A, wk, &cached, s);
+    int rc = tune_dot<R>(A, val, wk, &cached, s);
     if (rc != HK_OK) return rc;
   }
   if (cached.tuned) dp = cached;
@@ -1504,7 +1510,7 @@ static int tfqmr(hk_csr_s* A, const double2* val, const double2* b, double2* x, 
   SpmvPlan dp = default_dot_plan(A);
   SpmvPlan& cached = A->dot_plan[0];
   if (!cached.tuned && A->plan.tuned) {
-    int rc = tune_dot<R>(A, wk, &cached, s);
+    int rc = tune_dot<R>(A, val, wk, &cached, s);
     if (rc != HK_OK) return rc;
   }
   if (cached.tuned) dp = cached;
@@ -2019,12 +2025,13 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
     // the workspace vectors serve as tuning operands before the solve starts
     Work<R> tv{};
     tv.ahat = wk.ahat;
+    tv.dinv = wk.dinv;
     tv.p = wk.vec.r[1];
     tv.v = wk.vec.u[1];
     tv.rh = wk.rt;
     tv.partials = wk.partials;
     tv.st = wk.st;
-    int rc = tune_dot<R>(A, tv, &cached, s, !ordered);
+    int rc = tune_dot<R>(A, val, tv, &cached, s, !ordered);
     if (rc != HK_OK) return rc;
   }
   if (cached.tuned) dp = cached;
