@@ -30,6 +30,11 @@
  *     on one handle must not overlap (from several threads, or on several
  *     streams at once); use one handle per concurrent stream.  Distinct
  *     handles, and the BLAS-1 calls on distinct streams, are independent.
+ *     Cooperative launches (resident solves, batched solves) of one process run
+ *     one after the other on a device, whatever their streams: solves of several
+ *     threads take turns and give the bits of single calls.  Where such a launch is
+ *     refused, as by a second process on the device, a plain or mixed solve runs
+ *     as separate kernels (see hk_krylov_solve) and a batched one fails.
  */
 #ifndef HK_H_
 #define HK_H_

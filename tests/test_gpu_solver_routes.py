@@ -309,3 +309,49 @@ def test_bicgstab_l_starts_over_after_a_time_out(hk, oracle, monkeypatch, n):
     assert info["status"] == hk.HK_OK and info["resident"] == 0, info
     r = oracle.residual(rowptr, col, val, b, x.cpu().numpy())
     assert np.linalg.norm(r) <= 1.05e-12 * np.linalg.norm(b)
+
+
+def test_solves_of_two_threads_at_once(hk):
+    """Two handles, each in a thread and on a stream of its own: resident launches that
+    would each fill the device, with a BLAS-1 loop beside them on a third stream, give
+    the bits of single calls, every time."""
+    import threading
+    systems = [mesh_system((44, 45, 46), seed=1), mesh_system((46, 44, 43), seed=2)]
+    alone = []
+    for rowptr, col, val, b in systems:
+        A = hk.CSR(dev(rowptr), dev(col), dev(val))
+        x, info = hk.krylov_solve(A, dev(b), tol=1e-9)
+        assert info["resident"] == 1
+        alone.append((A, dev(b), x, info["iters"]))
+    torch.cuda.synchronize()
+    got, done = [[], []], threading.Event()
+
+    def work(k):
+        A, b, _, _ = alone[k]
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(6):
+                print("[case] thread", k, flush=True)
+                x, info = hk.krylov_solve(A, b, tol=1e-9)
+                got[k].append((x, info))
+            torch.cuda.current_stream().synchronize()
+
+    def noise():
+        with torch.cuda.stream(torch.cuda.Stream()):
+            u, v = torch.ones(1 << 20, dtype=torch.complex128, device=DEV), torch.zeros(1 << 20, dtype=torch.complex128, device=DEV)
+            while not done.is_set():
+                for _ in range(20):
+                    hk.zaxpy(0.5, u, v)
+                torch.cuda.current_stream().synchronize()
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    beside = threading.Thread(target=noise)
+    for t in [beside, *threads]:
+        t.start()
+    for t in threads:
+        t.join()
+    done.set()
+    beside.join()
+    for k in range(2):
+        assert len(got[k]) == 6
+        for x, info in got[k]:
+            assert info["resident"] == 1 and info["iters"] == alone[k][3] and torch.equal(x, alone[k][2]), (k, info)
