@@ -265,7 +265,8 @@ def _bench_sweep(hk, torch, np, dev, log, plain, max_iter, shape):
     if plain:
         log(f"plain every 8th frequency: {t_plain:.3f} s x 8 (iters {it_plain})")
     log("sweep phases", phases)
-    res["solve_sweep"] = {"systems": 64, "n": int(c["n"]), "time_s": round(t_sweep, 4), "phases": phases,
+    res["solve_sweep"] = {"systems": 64, "n": int(c["n"]), "time_s": round(t_sweep, 4),
+                          "resident": infos[0]["resident"], "phases_interleaved_launch": phases,
                           "shape": infos[0]["shape"], "shape_tuned": infos[0]["shape_tuned"],
                           "tune_s": round(tune_sweep, 4), "iters_min": min(its), "iters_max": max(its),
                           "us_per_iter_max": round(t_sweep / max(its) * 1e6, 2),
@@ -322,7 +323,8 @@ def _bench_uneven(hk, torch, np, dev, log, plain, max_iter, shape):
     if plain:
         log(f"32 plain solves: {t_seq:.3f} s")
     phases = uneven_phases(stamps.cpu().numpy(), min(i["iters"] for i in pinf), offs[-1], nnz, np)
-    res["solve_uneven"] = {"systems": 32, "rows": offs[-1], "time_s": round(t_bd, 4), "phases": phases,
+    res["solve_uneven"] = {"systems": 32, "rows": offs[-1], "time_s": round(t_bd, 4),
+                           "resident": infos[0]["resident"], "phases_tiled_launch": phases,
                            "shape": infos[0]["shape"], "shape_tuned": infos[0]["shape_tuned"],
                            "tune_s": round(tune_bd, 4), "iters_min": min(its), "iters_max": max(its),
                            "status_all_ok": all(i["status"] == 0 for i in infos),

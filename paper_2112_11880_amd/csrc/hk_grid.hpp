@@ -350,7 +350,7 @@ constexpr size_t kManyWords = 2 * kManyPart + kSumSets * kManyTot;
 
 // `waves`: the workgroup's partial sums by wave, waves[c * W + w] for c < nc,
 // written before the call; totals[c] on return, in LDS.  `call` starts at 0.
-// As grid_sum without INV otherwise; all threads of every workgroup call it.
+// As group_sum without INV otherwise; all threads of every workgroup call it.
 template <int NT>
 __device__ __forceinline__ bool grid_sum_many(const GridSum& gs, int G, int rank, unsigned long long* many,
                                               unsigned& call, int nc, const double* waves, double* totals) {

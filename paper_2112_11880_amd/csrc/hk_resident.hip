@@ -537,7 +537,7 @@ __global__ __launch_bounds__(NT, kResWaves) void k_res_tfqmr(ResArgs<double> A) 
 
 // ------------------------------------------------------------------ host side
 
-// Scratch: the words of grid_sum, those of grid_sum_many, the abort flag.
+// Scratch: the words of group_sum, those of grid_sum_many, the flags.
 constexpr size_t kResWords = kSumSets * kSumSetWords, kResMany = kManyWords;
 __global__ void k_res_reset(unsigned long long* words, size_t count, int* abort) {
   const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
@@ -704,19 +704,20 @@ static double many_iteration_us(int size, int slots, bool local) {
   return (local ? 7 : 12) + 0.02 * size + 4.6 * slots;
 }
 
+size_t ResSweepPlan::words() const {
+  return (size_t)groups * (kSumSets * kSumSetWords + (slots > 1 ? resident_many_words(slots) : 0));
+}
 // Rows per thread, or systems at a time: whichever gets through the systems in
 // less time, taken in rounds of one system per group, or as long as the slots
 // are full (each is filled again as soon as it is free).  64 systems of 117,649
 // rows: 291 ms with two rows per thread (two groups of one system), 212 with six
 // slots; two systems are faster with a group each (20 us per iteration against
 // 29).
-size_t ResSweepPlan::words() const {
-  return (size_t)groups * (kSumSets * kSumSetWords + (slots > 1 ? resident_many_words(slots) : 0));
-}
 bool resident_sweep_plan(int device, int64_t n, int64_t nnz, int max_row, int nsys, ResSweepPlan* plan) {
-  // a system of one workgroup stays with the interleaved launch, which is also
-  // the one that records barrier times: at that size a call with the record
-  // and one without have always given the same bits
+  // a system of one workgroup stays with the interleaved launch, not for its
+  // speed (63 iterations of 3 systems: 5.0 ms at 512 rows, 0.68 resident at 513)
+  // but because that launch records the barrier times: at such sizes a call with
+  // the record and one without give the same bits, as they always have
   if (n <= 512 || nnz <= 0 || max_row > kResEntries[2]) return false;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
