@@ -355,3 +355,18 @@ def test_solves_of_two_threads_at_once(hk):
         assert len(got[k]) == 6
         for x, info in got[k]:
             assert info["resident"] == 1 and info["iters"] == alone[k][3] and torch.equal(x, alone[k][2]), (k, info)
+
+
+@pytest.mark.parametrize("cells,shape", [((16, 15, 16), [1, 1, 4, 0]), ((25, 23, 24), [1, 1, 4, 0]), ((48, 48, 48), [1, 1, 8, 0]),
+                                         ((60, 45, 50), [1, 2, 8, 0])])
+def test_resident_bicgstab_8_repeats_its_bits(hk, cells, shape):
+    """l = 8 on one XCD with one and two workgroups per CU, on most CUs with one row
+    per thread and with two: the same bits from call to call and from a new handle."""
+    rowptr, col, val, b = mesh_system(cells)
+    print("[case] repeat bicgstab(8)", b.shape[0], flush=True)
+    A = hk.CSR(dev(rowptr), dev(col), dev(val))
+    x, info = hk.krylov_solve(A, dev(b), tol=1e-9, method="bicgstab_l", ell=8)
+    assert info["status"] == hk.HK_OK and info["shape"] == shape, info
+    for again in (A, A, hk.CSR(A.rowptr, A.col, A.val)):
+        y, other = hk.krylov_solve(again, dev(b), tol=1e-9, method="bicgstab_l", ell=8)
+        assert other == info and torch.equal(x, y)
