@@ -370,3 +370,27 @@ def test_resident_bicgstab_8_repeats_its_bits(hk, cells, shape):
     for again in (A, A, hk.CSR(A.rowptr, A.col, A.val)):
         y, other = hk.krylov_solve(again, dev(b), tol=1e-9, method="bicgstab_l", ell=8)
         assert other == info and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("n,nsys", [(5000, 3), (9000, 33), (40001, 20)])
+def test_sweep_keeps_nonfinite_columns_apart(hk, n, nsys):
+    """A NaN and an infinity in two right-hand sides end these systems only: the others
+    have the bits that they have beside zero columns."""
+    rowptr, col, val, _ = dominant(n, 15, n)
+    diag = col == np.repeat(np.arange(n), np.diff(rowptr))
+    K, M = np.where(diag, 1.0, val.real), np.where(diag, 0.2, val.imag)
+    kap = [complex(0.1 + 0.4 * j / nsys, 0.01 * (j + 1)) for j in range(nsys)]
+    B = np.zeros((n, 64), dtype=np.complex128)
+    B[:, :nsys] = np.random.default_rng(n).standard_normal((n, nsys))
+    B[:, [0, nsys - 1]] = 0
+    bad = B.copy()
+    bad[n // 2, 0], bad[1, nsys - 1] = np.nan, np.inf
+    arrays = (dev(rowptr), dev(col), dev(K), dev(M), kap)
+    print("[case] sweep, non-finite columns", n, nsys, flush=True)
+    X, infos = hk.sweep_solve(*arrays, dev(B), tol=1e-10)
+    Y, late = hk.sweep_solve(*arrays, dev(bad), tol=1e-10)
+    assert all(i["resident"] for i in infos + late)
+    assert [late[k]["status"] for k in (0, nsys - 1)] == [hk.HK_NONFINITE] * 2
+    for k in range(1, nsys - 1):
+        assert late[k]["status"] == hk.HK_OK and late[k]["iters"] == infos[k]["iters"]
+    assert torch.equal(X[:, 1:nsys - 1], Y[:, 1:nsys - 1])
