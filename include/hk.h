@@ -34,7 +34,10 @@
  *     one after the other on a device, whatever their streams: solves of several
  *     threads take turns and give the bits of single calls.  Where such a launch is
  *     refused, as by a second process on the device, a plain or mixed solve runs
- *     as separate kernels (see hk_krylov_solve) and a batched one fails.
+ *     as separate kernels (see hk_krylov_solve) and a batched one fails.  Where
+ *     device memory does not hold the workspace of a resident launch or of sliced
+ *     products, the launches that need less solve (the environment variable
+ *     HK_WORKSPACE_LIMIT, read at each call, refuses workspaces of more bytes).
  */
 #ifndef HK_H_
 #define HK_H_

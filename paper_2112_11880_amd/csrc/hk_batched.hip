@@ -1817,11 +1817,7 @@ struct DevArena : Arena {
     if (base) (void)hipFree(base);
   }
   int alloc(size_t n, const char* who) {
-    if (hipMalloc((void**)&base, n) != hipSuccess) {
-      base = nullptr;
-      (void)hipGetLastError();
-      HK_FAIL(HK_ENOMEM, "%s: hipMalloc(%zu)", who, n);
-    }
+    if (workspace_alloc((void**)&base, n) != hipSuccess) HK_FAIL(HK_ENOMEM, "%s: hipMalloc(%zu)", who, n);
     bytes = n;
     return HK_OK;
   }
@@ -2018,12 +2014,16 @@ extern "C" int hk_sweep_solve(int64_t n, int64_t nnz, const int32_t* d_rowptr, c
   // the resident solve of the systems (hk_resident.hip), where they fit; the
   // barrier stamps are those of the interleaved launch, and a shape given is its
   ResSweepPlan rp;
-  const bool resident = tuned && !opts->d_history && resident_sweep_plan(dev, n, nnz, max_row, nsys, &rp);
+  bool resident = tuned && !opts->d_history && resident_sweep_plan(dev, n, nnz, max_row, nsys, &rp);
   DevArena ar;
-  rc = ar.alloc(2 * a256(8 * (size_t)n) + a256(16 * kSys) + a256(64) +
-                (resident ? a256(16 * rp.pub()) + a256(16 * rp.own()) + 256 + a256(8 * (rp.words() + 32)) +
-                                a256(sizeof(ResBatchEnd) * kSys) + a256(4 * (kSys + 1)) : 0),
+  const size_t base_bytes = 2 * a256(8 * (size_t)n) + a256(16 * kSys) + a256(64);
+  rc = ar.alloc(base_bytes + (resident ? a256(16 * rp.pub()) + a256(16 * rp.own()) + 256 + a256(8 * (rp.words() + 32)) +
+                                             a256(sizeof(ResBatchEnd) * kSys) + a256(4 * (kSys + 1)) : 0),
                 "hk_sweep_solve");
+  if (rc == HK_ENOMEM && resident) {
+    resident = false;
+    rc = ar.alloc(base_bytes, "hk_sweep_solve");
+  }
   if (rc != HK_OK) return rc;
   SweepArgs a{};
   a.n = (int)n; a.nsys = nsys; a.rowptr = d_rowptr; a.col = d_col; a.K = d_K; a.M = d_M;
@@ -2266,7 +2266,7 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
   // the resident solve of the systems (hk_resident.hip), where each fits; the
   // barrier stamps are those of the tiled launch, and a shape given is its
   ResBatchPlan rp;
-  const bool resident = !shape_given(opts) && !opts->d_history && resident_batch_plan(A, nsys, row_off, &rp);
+  bool resident = !shape_given(opts) && !opts->d_history && resident_batch_plan(A, nsys, row_off, &rp);
   // static tiles of tile_rows rows that never straddle systems; the arrays
   // are sized for the smallest tiles
   int nt_max = 0;
@@ -2274,15 +2274,19 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
   const int64_t n = A->n;
   Arena ar;
   // the tiled launch's six vectors, or the resident solve's published ones
-  const size_t vstride = a256(16 * (size_t)std::max<int64_t>(n, rp.stride)) / 16;
-  const size_t nvec = resident ? std::max(6, 3 * kRing) : 6;
+  size_t vstride = 0, nvec = 0, bytes = 0;
   const size_t set_words = kSumSets * kSumSetWords, njobs = rp.job_sys.size();
-  const size_t bytes = 16 * vstride * nvec + 2 * a256(16 * (size_t)n) + 3 * a256(4 * (size_t)nt_max) +
-                       3 * a256(4 * (kSys + 1)) + a256(8 * 4 * (size_t)gmax * kSys) +
-                       a256(sizeof(BatchState)) + a256(sizeof(GridBar)) + a256(8 * 4 * (size_t)kXcds * kSys) +
-                       a256(64) + (resident ? a256(8 * (nsys * set_words + 32)) +
-                       a256(sizeof(ResBatchSystem) * kSys) + a256(sizeof(ResBatchEnd) * kSys) +
-                       a256(4 * rp.job_ptr.size()) + 2 * a256(4 * njobs) : 0);
+  auto lay_out = [&]() {
+    vstride = a256(16 * (size_t)(resident ? std::max<int64_t>(n, rp.stride) : n)) / 16;
+    nvec = resident ? std::max(6, 3 * kRing) : 6;
+    bytes = 16 * vstride * nvec + 2 * a256(16 * (size_t)n) + 3 * a256(4 * (size_t)nt_max) +
+            3 * a256(4 * (kSys + 1)) + a256(8 * 4 * (size_t)gmax * kSys) +
+            a256(sizeof(BatchState)) + a256(sizeof(GridBar)) + a256(8 * 4 * (size_t)kXcds * kSys) +
+            a256(64) + (resident ? a256(8 * (nsys * set_words + 32)) +
+            a256(sizeof(ResBatchSystem) * kSys) + a256(sizeof(ResBatchEnd) * kSys) +
+            a256(4 * rp.job_ptr.size()) + 2 * a256(4 * njobs) : 0);
+  };
+  lay_out();
   if (A->bws_bytes < bytes) {
     if (A->bws) {
       HK_HIP(hipStreamSynchronize(s));
@@ -2290,10 +2294,12 @@ extern "C" int hk_blockdiag_solve(hk_csr A, int32_t nsys, const int64_t* row_off
       A->bws = nullptr;
       A->bws_bytes = 0;
     }
-    if (hipMalloc(&A->bws, bytes) != hipSuccess) {
-      A->bws = nullptr;
-      HK_FAIL(HK_ENOMEM, "hk_blockdiag_solve: hipMalloc(%zu)", bytes);
+    if (workspace_alloc(&A->bws, bytes) != hipSuccess && resident) {
+      resident = false;  // the tiled launch has done with less
+      lay_out();
+      (void)workspace_alloc(&A->bws, bytes);
     }
+    if (!A->bws) HK_FAIL(HK_ENOMEM, "hk_blockdiag_solve: hipMalloc(%zu)", bytes);
     A->bws_bytes = bytes;
   }
   ar.base = (char*)A->bws;

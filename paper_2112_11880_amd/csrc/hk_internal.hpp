@@ -98,11 +98,17 @@ struct hk_csr_s {
   size_t bws_bytes = 0;
   // for the solvers' products of systems that do not fit the registers
   hk::SliceStore slices;
+  // this call's workspace went without the share of the resident launch and the
+  // slices, which memory did not hold
+  bool lean = false;
   // pinned host words the solver reads its status through
   int* pinned = nullptr;
 };
 
 namespace hk {
+// hipMalloc of a solve's workspace, refused above the bytes that the environment
+// variable HK_WORKSPACE_LIMIT holds (read at each call; tests use it).
+hipError_t workspace_alloc(void** p, size_t bytes);
 int spmv_tiles(const hk_csr_s* A, int L, int U);
 // Times every launch shape of the CSR product on A (its dtype and values)
 // and stores the fastest in A->plan (cached per matrix shape and dtype).

@@ -568,7 +568,7 @@ constexpr int kResMax[2][3] = {{2, 2, 1}, {4, 4, 2}};  // [complex64][class]
 
 ResShape resident_shape(const hk_csr_s* A, int prec) {
   ResShape sh;
-  if (A->plan_fixed || A->nnz <= 0 || A->max_row > kResEntries[2]) return sh;
+  if (A->plan_fixed || A->lean || A->nnz <= 0 || A->max_row > kResEntries[2]) return sh;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, A->device) != hipSuccess) {
     (void)hipGetLastError();

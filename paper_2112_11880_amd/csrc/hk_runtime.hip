@@ -1,4 +1,5 @@
 // hk_runtime.hip -- error text and reduction scratch of libhk.
+#include <cstdlib>
 #include <map>
 #include <mutex>
 #include <utility>
@@ -19,6 +20,19 @@ void set_error_text(const char* fmt, ...) {
 }
 
 const char* error_text() { return g_error.c_str(); }
+
+hipError_t workspace_alloc(void** p, size_t bytes) {
+  *p = nullptr;
+  const char* v = getenv("HK_WORKSPACE_LIMIT");
+  const unsigned long long most = v ? strtoull(v, nullptr, 10) : 0;
+  if (most > 0 && bytes > most) return hipErrorOutOfMemory;
+  const hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+  }
+  return e;
+}
 
 int reduce_scratch(hipStream_t s, size_t bytes, ReduceScratch** out) {
   static std::mutex mu;

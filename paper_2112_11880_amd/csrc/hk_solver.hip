@@ -556,7 +556,9 @@ static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 // work_bytes runs it with a counting take, carve with one that hands out
 // addresses, so the size and the layout cannot disagree.
 // Values of Ahat: A's with one padding entry (paired-entry products), or slices.
-static size_t ahat_elements(const hk_csr_s* A) { return (size_t)std::max<int64_t>(A->nnz + 1, A->slices.values); }
+static size_t ahat_elements(const hk_csr_s* A) {
+  return (size_t)(A->lean ? A->nnz + 1 : std::max<int64_t>(A->nnz + 1, A->slices.values));
+}
 
 template <class R, class Take> static Work<R> layout(Take take, const hk_csr_s* A) {
   using V = cplx<R>;
@@ -601,9 +603,18 @@ static int ensure_ws(void** ws, size_t* have, size_t need, hipStream_t s) {
     *ws = nullptr;
     *have = 0;
   }
-  if (hipMalloc(ws, need) != hipSuccess) HK_FAIL(HK_ENOMEM, "solver workspace: hipMalloc(%zu) failed", need);
+  if (workspace_alloc(ws, need) != hipSuccess) HK_FAIL(HK_ENOMEM, "solver workspace: hipMalloc(%zu) failed", need);
   *have = need;
   return HK_OK;
+}
+// The same for a solve on A, need(): without the share of the resident launch and
+// the slices where memory does not hold it.
+template <class Need>
+static int ensure_ws(hk_csr_s* A, void** ws, size_t* have, hipStream_t s, Need&& need) {
+  int rc = ensure_ws(ws, have, need(), s);
+  if (rc != HK_ENOMEM) return rc;
+  A->lean = true;
+  return ensure_ws(ws, have, need(), s);
 }
 
 static SpmvPlan slice_plan() {
@@ -634,11 +645,19 @@ constexpr int kOrderedPlan = 2;
 
 // The fused products' shape where none was fixed or tuned: slices if the handle
 // has them and the solve may use them, else its CSR shape.
-static SpmvPlan default_dot_plan(const hk_csr_s* A, bool slices = true) {
+static SpmvPlan default_dot_plan(const hk_csr_s* A, bool slices) {
   if (slices && A->slices.values > 0 && !A->plan_fixed) return slice_plan();
   SpmvPlan p = A->plan;
   p.nw = 0;
   return p;
+}
+
+// The shape of this call: that of slot `slot` (dot_plan) if it was fixed or tuned.
+static bool uses_slices(const hk_csr_s* A, int slot) { return slot != kOrderedPlan && !A->lean; }
+static SpmvPlan dot_plan_of(const hk_csr_s* A, int slot) {
+  const SpmvPlan& d = A->dot_plan[slot];
+  const bool slices = uses_slices(A, slot);
+  return d.tuned && (slices || d.L != kSliceL) ? d : default_dot_plan(A, slices);
 }
 
 // Ahat = A D^-1 in the layout of plan p.
@@ -764,7 +783,7 @@ static hipError_t launch_fin(const Work<R>& wk, int nb, double tol, long long ma
 // by the solve afterwards.
 template <class R>
 static int tune_dot(const hk_csr_s* A, const cplx<R>* val, const Work<R>& wk, SpmvPlan* out, hipStream_t s,
-                    bool slices = true) {
+                    bool slices) {
   std::vector<SpmvPlan> cands;
   for (int grid : {0, 2048}) {
     for (int L : {4, 8, 16, 32})
@@ -1047,13 +1066,12 @@ static int bicgstab(hk_csr_s* A, const cplx<R>* val, const cplx<R>* b, cplx<R>* 
   }
   // fused-product shape: one fixed by hk_csr_set_solver_plan or tuned (on
   // the first solve of a tuned handle), else the handle's CSR shape
-  SpmvPlan dp = default_dot_plan(A);
-  SpmvPlan& cached = A->dot_plan[sizeof(R) == 4 ? 1 : 0];
-  if (!cached.tuned && A->plan.tuned) {
-    int rc = tune_dot<R>(A, val, wk, &cached, s);
+  const int slot = sizeof(R) == 4 ? 1 : 0;
+  if (!A->dot_plan[slot].tuned && A->plan.tuned) {
+    int rc = tune_dot<R>(A, val, wk, &A->dot_plan[slot], s, uses_slices(A, slot));
     if (rc != HK_OK) return rc;
   }
-  if (cached.tuned) dp = cached;
+  const SpmvPlan dp = dot_plan_of(A, slot);
   HK_HIP(fill_ahat<V>(A, dp, val, wk.dinv, wk.ahat, s));
   const int gs = dot_grid(A, dp);
   SolveState init{};
@@ -1507,13 +1525,11 @@ static int tfqmr(hk_csr_s* A, const double2* val, const double2* b, double2* x, 
     const int rc = resident_solve<R>(A, HK_TFQMR, val, b, x, o, wk, info, &ran, s);
     if (rc != HK_OK || ran) return rc;
   }
-  SpmvPlan dp = default_dot_plan(A);
-  SpmvPlan& cached = A->dot_plan[0];
-  if (!cached.tuned && A->plan.tuned) {
-    int rc = tune_dot<R>(A, val, wk, &cached, s);
+  if (!A->dot_plan[0].tuned && A->plan.tuned) {
+    int rc = tune_dot<R>(A, val, wk, &A->dot_plan[0], s, uses_slices(A, 0));
     if (rc != HK_OK) return rc;
   }
-  if (cached.tuned) dp = cached;
+  const SpmvPlan dp = dot_plan_of(A, 0);
   HK_HIP(fill_ahat<V>(A, dp, val, wk.dinv, wk.ahat, s));
   const int gs = dot_grid(A, dp);
   SolveState init{};
@@ -2019,9 +2035,8 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
     });
     if (rc != HK_OK || ran) return rc;
   }
-  SpmvPlan dp = default_dot_plan(A, !ordered);
-  SpmvPlan& cached = A->dot_plan[ordered ? kOrderedPlan : 0];
-  if (!cached.tuned && A->plan.tuned) {
+  const int slot = ordered ? kOrderedPlan : 0;
+  if (!A->dot_plan[slot].tuned && A->plan.tuned) {
     // the workspace vectors serve as tuning operands before the solve starts
     Work<R> tv{};
     tv.ahat = wk.ahat;
@@ -2031,10 +2046,10 @@ static int bicgstab_l(hk_csr_s* A, const double2* val, const double2* b, double2
     tv.rh = wk.rt;
     tv.partials = wk.partials;
     tv.st = wk.st;
-    int rc = tune_dot<R>(A, val, tv, &cached, s, !ordered);
+    int rc = tune_dot<R>(A, val, tv, &A->dot_plan[slot], s, uses_slices(A, slot));
     if (rc != HK_OK) return rc;
   }
-  if (cached.tuned) dp = cached;
+  const SpmvPlan dp = dot_plan_of(A, slot);
   HK_HIP(fill_ahat<V>(A, dp, val, wk.dinv, wk.ahat, s));
   const int gs = dot_grid(A, dp);
   SolveState init{};
@@ -2117,7 +2132,7 @@ static int ensure_pinned(hk_csr_s* A) {
 // workgroup, paired layout} of precision slot prec (0 complex128, 1
 // complex64, kOrderedPlan), or the handle's CSR shape when none was fixed or tuned.
 static void report_shape(const hk_csr_s* A, int prec, hk_solve_info* info) {
-  const SpmvPlan d = A->dot_plan[prec].tuned ? A->dot_plan[prec] : default_dot_plan(A, prec != kOrderedPlan);
+  const SpmvPlan d = dot_plan_of(A, prec);
   info->shape[0] = d.L;
   info->shape[1] = d.U;
   info->shape[2] = d.nw;
@@ -2159,19 +2174,20 @@ extern "C" int hk_krylov_solve(hk_csr A, const void* d_b, void* d_x, const hk_so
   rc = ensure_pinned(A);
   if (rc != HK_OK) return rc;
   for (int k = 0; k < 4; ++k) info->shape[k] = 0;  // a resident solve reports its own
+  A->lean = false;
   const bool ordered = keeps_order(A, *opts);
   if (!ordered) rc = want_slices(A, A->dtype == HK_C64 ? 1 : 0, s);
   if (rc != HK_OK) return rc;
   if (A->dtype == HK_C64) {
     if (opts->method != HK_BICGSTAB) HK_FAIL(HK_EINVAL, "hk_krylov_solve: complex64 solves use BiCGStab only");
-    rc = ensure_ws(&A->ws32, &A->ws32_bytes, work_bytes<float>(A), s);
+    rc = ensure_ws(A, &A->ws32, &A->ws32_bytes, s, [&] { return work_bytes<float>(A); });
     if (rc != HK_OK) return rc;
     rc = bicgstab<float>(A, (const float2*)A->val, (const float2*)d_b, (float2*)d_x, *opts, A->ws32,
                          info, s);
   } else {
-    const size_t need = opts->method == HK_BICGSTAB_L ? bl_work_bytes<double>(A, opts->ell)
-                                                      : work_bytes<double>(A);
-    rc = ensure_ws(&A->ws, &A->ws_bytes, need, s);
+    rc = ensure_ws(A, &A->ws, &A->ws_bytes, s, [&] {
+      return opts->method == HK_BICGSTAB_L ? bl_work_bytes<double>(A, opts->ell) : work_bytes<double>(A);
+    });
     if (rc != HK_OK) return rc;
     if (opts->method == HK_BICGSTAB_L)
       rc = bicgstab_l_dispatch(A, opts->ell, (const double2*)A->val, (const double2*)d_b, (double2*)d_x, *opts,
@@ -2203,9 +2219,10 @@ extern "C" int hk_krylov_solve_mixed(hk_csr A, const void* d_b, void* d_x, doubl
   const size_t extra = align_up(16 * n) + 2 * align_up(8 * n) + align_up(64);
   rc = ensure_pinned(A);
   if (rc != HK_OK) return rc;
+  A->lean = false;
   rc = want_slices(A, 1, s);
   if (rc != HK_OK) return rc;
-  rc = ensure_ws(&A->ws32, &A->ws32_bytes, work_bytes<float>(A) + extra, s);
+  rc = ensure_ws(A, &A->ws32, &A->ws32_bytes, s, [&] { return work_bytes<float>(A) + extra; });
   if (rc != HK_OK) return rc;
   if (!A->val32) {
     if (hipMalloc(&A->val32, 8 * (size_t)(A->nnz > 0 ? A->nnz : 1)) != hipSuccess)

@@ -394,3 +394,74 @@ def test_sweep_keeps_nonfinite_columns_apart(hk, n, nsys):
     for k in range(1, nsys - 1):
         assert late[k]["status"] == hk.HK_OK and late[k]["iters"] == infos[k]["iters"]
     assert torch.equal(X[:, 1:nsys - 1], Y[:, 1:nsys - 1])
+
+
+def outcomes(hk, monkeypatch, call, low, high, step):
+    """What call() reports as the workspace limit grows from `low` to `high` bytes: -1 (refused) or its number."""
+    got, limit = [], float(low)
+    while limit < high:
+        monkeypatch.setenv("HK_WORKSPACE_LIMIT", str(int(limit)))
+        try:
+            got.append(call())
+        except hk.HKError as e:
+            assert e.code == -3, e  # HK_ENOMEM
+            got.append(-1)
+        limit *= step
+    monkeypatch.delenv("HK_WORKSPACE_LIMIT")
+    return got
+
+
+def test_small_workspaces_take_the_lean_launches(hk, monkeypatch):
+    """Where a workspace with room for the resident launch or for the slices is refused
+    and one without is not, the solve runs without them and to the same solution."""
+    rowptr, col, val, b = dominant(5000, 15, 9)
+    arrays, bd = (dev(rowptr), dev(col), dev(val)), dev(b)
+    far = with_far_entries(*mesh_system((30, 29, 30), "q1")[:3], 9000, 1e-3)
+    bf, farrays = dev(mesh_system((30, 29, 30), "q1")[3]), tuple(dev(a) for a in far)
+    _, off, rp, c, v, bb = dominant_blocks([3000, 900, 20000], 15, 5)
+    barrays, bbd = (dev(rp), dev(c), dev(v)), dev(bb)
+    diag = col == np.repeat(np.arange(5000), np.diff(rowptr))
+    srp, scol, sval, _ = dominant(1000, 8, 3)
+    sdiag = scol == np.repeat(np.arange(1000), np.diff(srp))
+    B = np.zeros((1000, 64), dtype=np.complex128)
+    B[:] = np.random.default_rng(1).standard_normal((1000, 64))
+    sweep = (dev(srp), dev(scol), dev(np.where(sdiag, 1.0, sval.real)), dev(np.where(sdiag, 0.2, sval.imag)),
+             [complex(0.1 + 0.001 * j, 0.01) for j in range(64)], dev(B))
+    assert diag.any()
+    kept = {}
+
+    def single(arrays, b, first, autotune=False, **kw):
+        x, info = hk.krylov_solve(hk.CSR(*arrays, autotune=autotune), b, tol=1e-10, **kw)
+        y = kept.setdefault((first, autotune, str(kw)), x)
+        assert info["status"] == hk.HK_OK and torch.allclose(x, y, rtol=1e-6, atol=1e-8 * float(y.abs().max()))
+        return int(info["shape"][0] == first)
+
+    def mixed():
+        x, info = hk.krylov_solve_mixed(hk.CSR(*arrays), bd, outer_tol=1e-9)
+        assert info["status"] == hk.HK_OK
+        return int(info["shape"][0] == 1)
+
+    def batch():
+        x, infos = hk.blockdiag_solve(hk.CSR(*barrays), off, bbd, tol=1e-10)
+        assert all(i["status"] == hk.HK_OK for i in infos)
+        y = kept.setdefault("batch", x)
+        assert torch.allclose(x, y, rtol=1e-6, atol=1e-8)
+        return infos[0]["resident"]
+
+    def sweeps():
+        X, infos = hk.sweep_solve(*sweep, tol=1e-10)
+        assert all(i["status"] == hk.HK_OK for i in infos)
+        Y = kept.setdefault("sweep", X)
+        assert torch.allclose(X, Y, rtol=1e-6, atol=1e-8)
+        return infos[0]["resident"]
+
+    cases = [(f"{m}", lambda m=m, kw=kw: single(arrays, bd, 1, method=m, **kw), 4e5, 2e7, 1.1) for m, kw in METHODS]
+    cases += [("slices", lambda: single(farrays, bf, 2), 6e6, 3e7, 1.02), ("slices, tuned", lambda: single(farrays, bf, 2, True), 6e6, 3e7, 1.02),
+              ("mixed", mixed, 4e5, 2e7, 1.1), ("batch", batch, 1e6, 6e7, 1.1), ("sweep", sweeps, 1e6, 4e8, 1.3)]
+    for name, call, low, high, step in cases:
+        print("[case] workspace limits", name, flush=True)
+        got = outcomes(hk, monkeypatch, call, low, high, step)
+        if name == "slices, tuned":  # the tuner may prefer another shape
+            assert -1 in got and got == sorted(got) or 1 not in got, (name, got)
+        else:
+            assert got == sorted(got) and {-1, 0}.issubset(got) and got[-1] >= 1, (name, got)
