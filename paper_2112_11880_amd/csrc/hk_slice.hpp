@@ -24,12 +24,14 @@ constexpr int kSliceL = 2;
 constexpr int kSliceWaves = 4;
 
 // Sum of row 64 * slice + lane of values at val + 64 ptr[slice]: in the order of
-// the columns, the entries of a step and of what precedes the diagonal summed by
-// themselves, which keeps the largest partial sums from being rounded at each
-// entry (as in the resident rows: 1.6e-16 of 15 entries on a random vector, 1.7e-16
-// of 27, against 2.7e-16 and 3.5e-16 in one chain); complex64 in double, whose
-// conversions are free beside the loads.  `ptr` and `off` are read by scalar
-// loads.
+// the columns, a step's five products added up by themselves (the first three in a
+// chain), which keeps the sum of the row from being rounded at each entry: 1.65e-16
+// of 15 entries on a random vector and 1.73e-16 of 27, no more than the row blocks of
+// 32 and 16 rows that such systems had (one chain over the row: 2.7e-16 and
+// 3.5e-16).  A BiCGStab iteration on 1.8M rows takes 253 us, as with one chain
+// (252.7); a cut after the diagonal by scalar branches took 254.5.  complex64 in
+// double, whose conversions are free beside the loads.  `ptr` and `off` are read by
+// scalar loads.
 template <class V>
 __device__ __forceinline__ V slice_row(int slice, int n, const int* __restrict__ ptr, const int* __restrict__ off,
                                        const V* __restrict__ val, const V* __restrict__ x) {
@@ -41,24 +43,16 @@ __device__ __forceinline__ V slice_row(int slice, int n, const int* __restrict__
   auto col = [&](int d) { return min(max(r + d, 0), n - 1); };
   auto wide = [](V v) { return make_double2(v.x, v.y); };
   for (; j + U <= end; j += U) {
-    int d[U];
     V a[U], b[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) d[u] = off[j + u];
 #pragma unroll
     for (int u = 0; u < U; ++u) a[u] = ldnt(val + (size_t)(j + u) * kWave + l);
 #pragma unroll
-    for (int u = 0; u < U; ++u) b[u] = x[col(d[u])];
+    for (int u = 0; u < U; ++u) b[u] = x[col(off[j + u])];
     double2 part = cmul(wide(a[0]), wide(b[0]));
+    part = cfma(wide(a[1]), wide(b[1]), part);
+    part = cfma(wide(a[2]), wide(b[2]), part);
 #pragma unroll
-    for (int u = 1; u < U; ++u) {
-      if (d[u - 1] == 0) {  // the same for the whole wave
-        acc = cadd(acc, part);
-        part = cmul(wide(a[u]), wide(b[u]));
-      } else {
-        part = cfma(wide(a[u]), wide(b[u]), part);
-      }
-    }
+    for (int u = 3; u < U; ++u) part = cadd(part, cmul(wide(a[u]), wide(b[u])));
     acc = cadd(acc, part);
   }
   double2 rest = make_double2(0, 0);

@@ -51,7 +51,7 @@ def test_row_sums_round_no_more_than_row_blocks(hk, elem, far, first):
     solve to 1e-12 is left with: some thousand of them, so that it follows their
     size within a few percent.  On a random vector the row blocks of 32 rows
     round by 1.68e-16 (rows of 15 entries) and 1.95e-16 (27), the resident rows by
-    1.52e-16 and 1.71e-16, the slices of 27 by 1.72e-16, one chain of multiply-adds
+    1.52e-16 and 1.71e-16, the slices of 27 by 1.73e-16, one chain of multiply-adds
     by 2.7e-16 and 3.5e-16: ratios of 0.9 here, of 1.6 and 1.8 with one chain."""
     rowptr, col, val, b = mesh_system((30, 29, 30), elem)
     if far:  # 28 entries: not resident, products on slices
