@@ -461,7 +461,8 @@ def test_small_workspaces_take_the_lean_launches(hk, monkeypatch):
     for name, call, low, high, step in cases:
         print("[case] workspace limits", name, flush=True)
         got = outcomes(hk, monkeypatch, call, low, high, step)
-        if name == "slices, tuned":  # the tuner may prefer another shape
-            assert -1 in got and got == sorted(got) or 1 not in got, (name, got)
+        if name == "slices, tuned":  # each handle's tuner may prefer another shape
+            first = next(k for k, g in enumerate(got) if g >= 0)
+            assert first > 0 and -1 not in got[first:], (name, got)
         else:
             assert got == sorted(got) and {-1, 0}.issubset(got) and got[-1] >= 1, (name, got)
